@@ -74,10 +74,10 @@ static void fill_view(pndf_hier* h)
     d.clu_t = h->clu_t;
     d.clu_e = h->clu_e;
     d.clu_det = h->clu_det;
-    d.bbox_c = h->bbox_c;
-    d.bbox_u = h->bbox_u;
-    d.grp = h->grp;
-    d.bbox_k = h->bbox_k;
+    d.oct_k = h->oct_k;
+    d.oct_c = h->oct_c;
+    d.clu_em = h->clu_em;
+    d.nodes = (uint32_t)h->nodes;
     d.quad = h->quad;
     d.n = m->n;
     d.L = m->L;
@@ -236,7 +236,7 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
     for (int l = 1; l <= m->L; ++l) nodes += (int64_t)(m->n >> l) * (m->n >> l);
     h->nodes = nodes;
     hipError_t e = hipMalloc(&h->bbox, sizeof(float4) * nodes);
-    if (e == hipSuccess) e = hipMalloc(&h->bbox_k, sizeof(uint2) * nodes);
+    if (e == hipSuccess) e = hipMalloc(&h->oct_k, sizeof(uint4) * nodes);
     if (e == hipSuccess) e = hipMalloc(&h->quad, sizeof(QuadRec) * (size_t)(m->n >> 1) * (size_t)(m->n >> 1));
     if (cluster) {
         if (e == hipSuccess) e = hipMalloc(&h->bbox_all, sizeof(float4) * nodes);
@@ -245,10 +245,8 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
         if (e == hipSuccess) e = hipMalloc(&h->clu_det, sizeof(float2) * nodes);
         if (e == hipSuccess) e = hipMalloc(&h->clu_t, sizeof(float4) * 2 * nodes);
         if (e == hipSuccess) e = hipMalloc(&h->bbox_clu, sizeof(float4) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->bbox_c, sizeof(uint2) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->bbox_u, sizeof(uint2) * nodes);
-        // whole groups of four (the top level's single node fills one)
-        if (e == hipSuccess) e = hipMalloc(&h->grp, sizeof(uint4) * ((nodes + 3) & ~(int64_t)3));
+        if (e == hipSuccess) e = hipMalloc(&h->oct_c, sizeof(uint4) * 3 * nodes);
+        if (e == hipSuccess) e = hipMalloc(&h->clu_em, sizeof(float2) * nodes);
     }
     fill_view(h);
     if (e == hipSuccess) e = build_hierarchy_levels(h, (hipStream_t)stream);
@@ -256,9 +254,9 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
         pndf_destroy_hierarchy(h);
         return hip_fail(e, "pndf_build_hierarchy");
     }
-    // per node: bbox 16, bbox_k 8; with clusters bbox_all 16, bbox_clu 16, bbox_c 8, bbox_u 8,
-    // grp 16, clu_n 32, clu_t 32, clu_e 4, clu_det 8; plus the level-1 leaf records
-    h->bytes = (int64_t)nodes * (16 + 8 + (cluster ? 16 + 16 + 8 + 8 + 16 + 32 + 32 + 4 + 8 : 0)) +
+    // per node: bbox 16, oct_k 16; with clusters bbox_all 16, bbox_clu 16, oct_c 48, clu_em 8,
+    // clu_n 32, clu_t 32, clu_e 4, clu_det 8; plus the level-1 leaf records
+    h->bytes = (int64_t)nodes * (16 + 16 + (cluster ? 16 + 16 + 48 + 8 + 32 + 32 + 4 + 8 : 0)) +
                (int64_t)sizeof(QuadRec) * (m->n >> 1) * (m->n >> 1);
     *out = h;
     return PNDF_OK;
@@ -275,10 +273,9 @@ void pndf_destroy_hierarchy(pndf_hier* h)
     (void)hipFree(h->clu_det);
     (void)hipFree(h->clu_t);
     (void)hipFree(h->bbox_clu);
-    (void)hipFree(h->bbox_c);
-    (void)hipFree(h->bbox_u);
-    (void)hipFree(h->grp);
-    (void)hipFree(h->bbox_k);
+    (void)hipFree(h->oct_k);
+    (void)hipFree(h->oct_c);
+    (void)hipFree(h->clu_em);
     mesh_release(h->mesh);
     delete h;
 }

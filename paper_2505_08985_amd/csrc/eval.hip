@@ -64,6 +64,15 @@ __device__ __forceinline__ double confirm_and_term(const QuerySetup& q, const do
     return hit_weight<KER>(q, I, J, lev, half, e1 * rs, e2 * rs, logn) * (S * R);
 }
 
+// Twice the area of a triangle (a, b, c) = v as the build evaluates it (products
+// rounded before the difference).
+__device__ __forceinline__ double hit_jacobian(const double v[6])
+{
+#pragma clang fp contract(off)
+    const double p = (v[4] - v[0]) * (v[3] - v[1]), r = (v[5] - v[1]) * (v[2] - v[0]);
+    return fabs(p - r);
+}
+
 // Per-lane hit sink of one hit-processing round: value/count modes add the term to
 // the exact accumulator at once; record mode also keeps (id, term) until the wave
 // writes its records in lane order.
@@ -315,7 +324,7 @@ __device__ __forceinline__ void hit_entry(const HierDev& H, const QuerySetup& q,
     const int half = (int)(e & 1u);
     const uint32_t kind = e >> 30;
     double v[6];
-    float det_used;
+    bool clamped;
     int I, J, lev;
     if (kind == (kHitCluster >> 30)) {
         lev = (int)((e >> 25) & 0xfu);
@@ -324,9 +333,8 @@ __device__ __forceinline__ void hit_entry(const HierDev& H, const QuerySetup& q,
         I = (int)morton_compact(m);
         J = (int)morton_compact(m >> 1);
         const float4 a = H.clu_t[2 * idx], b = H.clu_t[2 * idx + 1];
-        const float2 dd = H.clu_det[idx];
-        det_used = half ? dd.y : dd.x;
-        if (clamp_bits(a, b) & (1u << half)) {
+        clamped = (clamp_bits(a, b) & (1u << half)) != 0u;
+        if (clamped) {
             eqtri_f64(0.5 * ((double)a.z + (double)b.x), 0.5 * ((double)a.w + (double)b.y),
                       (double)(H.rho * (float)(1 << lev)), v);
         } else if (half == 0) {
@@ -355,9 +363,8 @@ __device__ __forceinline__ void hit_entry(const HierDev& H, const QuerySetup& q,
             n0 = p[0]; n1 = p[1]; n2 = p[w]; n3 = p[w + 1];
             dg = H.deg[(int64_t)J * H.n + I];
         }
-        const float2 dd = H.det[(int64_t)J * H.n + I];
-        det_used = half ? dd.y : dd.x;
-        if (dg & (1u << half)) {
+        clamped = (dg & (1u << half)) != 0u;
+        if (clamped) {
             eqtri_f64(0.5 * ((double)n1.x + (double)n2.x), 0.5 * ((double)n1.y + (double)n2.y), (double)H.rho, v);
         } else if (half == 0) {
             v[0] = n0.x; v[1] = n0.y; v[2] = n1.x; v[3] = n1.y; v[4] = n2.x; v[5] = n2.y;
@@ -365,6 +372,9 @@ __device__ __forceinline__ void hit_entry(const HierDev& H, const QuerySetup& q,
             v[0] = n3.x; v[1] = n3.y; v[2] = n2.x; v[3] = n2.y; v[4] = n1.x; v[5] = n1.y;
         }
     }
+    // the Jacobian is formed again from the corners just read, bit for bit the stored
+    // one: each stored value is 8 scattered bytes, a whole line from memory per hit
+    const float det_used = clamped ? H.eps : (float)(hit_jacobian(v) * (1.0 / (double)(1u << (2 * lev))));
     const double t = confirm_and_term<KER>(q, v, I, J, lev, half, det_used, H.logn);
     if (t >= 0.0) hs.put(q, acc, tri_id(lev, I, J, half), t);
 }
@@ -399,24 +409,33 @@ __device__ __forceinline__ void queue_hits(uint32_t* hq, int& hn, uint32_t& pend
     wave_sync();
 }
 
-// Is the query normal inside a box stored as order keys (half_key) of its corners,
-// (min x | min y << 16, max x | max y << 16)?  The query's key is that of h rounded
-// to the nearest half: rounding is monotone, so a box that contains h contains it.
+// Is the query normal inside an octagon (HierDev)?  The query's keys are those of its
+// x, y, x + y and x - y rounded to the nearest half: rounding is monotone, so an
+// octagon whose set holds h holds it.  Each packed saturating difference is zero
+// where its two bounds hold, so one compare decides all eight.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ bool key_in_box(uint32_t hk, uint32_t lo, uint32_t hi)
+__device__ __forceinline__ uint32_t sub_sat2(uint32_t a, uint32_t b)
 {
-    const u16x2 h = __builtin_bit_cast(u16x2, hk);
-    const u16x2 a = __builtin_elementwise_max(h, __builtin_bit_cast(u16x2, lo));
-    const u16x2 c = __builtin_elementwise_min(h, __builtin_bit_cast(u16x2, hi));
-    return (__builtin_bit_cast(uint32_t, a) == hk) & (__builtin_bit_cast(uint32_t, c) == hk);
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+__device__ __forceinline__ bool in_octagon(const QuerySetup& q, uint4 o)
+{
+    return ((sub_sat2(o.x, q.hkey) | sub_sat2(q.hkey, o.y)) | (sub_sat2(o.z, q.hdiag) | sub_sat2(q.hdiag, o.w))) == 0u;
 }
 
-// Nodes under the cut from this level up are tested against the box of their own
-// cluster triangles before their cluster test.  Below it that box is about as wide
-// as the subtree's (about 60 % of level-1 cluster nodes whose subtree box holds h
-// also hold it in their own box, under 25 % from level 3) and the extra 32 B read
-// does not pay: from level 1 the scratched 4096^2 map took 7 % longer than from 2.
-constexpr int kOwnBoxLevel = 2;
+// With the cut, the octagon that decides about a node: under the cut (e^l <= t) only
+// its own two cluster triangles are tested, so theirs; a node whose children are all
+// under the cut can only lead to those children's cluster tests, so the union of
+// their own; else everything beneath.
+__device__ __forceinline__ uint32_t oct_class(bool cut, bool kids_cut)
+{
+    return cut ? kOctOwn : (kids_cut ? kOctKids : kOctSub);
+}
+__device__ __forceinline__ uint4 load_octagon(const HierDev& H, uint32_t cls, uint32_t node)
+{
+    // (a 32-bit byte offset: 3 x 22.4 M nodes x 16 B at 8192^2)
+    return *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(H.oct_c) + (cls * H.nodes + node) * 16u);
+}
 
 // Cluster queue entry: level (4 bits) << 24 | Morton code of the node (< 2^24).
 constexpr int kCluShift = 24;
@@ -491,36 +510,21 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
     } else {
         bool ok = root_ok;
         const uint32_t m = root_item & kCodeMask;
-        const int64_t idx = level_offset(H.logn, root_level) + m;
+        const uint32_t idx = (uint32_t)level_offset(H.logn, root_level) + m;
+        bool cut = false, kids_cut = false;
+        if (CUT && ok) {
+            const float2 em = H.clu_em[idx];
+            cut = em.x <= q.t;
+            kids_cut = em.y <= q.t;
+        }
         if (ok && !roots_tested) {
-            // the node's box as order keys: of the map triangles, or under the cut of the
-            // map and cluster triangles (from its group record)
             acc.nodes += 1;
-            const uint2 b = CUT ? reinterpret_cast<const uint2*>(H.grp + (idx & ~(int64_t)3))[idx & 3] : H.bbox_k[idx];
-            ok = key_in_box(q.hkey, b.x, b.y);
+            ok = in_octagon(q, CUT ? load_octagon(H, oct_class(cut, kids_cut), idx) : H.oct_k[idx]);
         }
-        bool cut = false;
-        // (e^l from the node's group record, the one the root's key test reads; taking it
-        // there rather than from the per-node e^l array keeps one array pointer out of the
-        // kernel, whose scalar registers are at their limit)
-        if (CUT && ok &&
-            __uint_as_float(reinterpret_cast<const uint32_t*>(H.grp)[4 * (idx & ~(int64_t)3) + 8 + (idx & 3)]) <= q.t) {
-            cut = true;
-            if (root_level >= kOwnBoxLevel) {
-                // under the cut only the node's own two cluster triangles are tested:
-                // their box (inside the subtree's) decides
-                const uint2 c = H.bbox_c[idx];
-                ok = cut = key_in_box(q.hkey, c.x, c.y);
-            }
-        }
+        cut = cut && ok;
         const uint64_t bl = __ballot(ok && !cut);
-        if (ok && !cut) {
-            uint32_t item = root_item;
-            if (CUT && root_level >= 2 &&
-                __uint_as_float(reinterpret_cast<const uint32_t*>(H.grp)[4 * (idx & ~(int64_t)3) + 12 + (idx & 3)]) <= q.t)
-                item |= kAllCut;
-            nl.put(root_level, __popcll(bl & ((1ull << lane) - 1ull)), item);
-        }
+        if (ok && !cut)
+            nl.put(root_level, __popcll(bl & ((1ull << lane) - 1ull)), root_item | (kids_cut ? kAllCut : 0u));
         if (CUT) {
             const uint64_t bc = __ballot(cut);
             if (cut) cq[__popcll(bc & ((1ull << lane) - 1ull))] = ((uint32_t)root_level << kCluShift) | m;
@@ -645,40 +649,38 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
                 pend = leaf_quad_mask(H, q, m, inside, rx0, ry0, acc);
                 ebase = m << 3;
             } else {
-                // the four child boxes are one Morton segment (32 B of keys): loaded
-                // whole, children outside the support masked afterwards.  With the cut,
-                // the group record (64 B: their keys, residuals and their children's
-                // largest residuals), or for a node whose children are all under the
-                // cut only the boxes they are tested against.
-                const int64_t c0 = level_offset(H.logn, l - 1) + 4 * (int64_t)m;
-                // every load is issued before any is used (one memory round trip per
-                // expansion): the boxes, then with the cut the residual words
-                const bool allc = CUT && (entry & kAllCut) != 0u;
-                const uint4* kp = !CUT ? reinterpret_cast<const uint4*>(H.bbox_k + c0)
-                                  : (allc && l - 1 >= kOwnBoxLevel) ? reinterpret_cast<const uint4*>(H.bbox_c + c0)
-                                                                    : H.grp + c0;
-                const uint4 b01 = kp[0], b23 = kp[1];
-                uint4 u01 = make_uint4(0u, 0xffffffffu, 0u, 0xffffffffu), u23 = u01;
+                // the four children are one Morton segment; children outside the support
+                // are masked afterwards.  Without the cut their octagons (64 B) are read
+                // at once.  With it, first their residuals and their children's largest
+                // (32 B, four sibling groups to a line) unless all are known to be under
+                // the cut, then for each child the one octagon that decides about it: a
+                // second round trip, but 96 B at most instead of the three boxes of every
+                // child, and from level 3 up mostly one class for the whole group.
+                const uint32_t c0 = (uint32_t)level_offset(H.logn, l - 1) + 4u * m;
+                uint4 o0, o1, o2, o3;
                 if (CUT) {
-                    uint4 w2 = make_uint4(0u, 0u, 0u, 0u), w3 = w2;
-                    if (!allc) {
-                        w2 = H.grp[c0 + 2];
-                        w3 = H.grp[c0 + 3];
-                        if (l - 1 >= 3) {
-                            // the children's union boxes, for those whose own children
-                            // all turn out to be under the cut
-                            const uint4* up = reinterpret_cast<const uint4*>(H.bbox_u + c0);
-                            u01 = up[0];
-                            u23 = up[1];
-                        }
+                    uint32_t k0 = kOctOwn, k1 = kOctOwn, k2 = kOctOwn, k3 = kOctOwn;
+                    cut4 = 0xfu;
+                    if (!(entry & kAllCut)) {
+                        const float4* ep = reinterpret_cast<const float4*>(
+                            reinterpret_cast<const char*>(H.clu_em) + c0 * 8u);
+                        const float4 ea = ep[0], eb = ep[1];
+                        cut4 = (uint32_t)(ea.x <= q.t) | ((uint32_t)(ea.z <= q.t) << 1) |
+                               ((uint32_t)(eb.x <= q.t) << 2) | ((uint32_t)(eb.z <= q.t) << 3);
+                        all4 = (uint32_t)(ea.y <= q.t) | ((uint32_t)(ea.w <= q.t) << 1) |
+                               ((uint32_t)(eb.y <= q.t) << 2) | ((uint32_t)(eb.w <= q.t) << 3);
+                        k0 = oct_class(ea.x <= q.t, ea.y <= q.t);
+                        k1 = oct_class(ea.z <= q.t, ea.w <= q.t);
+                        k2 = oct_class(eb.x <= q.t, eb.y <= q.t);
+                        k3 = oct_class(eb.z <= q.t, eb.w <= q.t);
                     }
-                    const float4 ce = __builtin_bit_cast(float4, w2), cm = __builtin_bit_cast(float4, w3);
-                    cut4 = allc ? 0xfu
-                                : (uint32_t)(ce.x <= q.t) | ((uint32_t)(ce.y <= q.t) << 1) |
-                                      ((uint32_t)(ce.z <= q.t) << 2) | ((uint32_t)(ce.w <= q.t) << 3);
-                    all4 = allc ? 0u
-                                : (uint32_t)(cm.x <= q.t) | ((uint32_t)(cm.y <= q.t) << 1) |
-                                      ((uint32_t)(cm.z <= q.t) << 2) | ((uint32_t)(cm.w <= q.t) << 3);
+                    o0 = load_octagon(H, k0, c0);
+                    o1 = load_octagon(H, k1, c0 + 1);
+                    o2 = load_octagon(H, k2, c0 + 2);
+                    o3 = load_octagon(H, k3, c0 + 3);
+                } else {
+                    const uint4* op = reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(H.oct_k) + c0 * 16u);
+                    o0 = op[0]; o1 = op[1]; o2 = op[2]; o3 = op[3];
                 }
                 uint32_t ov = 0xfu;  // children meeting the support box
                 cin = 0xfu;
@@ -691,33 +693,8 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
                     cin = quad_bits(pair_in_run(I, rx.ai, rx.ni, mk), pair_in_run(J, ry.ai, ry.ni, mk));
                 }
                 tested = (uint32_t)__popc(ov);
-                chm = ((uint32_t)key_in_box(q.hkey, b01.x, b01.y) | ((uint32_t)key_in_box(q.hkey, b01.z, b01.w) << 1) |
-                       ((uint32_t)key_in_box(q.hkey, b23.x, b23.y) << 2) |
-                       ((uint32_t)key_in_box(q.hkey, b23.z, b23.w) << 3)) & ov;
-                if (CUT && all4) {
-                    // a child whose children are all under the cut, none of whose
-                    // children's own boxes holds h, would only test clusters that
-                    // cannot hit: it is not pushed
-                    const uint32_t uin = (uint32_t)key_in_box(q.hkey, u01.x, u01.y) |
-                                         ((uint32_t)key_in_box(q.hkey, u01.z, u01.w) << 1) |
-                                         ((uint32_t)key_in_box(q.hkey, u23.x, u23.y) << 2) |
-                                         ((uint32_t)key_in_box(q.hkey, u23.z, u23.w) << 3);
-                    // (from level 3, where the union keys are read: a second box test each)
-                    const uint32_t utested = l - 1 >= 3 ? all4 & ~cut4 & chm : 0u;
-                    tested += (uint32_t)__popc(utested);
-                    chm &= ~(utested & ~uin);
-                }
-                if (CUT && !(entry & kAllCut) && l - 1 >= kOwnBoxLevel && (chm & cut4)) {
-                    // children under the cut: the box of their own cluster triangles
-                    // (inside the subtree's box) decides instead, another 32 B segment
-                    const uint4* cc = reinterpret_cast<const uint4*>(H.bbox_c + c0);
-                    const uint4 c01 = cc[0], c23 = cc[1];
-                    const uint32_t own = (uint32_t)key_in_box(q.hkey, c01.x, c01.y) |
-                                         ((uint32_t)key_in_box(q.hkey, c01.z, c01.w) << 1) |
-                                         ((uint32_t)key_in_box(q.hkey, c23.x, c23.y) << 2) |
-                                         ((uint32_t)key_in_box(q.hkey, c23.z, c23.w) << 3);
-                    chm &= ~cut4 | own;
-                }
+                chm = ((uint32_t)in_octagon(q, o0) | ((uint32_t)in_octagon(q, o1) << 1) |
+                       ((uint32_t)in_octagon(q, o2) << 2) | ((uint32_t)in_octagon(q, o3) << 3)) & ov;
                 m4 = 4 * m;
             }
         }

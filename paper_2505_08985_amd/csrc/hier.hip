@@ -202,7 +202,86 @@ __device__ __forceinline__ float4 empty_box()
     return make_float4(INFINITY, INFINITY, -INFINITY, -INFINITY);
 }
 
+// ---- octagons (see HierDev): bounds of x, y, u = x + y, v = x - y.  u and v are
+// taken in FP64 and every bound is rounded outward to half precision, so unions of
+// octagons are exact on the keys.
+struct Oct {
+    float4 b;        // min x, min y, max x, max y
+    double ul, vl, uh, vh;
+};
+
+__device__ __forceinline__ Oct empty_oct()
+{
+    return Oct{empty_box(), (double)INFINITY, (double)INFINITY, -(double)INFINITY, -(double)INFINITY};
+}
+
+__device__ __forceinline__ void oct_add_diag(Oct& o, double u, double v, double r)
+{
+    o.ul = fmin(o.ul, u - r); o.vl = fmin(o.vl, v - r);
+    o.uh = fmax(o.uh, u + r); o.vh = fmax(o.vh, v + r);
+}
+
+__device__ __forceinline__ void oct_add(Oct& o, float x, float y)
+{
+    box_add(o.b, x, y);
+    oct_add_diag(o, (double)x + (double)y, (double)x - (double)y, 0.0);
+}
+
+// A replacement triangle lies in the disk of its circumradius rho, sqrt(2) rho wide
+// along a diagonal; the margin as in box_add_eqtri.
+__device__ __forceinline__ void oct_add_eqtri(Oct& o, float cx, float cy, float rho)
+{
+    box_add_eqtri(o.b, cx, cy, rho);
+    oct_add_diag(o, (double)cx + (double)cy, (double)cx - (double)cy, 1.4142136 * ((double)rho * (1.0 + 1e-6) + 1e-6));
+}
+
+// keys of a pair of minima (rounded down) or maxima (rounded up); the zeros: a
+// minimum of +0 becomes -0, a maximum of -0 becomes +0
+__device__ __forceinline__ uint32_t min_keys(float a, float b)
+{
+    uint32_t x = __half_as_ushort(__float2half_rd(a)), y = __half_as_ushort(__float2half_rd(b));
+    if (x == 0u) x = 0x8000u;
+    if (y == 0u) y = 0x8000u;
+    return half_key(x) | (half_key(y) << 16);
+}
+
+__device__ __forceinline__ uint32_t max_keys(float a, float b)
+{
+    uint32_t x = __half_as_ushort(__float2half_ru(a)), y = __half_as_ushort(__float2half_ru(b));
+    if (x == 0x8000u) x = 0u;
+    if (y == 0x8000u) y = 0u;
+    return half_key(x) | (half_key(y) << 16);
+}
+
+__device__ __forceinline__ uint4 oct_keys(const Oct& o)
+{
+    return make_uint4(min_keys(o.b.x, o.b.y), max_keys(o.b.z, o.b.w),
+                      min_keys(__double2float_rd(o.ul), __double2float_rd(o.vl)),
+                      max_keys(__double2float_ru(o.uh), __double2float_ru(o.vh)));
+}
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint4 oct_union(uint4 a, uint4 b)
+{
+    auto lo = [](uint32_t p, uint32_t q) {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, p), __builtin_bit_cast(u16x2, q)));
+    };
+    auto hi = [](uint32_t p, uint32_t q) {
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, p), __builtin_bit_cast(u16x2, q)));
+    };
+    return make_uint4(lo(a.x, b.x), hi(a.y, b.y), lo(a.z, b.z), hi(a.w, b.w));
+}
+
+__device__ __forceinline__ uint4 oct_union4(const uint4* c)
+{
+    return oct_union(oct_union(c[0], c[1]), oct_union(c[2], c[3]));
+}
+
 struct LevelOut {
+    uint4* oct_k;    // octagons of this level (HierDev::oct_k and the three of oct_c)
+    uint4* oct_s;
+    uint4* oct_o;
+    uint4* oct_u;
     float4* bbox;
     float4* bbox_all;
     float4* bbox_clu;
@@ -215,8 +294,8 @@ struct LevelOut {
 // Store the fitted normals of node idx (level side s): float32 normals, the cluster
 // triangles' Jacobians and clamp decisions (FP64 from the stored float32 normals, as
 // the evaluation uses them) with the test record that carries them, the FP64 normals
-// for the residual pass; returns the box of the cluster triangles.
-__device__ float4 store_cluster(const HierDev& H, const LevelOut& o, int64_t idx, int s, const double N[4][2],
+// for the residual pass; returns the octagon of the cluster triangles.
+__device__ Oct store_cluster(const HierDev& H, const LevelOut& o, int64_t idx, int s, const double N[4][2],
                                 double* __restrict__ nfit)
 {
     float2 f[4];
@@ -234,13 +313,13 @@ __device__ float4 store_cluster(const HierDev& H, const LevelOut& o, int64_t idx
     const float qnan = __int_as_float(0x7fc00000);
     o.clu_t[2 * idx] = make_float4(cl ? qnan : f[0].x, f[0].y, f[1].x, f[1].y);
     o.clu_t[2 * idx + 1] = make_float4(f[2].x, f[2].y, cu ? qnan : f[3].x, f[3].y);
-    float4 b = empty_box();
+    Oct b = empty_oct();
     const float cx = 0.5f * (f[1].x + f[2].x), cy = 0.5f * (f[1].y + f[2].y);
     const float rho = H.rho * (float)s;
-    if (cl) box_add_eqtri(b, cx, cy, rho);
-    else { box_add(b, f[0].x, f[0].y); box_add(b, f[1].x, f[1].y); box_add(b, f[2].x, f[2].y); }
-    if (cu) box_add_eqtri(b, cx, cy, rho);
-    else { box_add(b, f[3].x, f[3].y); box_add(b, f[2].x, f[2].y); box_add(b, f[1].x, f[1].y); }
+    if (cl) oct_add_eqtri(b, cx, cy, rho);
+    else { oct_add(b, f[0].x, f[0].y); oct_add(b, f[1].x, f[1].y); oct_add(b, f[2].x, f[2].y); }
+    if (cu) oct_add_eqtri(b, cx, cy, rho);
+    else { oct_add(b, f[3].x, f[3].y); oct_add(b, f[2].x, f[2].y); oct_add(b, f[1].x, f[1].y); }
     return b;
 }
 
@@ -264,19 +343,21 @@ __global__ void k_level1(HierDev H, LevelOut o, QuadRec* __restrict__ quad, doub
         r.pad = 0;
         quad[t] = r;
     }
-    float4 box = empty_box();
+    Oct box = empty_oct();
     for (int dj = 0; dj < 2; ++dj)
         for (int di = 0; di < 2; ++di) {
             const int k = 3 * dj + di;
             const float2 n0 = tx[k], n1 = tx[k + 1], n2 = tx[k + 3], n3 = tx[k + 4];
             const uint8_t dg = H.deg[(int64_t)(2 * J + dj) * H.n + 2 * I + di];
             const float cx = 0.5f * (n1.x + n2.x), cy = 0.5f * (n1.y + n2.y);
-            if (dg & 1) box_add_eqtri(box, cx, cy, H.rho);
-            else { box_add(box, n0.x, n0.y); box_add(box, n1.x, n1.y); box_add(box, n2.x, n2.y); }
-            if (dg & 2) box_add_eqtri(box, cx, cy, H.rho);
-            else { box_add(box, n3.x, n3.y); box_add(box, n2.x, n2.y); box_add(box, n1.x, n1.y); }
+            if (dg & 1) oct_add_eqtri(box, cx, cy, H.rho);
+            else { oct_add(box, n0.x, n0.y); oct_add(box, n1.x, n1.y); oct_add(box, n2.x, n2.y); }
+            if (dg & 2) oct_add_eqtri(box, cx, cy, H.rho);
+            else { oct_add(box, n3.x, n3.y); oct_add(box, n2.x, n2.y); oct_add(box, n1.x, n1.y); }
         }
-    o.bbox[t] = box;
+    o.bbox[t] = box.b;
+    const uint4 map_keys = oct_keys(box);
+    o.oct_k[t] = map_keys;
     if (!cluster) return;
     const double eps = (double)H.eps;
     // the 8 fine triangles (cell c4 = di + 2 dj: lower (n0, n1, n2), upper (n3, n2, n1))
@@ -296,17 +377,23 @@ __global__ void k_level1(HierDev H, LevelOut o, QuadRec* __restrict__ quad, doub
     for (int k = 0; k < kStat; ++k) { M[k] = lo[k]; M[kStat + k] = up[k]; }
     double N[4][2];
     solve_cluster(lo, up, N);
-    float4 cb = store_cluster(H, o, t, 2, N, nfit);
+    const Oct own = store_cluster(H, o, t, 2, N, nfit);
+    const uint4 own_keys = oct_keys(own);
+    float4 cb = own.b;
     o.bbox_clu[t] = cb;
-    box_union(cb, box);
+    box_union(cb, box.b);
     o.bbox_all[t] = cb;
+    o.oct_o[t] = own_keys;
+    o.oct_s[t] = oct_union(own_keys, map_keys);
+    // (a level-1 node's children are cells: never asked for, excludes nothing)
+    o.oct_u[t] = make_uint4(0u, 0xffffffffu, 0u, 0xffffffffu);
 }
 
-// Level l >= 2 from level l-1: boxes are unions of the children, half statistics
-// gathered from the children's.  Thread index = Morton code; the children of node
+// Level l >= 2 from level l-1 (co: its arrays): boxes and octagons are unions of the
+// children's, half statistics gathered from the children's.  Thread index = Morton code; the children of node
 // t are 4t + (di + 2 dj).
 __global__ void k_level_up(HierDev H, int level, LevelOut o, const float4* __restrict__ cbox,
-                           const float4* __restrict__ cbox_all, const double* __restrict__ cstat,
+                           const float4* __restrict__ cbox_all, LevelOut co, const double* __restrict__ cstat,
                            double* __restrict__ stat, double* __restrict__ nfit, int cluster)
 {
     const int m = H.n >> level;
@@ -318,6 +405,7 @@ __global__ void k_level_up(HierDev H, int level, LevelOut o, const float4* __res
     box_union(box, cbox[c00 + 2]);
     box_union(box, cbox[c00 + 3]);
     o.bbox[t] = box;
+    o.oct_k[t] = oct_union4(co.oct_k + c00);
     if (!cluster) return;
     double lo[kStat] = {0}, up[kStat] = {0};
     gather_children([&](int c4, int h) { return cstat + (c00 + c4) * (2 * kStat) + h * kStat; }, lo, up);
@@ -325,7 +413,12 @@ __global__ void k_level_up(HierDev H, int level, LevelOut o, const float4* __res
     for (int k = 0; k < kStat; ++k) { M[k] = lo[k]; M[kStat + k] = up[k]; }
     double N[4][2];
     solve_cluster(lo, up, N);
-    float4 cb = store_cluster(H, o, t, 1 << level, N, nfit);
+    const Oct own = store_cluster(H, o, t, 1 << level, N, nfit);
+    const uint4 own_keys = oct_keys(own);
+    o.oct_o[t] = own_keys;
+    o.oct_s[t] = oct_union(own_keys, oct_union4(co.oct_s + c00));
+    o.oct_u[t] = oct_union4(co.oct_o + c00);
+    float4 cb = own.b;
     o.bbox_clu[t] = cb;
     box_union(cb, cbox_all[c00]);
     box_union(cb, cbox_all[c00 + 1]);
@@ -448,73 +541,20 @@ hipError_t export_rowmajor(const void* src, void* dst, int m, int words, hipStre
     return hipGetLastError();
 }
 
-// The traversal's boxes in half precision, minima rounded down and maxima up, as
-// order keys (half_key): a rounded box contains the exact one, so it prunes a little
-// less but never wrongly; four child boxes take 32 B instead of 64 and each test is
-// two packed 16-bit integer operations (the float32 boxes stay for the exports).
-__device__ __forceinline__ uint2 box_keys(float4 b)
-{
-    uint32_t x0 = __half_as_ushort(__float2half_rd(b.x)), y0 = __half_as_ushort(__float2half_rd(b.y));
-    uint32_t x1 = __half_as_ushort(__float2half_ru(b.z)), y1 = __half_as_ushort(__float2half_ru(b.w));
-    // the zeros: a minimum of +0 becomes -0, a maximum of -0 becomes +0
-    if (x0 == 0u) x0 = 0x8000u;
-    if (y0 == 0u) y0 = 0x8000u;
-    if (x1 == 0x8000u) x1 = 0u;
-    if (y1 == 0x8000u) y1 = 0u;
-    return make_uint2(half_key(x0) | (half_key(y0) << 16), half_key(x1) | (half_key(y1) << 16));
-}
-
-__global__ void k_key_boxes(const float4* __restrict__ src, uint2* __restrict__ dst, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    dst[i] = box_keys(src[i]);
-}
-
-// Keys of a box that contains every normal (minimum key 0, maximum key 0xffff).
-__global__ void k_fill_keys_all(uint2* __restrict__ dst, int64_t n)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    dst[i] = make_uint2(0u, 0xffffffffu);
-}
-
-// Union keys (HierDev::bbox_u) of one level l >= 3: the box of the node's four
-// children's own cluster triangles.  A node whose children are all under the cut
-// is skipped when this box misses h: none of their cluster tests could hit.
-__global__ void k_union_keys(HierDev H, int level, const float4* __restrict__ bbox_clu, uint2* __restrict__ dst)
-{
-    const int64_t m = (int64_t)(H.n >> level) * (H.n >> level);
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= m) return;
-    const float4* c = bbox_clu + level_offset(H.logn, level - 1) + 4 * t;
-    float4 u = c[0];
-    box_union(u, c[1]);
-    box_union(u, c[2]);
-    box_union(u, c[3]);
-    dst[level_offset(H.logn, level) + t] = box_keys(u);
-}
-
-// The cut traversal's sibling-group records (HierDev::grp) of one level: thread t
-// writes node t's words (its keys are those of bbox_all, as k_key_boxes forms them).
-__global__ void k_group_records(HierDev H, int level, uint32_t* __restrict__ grp)
+// e^l and the largest e^l of the four children side by side (HierDev::clu_em) of one
+// level: an expansion reads its four children's in one 32 B segment.
+__global__ void k_residual_pairs(HierDev H, int level, float2* __restrict__ em)
 {
     const int64_t m = (int64_t)(H.n >> level) * (H.n >> level);
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= m) return;
     const int64_t idx = level_offset(H.logn, level) + t;
-    uint32_t* w = grp + 4 * (idx & ~(int64_t)3);   // 16 words per group
-    const int c = (int)(idx & 3);
-    const uint2 k = box_keys(H.bbox_all[idx]);
-    w[2 * c] = k.x;
-    w[2 * c + 1] = k.y;
-    w[8 + c] = __float_as_uint(H.clu_e[idx]);
-    float emc = INFINITY;
+    float kids = INFINITY;
     if (level >= 2) {
         const float* ce = H.clu_e + level_offset(H.logn, level - 1) + 4 * t;
-        emc = fmaxf(fmaxf(ce[0], ce[1]), fmaxf(ce[2], ce[3]));
+        kids = fmaxf(fmaxf(ce[0], ce[1]), fmaxf(ce[2], ce[3]));
     }
-    w[12 + c] = __float_as_uint(emc);
+    em[idx] = make_float2(H.clu_e[idx], kids);
 }
 
 hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
@@ -550,6 +590,10 @@ hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
         LevelOut o;
         const int64_t off = level_offset(H.logn, level);
         o.bbox = h->bbox + off;
+        o.oct_k = h->oct_k + off;
+        o.oct_s = h->cluster ? h->oct_c + kOctSub * h->nodes + off : nullptr;
+        o.oct_o = h->cluster ? h->oct_c + kOctOwn * h->nodes + off : nullptr;
+        o.oct_u = h->cluster ? h->oct_c + kOctKids * h->nodes + off : nullptr;
         o.bbox_all = h->cluster ? h->bbox_all + off : nullptr;
         o.bbox_clu = h->cluster ? h->bbox_clu + off : nullptr;
         o.clu_n = h->cluster ? h->clu_n + 2 * off : nullptr;
@@ -582,30 +626,13 @@ hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
         double* os = stat[(level - 1) & 1];
         hipLaunchKernelGGL(k_level_up, dim3((unsigned)((m + bs - 1) / bs)), dim3(bs), 0, s, H,
                            level, out_for(level), h->bbox + coff,
-                           h->cluster ? h->bbox_all + coff : nullptr, cs, os, nfit, h->cluster);
+                           h->cluster ? h->bbox_all + coff : nullptr, out_for(level - 1), cs, os, nfit, h->cluster);
         err = hipGetLastError();
         if (err == hipSuccess && h->cluster) err = residual(level);
     }
-    if (err == hipSuccess) {
-        const unsigned g = (unsigned)((h->nodes + 255) / 256);
-        hipLaunchKernelGGL(k_key_boxes, dim3(g), dim3(256), 0, s, h->bbox, h->bbox_k, h->nodes);
-        if (h->cluster) {
-            hipLaunchKernelGGL(k_key_boxes, dim3(g), dim3(256), 0, s, h->bbox_clu, h->bbox_c, h->nodes);
-            // (levels 1 and 2 keep the all-inclusive box: their children's own boxes are
-            // not what those children are tested against)
-            hipLaunchKernelGGL(k_fill_keys_all, dim3(g), dim3(256), 0, s, h->bbox_u, h->nodes);
-            for (int level = 3; level <= H.L; ++level) {
-                const int64_t m = (int64_t)(n >> level) * (n >> level);
-                hipLaunchKernelGGL(k_union_keys, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, H, level,
-                                   h->bbox_clu, h->bbox_u);
-            }
-            // (the top level's group holds one node: its other words are never read)
-            for (int level = 1; level <= H.L; ++level) {
-                const int64_t m = (int64_t)(n >> level) * (n >> level);
-                hipLaunchKernelGGL(k_group_records, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, H, level,
-                                   reinterpret_cast<uint32_t*>(h->grp));
-            }
-        }
+    for (int level = 1; level <= H.L && err == hipSuccess && h->cluster; ++level) {
+        const int64_t m = (int64_t)(n >> level) * (n >> level);
+        hipLaunchKernelGGL(k_residual_pairs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, H, level, h->clu_em);
         err = hipGetLastError();
     }
     if (err == hipSuccess) err = hipStreamSynchronize(s);

@@ -92,14 +92,14 @@ struct HierDev {
     const float2* det;      // n x n Jacobians used by the evaluation (lower, upper)
     const float4* bbox;     // all levels packed: min x, min y, max x, max y (map triangles)
     const float4* bbox_all; // same, extended by cluster triangles (nullptr without clusters)
-    const uint2* bbox_k;    // bbox as order keys of halves rounded outward (min down, max up): see half_key
-    const uint2* bbox_c;    // the node's own two cluster triangles' box, the same way
-    const uint2* bbox_u;    // from level 3: the union of its four children's own boxes (bbox_c), the same way
-    // (clusters) one 64 B record per group of four sibling nodes 4k..4k+3, in 16 B
-    // words: their bbox_all as keys like bbox_k (two nodes per word), their e^l, and
-    // per node the largest e^l of its four children (+inf at level 1): what the cut
-    // traversal reads when it expands their parent
-    const uint4* grp;
+    // octagons of the traversal (see Octagon): oct_k the map triangles beneath the node
+    // (tau = 0); with clusters oct_c holds three arrays of `nodes` octagons, indexed
+    // cls * nodes + node: kOctSub the map and cluster triangles beneath the node,
+    // kOctOwn its own two cluster triangles, kOctKids (from level 2) the union of its
+    // four children's kOctOwn
+    const uint4* oct_k;
+    const uint4* oct_c;
+    const float2* clu_em;   // per node e^l and the largest e^l of its four children (+inf at level 1)
     // the cluster test record, 2 float4 per node: (N0.x, N0.y, N1.x, N1.y), (N2.x,
     // N2.y, N3.x, N3.y), except that a clamped triangle's free vertex (N0 of the
     // lower, N3 of the upper: its replacement is built from the shared edge N1 N2
@@ -108,6 +108,7 @@ struct HierDev {
     const float* clu_e;     // e^l per node
     const float2* clu_det;  // cluster triangle Jacobians (lower, upper), eps when clamped
     const QuadRec* quad;    // level-1 leaf records (Morton order)
+    uint32_t nodes;         // nodes of all levels
     int n, L, logn;
     float eps;
     float rho;              // circumradius of the clamp replacement triangle (area eps / 2)
@@ -122,14 +123,28 @@ __device__ __forceinline__ uint32_t clamp_bits(float4 a, float4 b)
 }
 
 // Order key of a half-precision value (IEEE binary16 bits): unsigned keys compare
-// like the values (negative values mirrored below 0x8000, zero signs aside), so a
-// box test is two packed 16-bit integer min / max operations.  Box keys are
-// normalised so that the two zeros never exclude: a minimum of +0 is stored as -0
-// (key 0x7fff) and a maximum of -0 as +0 (key 0x8000).
+// like the values (negative values mirrored below 0x8000, zero signs aside), so
+// bounds are tested two at a time with packed 16-bit integer operations.  Octagon
+// bounds are normalised so that the two zeros never exclude: a minimum of +0 is
+// stored as -0 (key 0x7fff) and a maximum of -0 as +0 (key 0x8000).
 __host__ __device__ __forceinline__ uint32_t half_key(uint32_t bits)
 {
     return (bits & 0x8000u) ? (~bits & 0xffffu) : (bits | 0x8000u);
 }
+
+// Octagon of a set of normals (16 B): the bounds of x, y, u = x + y and v = x - y,
+// each rounded outward to half precision and stored as order keys,
+//   .x = min x | min y << 16, .y = max x | max y << 16, .z = min u | min v << 16,
+//   .w = max u | max v << 16.
+// The two diagonal slabs cut the corners that an axis-aligned box leaves empty: on
+// the power-law maps a descent expands 26 % fewer nodes than with boxes, on the
+// scratched maps, whose grooves put a node's normals along a slanted line, 28 to
+// 36 % fewer and tests 45 % fewer clusters and leaf records (counted on the CPU,
+// 2048^2 maps).  2^20 queries of sigma 1 to 64 on the 2048^2 power-law map, tau = 0:
+// 8.93 -> 7.67 ms; 2^21 of sigma 1 to 8192 at 8192^2, tau = 1e-3: 108 -> 97 ms (both
+// with the hit stage's Jacobians formed instead of read).  Rounding is monotone: u and v are rounded to FP64 both here and for
+// the query's normal, so an octagon never excludes a normal of its set.
+enum { kOctSub = 0, kOctOwn = 1, kOctKids = 2 };
 
 // First node of level l (1 <= l <= logn + 1) in the packed per-level arrays: the
 // levels below hold sum_{k=1}^{l-1} (n / 2^k)^2 = (n^2 - (n / 2^(l-1))^2) / 3 nodes.
@@ -261,11 +276,10 @@ struct pndf_hier {
     int64_t nodes = 0;
     float4* bbox = nullptr;
     float4* bbox_all = nullptr;
-    uint2* bbox_k = nullptr;
+    uint4* oct_k = nullptr;
+    uint4* oct_c = nullptr;       // 3 x nodes (kOctSub, kOctOwn, kOctKids)
+    float2* clu_em = nullptr;
     float4* bbox_clu = nullptr;   // box of the node's own cluster triangles (float32)
-    uint2* bbox_c = nullptr;
-    uint2* bbox_u = nullptr;
-    uint4* grp = nullptr;
     float4* clu_n = nullptr;      // the fitted normals as float32 (exported; the kernels read clu_t)
     float4* clu_t = nullptr;
     float* clu_e = nullptr;
@@ -362,7 +376,7 @@ struct QuerySetup {
     int cxlo, cxhi, cylo, cyhi;  // included unrolled cell range per axis
     int l0;                      // entry level
     float t;                     // cut threshold fl(fl(rx ry) tau)
-    uint32_t hkey;               // order keys (half_key) of h rounded to halves: x | y << 16
+    uint32_t hkey, hdiag;        // order keys (half_key) of h rounded to halves: x | y << 16, x + y | x - y << 16
     double kx, ky;               // Gaussian: log2(e) / (2 sigma^2)
     double norm;                 // the kernel's peak: 1 / (2 pi sx sy), 1 / (pi rx ry) or 1 / (4 rx ry)
     int fexp;                    // binary point of the exact accumulator (units of 2^fexp)
@@ -386,6 +400,9 @@ __device__ inline QuerySetup setup_query(const pndf_query& qr, float s2r, float 
     q.ry = ry;
     q.hkey = half_key(__half_as_ushort(__float2half_rn(qr.hx))) |
              (half_key(__half_as_ushort(__float2half_rn(qr.hy))) << 16);
+    const double hu = (double)qr.hx + (double)qr.hy, hv = (double)qr.hx - (double)qr.hy;
+    q.hdiag = half_key(__half_as_ushort(__float2half_rn((float)hu))) |
+              (half_key(__half_as_ushort(__float2half_rn((float)hv))) << 16);
     if (!ok) {
         q.cxlo = q.cylo = 0; q.cxhi = q.cyhi = -1; q.l0 = 0; q.t = -1.f;
         q.kx = q.ky = q.norm = 0.0;
@@ -452,6 +469,7 @@ __device__ __forceinline__ QuerySetup uniform_query(const QuerySetup& q)
     u.l0 = __builtin_amdgcn_readfirstlane(q.l0);
     u.t = uniform_f32(q.t);
     u.hkey = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.hkey);
+    u.hdiag = (uint32_t)__builtin_amdgcn_readfirstlane((int)q.hdiag);
     u.kx = uniform_f64(q.kx); u.ky = uniform_f64(q.ky); u.norm = uniform_f64(q.norm);
     u.fexp = __builtin_amdgcn_readfirstlane(q.fexp);
     u.valid = __builtin_amdgcn_readfirstlane((int)q.valid) != 0;
