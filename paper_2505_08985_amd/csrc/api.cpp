@@ -77,6 +77,7 @@ static void fill_view(pndf_hier* h)
     d.oct_k = h->oct_k;
     d.oct_c = h->oct_c;
     d.clu_em = h->clu_em;
+    d.tile_e = h->tile_e;
     d.nodes = (uint32_t)h->nodes;
     d.quad = h->quad;
     d.n = m->n;
@@ -247,6 +248,7 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
         if (e == hipSuccess) e = hipMalloc(&h->bbox_clu, sizeof(float4) * nodes);
         if (e == hipSuccess) e = hipMalloc(&h->oct_c, sizeof(uint4) * 3 * nodes);
         if (e == hipSuccess) e = hipMalloc(&h->clu_em, sizeof(float2) * nodes);
+        if (e == hipSuccess) e = hipMalloc(&h->tile_e, sizeof(float2) * 2 * kMaxTiles);
     }
     fill_view(h);
     if (e == hipSuccess) e = build_hierarchy_levels(h, (hipStream_t)stream);
@@ -276,6 +278,7 @@ void pndf_destroy_hierarchy(pndf_hier* h)
     (void)hipFree(h->oct_k);
     (void)hipFree(h->oct_c);
     (void)hipFree(h->clu_em);
+    (void)hipFree(h->tile_e);
     mesh_release(h->mesh);
     delete h;
 }
@@ -391,11 +394,16 @@ pndf_status pndf_eval_batch(const pndf_hier* h, const pndf_query* d_q, int64_t n
     if (st != PNDF_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     uint32_t* order = nullptr;
+    const uint32_t* narrow = nullptr;
+    TileWork tile{};
     hipError_t e = hipSuccess;
-    if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER))
-        e = make_order(h->dev, d_q, nq, &order, s);
-    EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel};
+    if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER)) {
+        make_tiles(h->dev, nq, &tile, s);
+        e = make_order(h->dev, d_q, nq, o.sigma_to_r, tile, &order, &narrow, s);
+    }
+    EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, narrow, tile};
     if (e == hipSuccess) e = launch_eval(h->dev, a, o.algo, s);
+    free_tiles(tile, s);
     free_order(order, s);
     return e == hipSuccess ? PNDF_OK : hip_fail(e, "pndf_eval_batch");
 }
@@ -412,7 +420,7 @@ pndf_status pndf_eval_batch_noalloc(const pndf_hier* h, const pndf_query* d_q, i
     hipError_t e = hipSuccess;
     if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER))
         e = make_order_static(h->dev, d_q, nq, &order, s);
-    EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel};
+    EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, nullptr, {}};
     if (e == hipSuccess) e = launch_eval(h->dev, a, o.algo, s);
     return e == hipSuccess ? PNDF_OK : hip_fail(e, "pndf_eval_batch_noalloc");
 }
@@ -425,7 +433,7 @@ pndf_status pndf_eval_counts(const pndf_hier* h, const pndf_query* d_q, int64_t 
     pndf_status st = eval_common(h, d_q, nq, opts, d_out, &o);
     if (st != PNDF_OK) return st;
     if (nq > 0 && !d_counts) return invalid("counts pointer is NULL");
-    EvalArgs a{d_q, nullptr, nq, 0, 0, d_out, d_counts, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel};
+    EvalArgs a{d_q, nullptr, nq, 0, 0, d_out, d_counts, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, nullptr, {}};
     hipError_t e = launch_eval(h->dev, a, o.algo, (hipStream_t)stream);
     return e == hipSuccess ? PNDF_OK : hip_fail(e, "pndf_eval_counts");
 }
@@ -447,7 +455,7 @@ pndf_status pndf_eval_hits(const pndf_hier* h, const pndf_query* d_q, int64_t nq
     uint32_t* d_counts = nullptr;
     hipError_t e = hipMalloc(&d_counts, sizeof(uint32_t) * 4 * (size_t)nq);
     if (e != hipSuccess) return hip_fail(e, "pndf_eval_hits");
-    EvalArgs a{d_q, nullptr, nq, 0, 0, d_out, d_counts, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel};
+    EvalArgs a{d_q, nullptr, nq, 0, 0, d_out, d_counts, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, nullptr, {}};
     e = launch_eval(h->dev, a, o.algo, s);
     std::vector<uint32_t> counts((size_t)nq * 4);
     if (e == hipSuccess)
@@ -459,7 +467,7 @@ pndf_status pndf_eval_hits(const pndf_hier* h, const pndf_query* d_q, int64_t nq
         e = hipMemcpyAsync(d_offsets, offs.data(), sizeof(uint64_t) * (nq + 1), hipMemcpyHostToDevice, s);
     *required = offs[nq];
     if (e == hipSuccess && offs[nq] <= capacity && offs[nq] > 0) {
-        EvalArgs b{d_q, nullptr, nq, 0, 0, d_out, nullptr, d_offsets, d_ids, d_terms, o.tau, o.sigma_to_r, o.kernel};
+        EvalArgs b{d_q, nullptr, nq, 0, 0, d_out, nullptr, d_offsets, d_ids, d_terms, o.tau, o.sigma_to_r, o.kernel, nullptr, {}};
         e = launch_eval(h->dev, b, o.algo, s);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(s);

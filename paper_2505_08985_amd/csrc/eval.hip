@@ -469,6 +469,52 @@ struct NodeLists {
     }
 };
 
+enum { kTilesNone = 0, kTilesEmit = 1, kTilesItem = 2 };
+
+// Reserve n items of the wave's segment; the first one's place, or -1 when they do
+// not all fit (what the failed reservation covers is marked unused).  Every lane
+// calls it with the same n > 0.
+__device__ __forceinline__ int64_t tile_reserve(const TileWork& T, int n)
+{
+    const uint32_t seg = blockIdx.x & (kTileSegs - 1);
+    uint32_t at = 0;
+    if (lane_id() == 0) at = atomicAdd(&T.ctl->seg[seg].v, (uint32_t)n);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+    unsigned long long* const raw = T.raw + (size_t)seg * T.segcap;
+    if (at + (uint32_t)n <= T.segcap) return (int64_t)seg * T.segcap + at;
+    for (uint32_t i = at + lane_id(); i < T.segcap; i += 64) raw[i] = ~0ull;
+    return -1;
+}
+
+// Does node m of level lev >= kTileLevel, whose box holds h and which is not under the
+// cut, become an item?  Residuals grow with the level (a node's fit restricted to a
+// child is no better than the child's own), so the largest one some levels beneath
+// tells whether the descent gets that far.
+template <bool CUT>
+__device__ __forceinline__ bool tile_item(const HierDev& H, const QuerySetup& q, int lev, uint32_t m)
+{
+    if (!CUT) return lev == kTileLevel;
+    const float2 e = H.tile_e[(uint32_t)(level_offset(H.logn, lev) - level_offset(H.logn, kTileLevel)) + m];
+    return e.x > q.t && (lev == kTileLevel || e.y <= q.t);
+}
+
+// An item's word: the query's place, the node's level less kTileLevel (bits 24..27
+// of the low half: Morton codes of these levels take at most 10) and its list item.
+constexpr int kItemLevelShift = 24;
+__device__ __forceinline__ unsigned long long tile_word(unsigned long long place, int lev, uint32_t item)
+{
+    return (place << 32) | ((uint32_t)(lev - kTileLevel) << kItemLevelShift) | item;
+}
+__device__ __forceinline__ int tile_word_level(unsigned long long w)
+{
+    return kTileLevel + (int)(((uint32_t)w >> kItemLevelShift) & 0xfu);
+}
+// the first tile beneath an item's node
+__device__ __forceinline__ uint32_t tile_word_bin(unsigned long long w)
+{
+    return ((uint32_t)w & 0xffffu) << (2 * (tile_word_level(w) - kTileLevel));
+}
+
 // The shared descent.  List items are nodes (Morton codes) whose box contains h,
 // whose region meets the support box and which are not under the cluster cut.  A
 // lane takes one item: a level-1 node tests its 2 x 2 cells from its leaf record;
@@ -485,10 +531,14 @@ struct NodeLists {
 // before each step: half of the items of its highest non-empty list (the largest
 // subtrees it holds), if that level is at least split_level, become tasks of the
 // global queue.  A full queue simply leaves them here.
-template <int MODE, bool CUT, bool SPAWN, int KER>
+// With TILES == kTilesEmit, children (or roots) of level kTileLevel with enough
+// beneath them become items of the tile queue instead of list entries; what does not
+// fit there stays here.  With TILES == kTilesItem the root is one such item, ready to expand.
+template <int MODE, bool CUT, bool SPAWN, int KER, int TILES = kTilesNone>
 __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, int root_level,
                         bool root_ok, uint32_t root_item, bool roots_tested, int split_level,
-                        unsigned long long qidx, const TaskQueue& Q, Acc& acc, Rec& rec)
+                        unsigned long long qidx, const TaskQueue& Q, Acc& acc, Rec& rec,
+                        const TileWork& T = TileWork{})
 {
     static_assert(!SPAWN || MODE == kModeValue, "donation is only used by value-mode workers");
     const int lane = threadIdx.x & 63;
@@ -501,7 +551,12 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
     uint32_t nonempty = 0;   // bit l: list of level l non-empty (wave-uniform)
     int cntv = 0;            // lane l holds the size of list l
     const AxisRuns rx0 = axis_runs(q.cxlo, q.cxhi, 0, H.n), ry0 = axis_runs(q.cylo, q.cyhi, 0, H.n);
-    if (root_level == 0) {
+    if constexpr (TILES == kTilesItem) {
+        if (lane == 0) nl.put(root_level, 0, root_item);
+        if (lane == root_level) cntv = 1;
+        nonempty = 1u << root_level;
+        wave_sync();
+    } else if (root_level == 0) {
         const int i = (int)(root_item & 0xffffu), j = (int)(root_item >> 16);
         if (root_ok) {
             pend = plane_cell_mask(H, q, i, j, acc);
@@ -522,9 +577,17 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
             ok = in_octagon(q, CUT ? load_octagon(H, oct_class(cut, kids_cut), idx) : H.oct_k[idx]);
         }
         cut = cut && ok;
+        const uint32_t entry = root_item | (kids_cut ? kAllCut : 0u);
+        if (TILES == kTilesEmit && root_level >= kTileLevel) {
+            const uint64_t be = __ballot(ok && !cut && tile_item<CUT>(H, q, root_level, m));
+            const int64_t out = be ? tile_reserve(T, __popcll(be)) : -1;
+            if (out >= 0 && ((be >> lane) & 1ull)) {
+                T.raw[out + __popcll(be & ((1ull << lane) - 1ull))] = tile_word(qidx, root_level, entry);
+                ok = false;
+            }
+        }
         const uint64_t bl = __ballot(ok && !cut);
-        if (ok && !cut)
-            nl.put(root_level, __popcll(bl & ((1ull << lane) - 1ull)), root_item | (kids_cut ? kAllCut : 0u));
+        if (ok && !cut) nl.put(root_level, __popcll(bl & ((1ull << lane) - 1ull)), entry);
         if (CUT) {
             const uint64_t bc = __ballot(cut);
             if (cut) cq[__popcll(bc & ((1ull << lane) - 1ull))] = ((uint32_t)root_level << kCluShift) | m;
@@ -706,12 +769,38 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
             // goes back to its own list whole and is expanded again later.  Child
             // positions grow with the lane, so the parents that fit are a prefix and the
             // first one with children always fits.
-            const uint32_t chl = CUT ? chm & ~cut4 : chm, chc = CUT ? chm & cut4 : 0u;
-            int total;
-            const int nch = __popc(chl);
-            const int pos = wave_prefix_small(nch, &total);
+            uint32_t chl = CUT ? chm & ~cut4 : chm;
+            const uint32_t chc = CUT ? chm & cut4 : 0u;
+            uint32_t che = 0;  // of the list children, those to leave as items
+            if (TILES == kTilesEmit && l - 1 >= kTileLevel) {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((chl & (1u << c)) && tile_item<CUT>(H, q, l - 1, m4 + c)) che |= 1u << c;
+                chl &= ~che;
+            }
             const int below = __builtin_amdgcn_readlane(cntv, l - 1);
-            const bool back = nch > 0 && below + pos + nch > kListCap;
+            int total, nch = __popc(chl), pos = wave_prefix_small(nch, &total);
+            bool back = nch > 0 && below + pos + nch > kListCap;
+            if (TILES == kTilesEmit && l - 1 >= kTileLevel) {
+                // (a parent that goes back leaves no items now: it is expanded again)
+                int n;
+                const int at = wave_prefix_small(back ? 0 : __popc(che), &n);
+                const int64_t out = n ? tile_reserve(T, n) : -1;
+                if (out >= 0) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (!back && (che & (1u << c)))
+                            T.raw[out + at + __popc(che & ((1u << c) - 1u))] =
+                                tile_word(qidx, l - 1, (m4 + c) | ((cin >> c) & 1u ? kInside : 0u) |
+                                                           ((all4 >> c) & 1u ? kAllCut : 0u));
+                } else if (n) {
+                    // no room: all of them are evaluated here
+                    chl |= che;
+                    nch = __popc(chl);
+                    pos = wave_prefix_small(nch, &total);
+                    back = nch > 0 && below + pos + nch > kListCap;
+                }
+            }
             const uint64_t bb = __ballot(back);
             if (!back) {
                 // child c goes to below + pos + (number of list children before it)
@@ -783,6 +872,13 @@ __device__ __forceinline__ int descent_start(const HierDev& H, const QuerySetup&
             lr = l2;
     }
     return lr;
+}
+
+// Limb `lane` (32 bits) of a wave-uniform sum, for lanes below 6.
+__device__ __forceinline__ unsigned long long limb_of(const Fix192& d, int lane)
+{
+    const uint64_t w = lane < 2 ? d.w0 : (lane < 4 ? d.w1 : d.w2);
+    return lane & 1 ? w >> 32 : w & 0xffffffffull;
 }
 
 template <int MODE>
@@ -868,6 +964,7 @@ __global__ __launch_bounds__(64) void k_eval_plain(HierDev H, EvalArgs a)
     const int64_t local = xcd_contiguous(blockIdx.x, gridDim.x);
     if (local >= a.slots) return;
     const int64_t slot = a.slot0 + local;
+    if (MODE == kModeValue && a.narrow && slot >= (int64_t)*a.narrow) return;  // a wide query (k_tile_emit)
     const int64_t qi = a.order ? (int64_t)a.order[slot] : slot;
     uint32_t* lists = lds;
     const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, a.kernel));
@@ -881,6 +978,207 @@ __global__ __launch_bounds__(64) void k_eval_plain(HierDev H, EvalArgs a)
     TaskQueue none{};
     descend<MODE, CUT, false, KER>(H, q, lists, lr, ok, item, false, 0, 0, none, acc, rec);
     finish<MODE>(a, qi, q, acc);
+}
+
+// ------------------------------------------------------------ tiles
+// Both kernels below run on a fixed grid (the counts are known on the device only):
+// a wave claims runs of consecutive pieces of work, from its XCD's eighth of them
+// first, so that the waves of an XCD stay on neighbouring queries or on the same few
+// tiles.  Claims shrink towards the end of a share.
+constexpr unsigned kTileWaves = 256 * 24;  // 24 waves per compute unit are resident
+
+struct Claim {
+    uint32_t at, end;
+};
+
+// The wave's next run of [0, total), at most `most` long; at == end when none is
+// left.  `x` counts the shares already exhausted.
+__device__ __forceinline__ Claim claim_run(TileCtl::Count* ctr, uint32_t total, uint32_t most, int* x)
+{
+    const uint32_t workers = max(1u, gridDim.x / kXcd);
+    for (; *x < kXcd; ++*x) {
+        const int s = ((int)(blockIdx.x & (kXcd - 1)) + *x) & (kXcd - 1);
+        const uint32_t lo = (uint32_t)((uint64_t)total * s / kXcd);
+        const uint32_t len = (uint32_t)((uint64_t)total * (s + 1) / kXcd) - lo;
+        uint32_t at = len, n = 0;
+        if (lane_id() == 0) {
+            const uint32_t seen = __hip_atomic_load(&ctr[s].v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (seen < len) {
+                n = max(1u, min(most, (len - seen) / (2u * workers)));
+                at = atomicAdd(&ctr[s].v, n);
+            }
+        }
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+        n = (uint32_t)__builtin_amdgcn_readfirstlane((int)n);
+        if (at < len) return Claim{lo + at, lo + min(at + n, len)};
+    }
+    return Claim{0, 0};
+}
+
+// At one query a claim the counters' atomics, about 70 ns each on one address, set
+// the pace (2^19 queries: 4.8 ms).
+constexpr uint32_t kWideClaim = 8;
+
+// The wide queries of a round: each leaves its tiles as items and stores its set-up
+// and its sum so far (of what it evaluated above or instead of items).
+template <bool CUT, int KER>
+__global__ __launch_bounds__(64) void k_tile_emit(HierDev H, EvalArgs a)
+{
+    extern __shared__ uint32_t lds[];
+    const TileWork& T = a.tile;
+    const int lane = lane_id();
+    const int64_t first = (int64_t)*a.narrow + a.slot0;
+    const int64_t wide = min(a.nq - first, (int64_t)T.round);
+    if (wide <= 0) return;
+    TaskQueue none{};
+    Rec rec{nullptr, nullptr, 0, 0};
+    int x = 0;
+    while (true) {
+        const Claim c = claim_run(T.ctl->qclaim, (uint32_t)wide, kWideClaim, &x);
+        if (c.at >= c.end) break;
+        for (uint32_t local = c.at; local < c.end; ++local) {
+            const int64_t qi = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.order[first + local]);
+            const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, a.kernel));
+            Acc acc;
+            const int lr = max(descent_start<CUT>(H, q), kTileLevel);
+            bool ok;
+            const uint32_t item = root_item(H, q, lr, &ok);
+            descend<kModeValue, CUT, false, KER, kTilesEmit>(H, q, lds, lr, ok, item, false, 0, (unsigned long long)local,
+                                                             none, acc, rec, T);
+            const Fix192 d = wave_sum_fix(acc.d);
+            if (lane < 6) T.acc[6 * (size_t)local + lane] = limb_of(d, lane);
+            if (lane == 0) T.setup[local] = q;
+        }
+    }
+}
+
+// The items, in tile order.  An item's sum is added limb by limb, which needs no
+// carries between waves and nothing to wait for.
+constexpr uint32_t kTileClaim = 8;
+
+template <bool CUT, int KER>
+__global__ __launch_bounds__(64) void k_eval_tiles(HierDev H, EvalArgs a)
+{
+    extern __shared__ uint32_t lds[];
+    const TileWork& T = a.tile;
+    const int lane = lane_id();
+    const uint32_t total = T.ctl->total;
+    TaskQueue none{};
+    Rec rec{nullptr, nullptr, 0, 0};
+    int x = 0;
+    while (true) {
+        const Claim c = claim_run(T.ctl->claim, total, kTileClaim, &x);
+        if (c.at >= c.end) break;
+        for (uint32_t i = c.at; i < c.end; ++i) {
+            const unsigned long long w = uniform_u64(T.items[i]);
+            const uint32_t slot = (uint32_t)(w >> 32);
+            const QuerySetup q = uniform_query(T.setup[slot]);
+            Acc acc;
+            descend<kModeValue, CUT, false, KER, kTilesItem>(H, q, lds, tile_word_level(w), true,
+                                                             (uint32_t)w & ~(0xfu << kItemLevelShift), true, 0, 0, none,
+                                                             acc, rec);
+            if (__ballot((acc.d.w0 | acc.d.w1 | acc.d.w2) != 0ull)) {
+                const Fix192 d = wave_sum_fix(acc.d);
+                if (lane < 6) atomicAdd(&T.acc[6 * (size_t)slot + lane], limb_of(d, lane));
+            }
+        }
+    }
+}
+
+__device__ __forceinline__ void tile_reset(TileCtl* c, int t)
+{
+    if (t < kTileSegs) c->seg[t].v = 0;
+    if (t < kXcd) c->qclaim[t].v = c->claim[t].v = 0;
+    if (t == 0) c->total = 0;
+    if (t < kMaxTiles) c->hist[t] = c->cursor[t] = 0;
+}
+
+constexpr int kTileParts = 8;  // blocks per segment of the sorting passes
+
+// Count the items of each tile (LDS first: one global atomic per tile and block).
+__global__ __launch_bounds__(256) void k_tile_hist(TileWork T)
+{
+    __shared__ uint32_t loc[kMaxTiles];
+    const uint32_t seg = blockIdx.x & (kTileSegs - 1), part = blockIdx.x / kTileSegs;
+    const uint32_t cnt = min(T.ctl->seg[seg].v, T.segcap);
+    if (part * 256u >= cnt) return;
+    for (int b = threadIdx.x; b < T.tiles; b += 256) loc[b] = 0u;
+    __syncthreads();
+    const unsigned long long* raw = T.raw + (size_t)seg * T.segcap;
+    for (uint32_t i = part * 256u + threadIdx.x; i < cnt; i += 256u * kTileParts) {
+        const unsigned long long w = raw[i];
+        if (w != ~0ull) atomicAdd(&loc[tile_word_bin(w)], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < T.tiles; b += 256)
+        if (loc[b]) atomicAdd(&T.ctl->hist[b], loc[b]);
+}
+
+// Place the items by tile: each block counts its share again, reserves its range of
+// every tile (the tiles' first places are a scan of the counts) and writes.
+__global__ __launch_bounds__(256) void k_tile_scatter(TileWork T)
+{
+    __shared__ uint32_t loc[kMaxTiles], first[kMaxTiles], part_sum[256];
+    const uint32_t seg = blockIdx.x & (kTileSegs - 1), part = blockIdx.x / kTileSegs;
+    const uint32_t cnt = min(T.ctl->seg[seg].v, T.segcap);
+    const bool none = part * 256u >= cnt;
+    if (none && blockIdx.x != 0) return;
+    const int t = threadIdx.x, per = (T.tiles + 255) / 256;
+    uint32_t sum = 0;
+    for (int k = 0; k < per; ++k)
+        if (t * per + k < T.tiles) sum += T.ctl->hist[t * per + k];
+    part_sum[t] = sum;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {
+        const uint32_t v = t >= o ? part_sum[t - o] : 0u;
+        __syncthreads();
+        part_sum[t] += v;
+        __syncthreads();
+    }
+    if (blockIdx.x == 0 && t == 255) T.ctl->total = part_sum[255];
+    uint32_t run = part_sum[t] - sum;
+    for (int k = 0; k < per; ++k)
+        if (t * per + k < T.tiles) {
+            first[t * per + k] = run;
+            loc[t * per + k] = 0u;
+            run += T.ctl->hist[t * per + k];
+        }
+    __syncthreads();
+    if (none) return;
+    const unsigned long long* raw = T.raw + (size_t)seg * T.segcap;
+    for (uint32_t i = part * 256u + t; i < cnt; i += 256u * kTileParts) {
+        const unsigned long long w = raw[i];
+        if (w != ~0ull) atomicAdd(&loc[tile_word_bin(w)], 1u);
+    }
+    __syncthreads();
+    for (int b = t; b < T.tiles; b += 256)
+        if (loc[b]) loc[b] = first[b] + atomicAdd(&T.ctl->cursor[b], loc[b]);
+    __syncthreads();
+    for (uint32_t i = part * 256u + t; i < cnt; i += 256u * kTileParts) {
+        const unsigned long long w = raw[i];
+        if (w != ~0ull) T.items[atomicAdd(&loc[tile_word_bin(w)], 1u)] = w;
+    }
+}
+
+// Results of the round's wide queries: the limbs' carries into the 192-bit sum.  The
+// last thing of a round, so it clears the control block for the next one.
+__global__ __launch_bounds__(256) void k_tile_finish(EvalArgs a)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    tile_reset(a.tile.ctl, t);
+    const int64_t first = (int64_t)*a.narrow + a.slot0;
+    const int64_t wide = min(a.nq - first, (int64_t)a.tile.round);
+    for (int64_t local = t; local < wide; local += (int64_t)gridDim.x * 256) {
+        const unsigned long long* w = a.tile.acc + 6 * local;
+        uint64_t limb[6], carry = 0;
+        for (int k = 0; k < 6; ++k) {
+            const uint64_t lo = (w[k] & 0xffffffffull) + (carry & 0xffffffffull);
+            limb[k] = lo & 0xffffffffull;
+            carry = (lo >> 32) + (w[k] >> 32) + (carry >> 32);
+        }
+        const Fix192 d{limb[0] | (limb[1] << 32), limb[2] | (limb[3] << 32), limb[4] | (limb[5] << 32)};
+        a.out[a.order[first + local]] = fix_to_float(d, a.tile.setup[local].fexp);
+    }
 }
 
 // ------------------------------------------------------------ persistent
@@ -917,7 +1215,7 @@ __global__ void k_persist_reset(QueueCtl* ctl, Fix192* acc, int* fexp, const pnd
         fexp[i] = 0;
     }
     if (hist)
-        for (long long i = t; i < nb; i += (long long)gridDim.x * blockDim.x) hist[i] = 0;
+        for (long long i = t; i < 2 * nb; i += (long long)gridDim.x * blockDim.x) hist[i] = 0;
     if (t == 0) {
         for (int x = 0; x < kXcds; ++x) ctl->qhead[x].v = 0;
         ctl->head = 0;
@@ -1178,6 +1476,27 @@ __global__ void k_persist_finalize(const QueueCtl* ctl, const Fix192* acc, const
     }
 }
 
+// The wide queries of a batch, in rounds (their number is known on the
+// device only: a round without any costs its five launches).
+template <bool CUT, int KER>
+hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s)
+{
+    const size_t lds = sizeof(uint32_t) * wave_lds_words(H.L, CUT);
+    for (int64_t off = 0; off < a.nq; off += a.tile.round) {
+        a.slot0 = off;
+        hipLaunchKernelGGL((k_tile_emit<CUT, KER>), dim3((unsigned)std::min<int64_t>(kTileWaves, a.nq - off)), dim3(64), lds,
+                           s, H, a);
+        hipLaunchKernelGGL(k_tile_hist, dim3(kTileSegs * kTileParts), dim3(256), 0, s, a.tile);
+        hipLaunchKernelGGL(k_tile_scatter, dim3(kTileSegs * kTileParts), dim3(256), 0, s, a.tile);
+        hipLaunchKernelGGL((k_eval_tiles<CUT, KER>), dim3(kTileWaves), dim3(64), lds, s, H, a);
+        const unsigned fin = (unsigned)std::max<int64_t>(kMaxTiles / 256, std::min<int64_t>(1024, (a.nq - off + 255) / 256));
+        hipLaunchKernelGGL(k_tile_finish, dim3(fin), dim3(256), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // Launches cover at most launch_chunk() queries (grid dimensions stay far below
 // 2^32 work-items).
 template <int MODE, int KER>
@@ -1202,6 +1521,8 @@ hipError_t launch_mode(const HierDev& H, const EvalArgs& a0, int algo, hipStream
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
+    if (MODE == kModeValue && a0.narrow)
+        return a0.tau > 0.f ? launch_tiles<true, KER>(H, a0, s) : launch_tiles<false, KER>(H, a0, s);
     return hipSuccess;
 }
 
@@ -1216,111 +1537,136 @@ hipError_t launch_kernel(const HierDev& H, const EvalArgs& a, int algo, hipStrea
 // ------------------------------------------------------------ query order
 constexpr int kOrderBits = 6;  // 64 x 64 buckets
 
-__global__ void k_order_zero(uint32_t* hist, int nb)
+// With tiles, buckets [nb, 2 nb) hold the wide queries (half-width above `wide`), so
+// they come last in the same spatial order.
+struct OrderArgs {
+    const pndf_query* q;
+    int64_t nq;
+    int n, bshift, nb, bins;   // bins = 2 nb with tiles, else nb
+    float s2r, wide;
+    uint32_t* key;
+    uint32_t* hist;            // bins counters, then bins cursors
+    uint32_t* order;
+    uint32_t* narrow;          // number of queries that are not wide (nullptr without tiles)
+    TileCtl* ctl;
+};
+
+__global__ void k_order_zero(OrderArgs o)
 {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nb; i += gridDim.x * blockDim.x) hist[i] = 0;
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int i = t; i < 2 * o.bins; i += gridDim.x * blockDim.x) o.hist[i] = 0;
+    if (o.ctl) tile_reset(o.ctl, t);
 }
 
-// The histogram and the scatter count in LDS first (bins < 4096: at most 64 x 64
-// Morton buckets), so the global counters see one atomic per non-empty bin per
-// workgroup instead of one per query; a workgroup takes a large strided share of
-// the batch (the grid is small, order_blocks).
-constexpr int kOrderMaxBins = 4096;
+constexpr int kOrderMaxBins = 8192;
+constexpr int kOrderThreads = 1024;
 
-__device__ __forceinline__ void order_hist(const pndf_query* __restrict__ q, int64_t nq, int n, int bshift,
-                                           uint32_t* __restrict__ key, uint32_t* __restrict__ hist)
+__device__ __forceinline__ uint32_t order_bucket(const pndf_query& q, int n, int bshift)
+{
+    if (!(fabsf(q.x) <= 16777216.0f && fabsf(q.y) <= 16777216.0f)) return 0;  // (NaN too)
+    const uint32_t cx = (uint32_t)((int)floorf(q.x) & (n - 1)) >> bshift;
+    const uint32_t cy = (uint32_t)((int)floorf(q.y) & (n - 1)) >> bshift;
+    return morton(cx, cy);
+}
+
+// The histogram and the scatter count in LDS first, so the global counters see one
+// atomic per non-empty bin per workgroup instead of one per query; a workgroup takes
+// a strided share of the batch (order_blocks).
+__device__ __forceinline__ void order_hist(const pndf_query* __restrict__ q, int64_t nq, int n, int bshift, int nb, int bins,
+                                           float s2r, float wide, uint32_t* __restrict__ key, uint32_t* __restrict__ hist)
 {
     __shared__ uint32_t loc[kOrderMaxBins];
-    for (int b = threadIdx.x; b < kOrderMaxBins; b += blockDim.x) loc[b] = 0u;
+    for (int b = threadIdx.x; b < bins; b += blockDim.x) loc[b] = 0u;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nq;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const float x = q[i].x, y = q[i].y;
-        uint32_t k = 0;
-        if (fabsf(x) <= 16777216.0f && fabsf(y) <= 16777216.0f) {  // false for NaN
-            const uint32_t cx = (uint32_t)((int)floorf(x) & (n - 1)) >> bshift;
-            const uint32_t cy = (uint32_t)((int)floorf(y) & (n - 1)) >> bshift;
-            k = morton(cx, cy);
+        const pndf_query qr = q[i];
+        uint32_t k = order_bucket(qr, n, bshift);
+        if (bins > nb) {
+            // (a query the evaluation rejects is not wide: k_eval_plain answers it)
+            const QuerySetup u = setup_support(qr, s2r);
+            if (u.valid && fmaxf(u.rx, u.ry) > wide) k += nb;
         }
         key[i] = k;
         atomicAdd(&loc[k], 1u);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < kOrderMaxBins; b += blockDim.x)
+    for (int b = threadIdx.x; b < bins; b += blockDim.x)
         if (loc[b]) atomicAdd(&hist[b], loc[b]);
 }
 
-// exclusive scan of nb <= 4096 counters by one workgroup of 1024 threads
-__global__ __launch_bounds__(1024) void k_order_scan(uint32_t* hist, int nb)
+// exclusive scan of `bins` counters into LDS by a workgroup of 1024 threads
+__device__ __forceinline__ void order_scan(const uint32_t* __restrict__ hist, int bins, uint32_t* first)
 {
-    __shared__ uint32_t part[1024];
-    const int t = threadIdx.x, per = (nb + 1023) / 1024;
+    __shared__ uint32_t part[kOrderThreads];
+    const int t = threadIdx.x, per = (bins + kOrderThreads - 1) / kOrderThreads;
     uint32_t sum = 0;
-    for (int k = 0; k < per; ++k) {
-        const int i = t * per + k;
-        if (i < nb) sum += hist[i];
-    }
+    for (int k = 0; k < per; ++k)
+        if (t * per + k < bins) sum += hist[t * per + k];
     part[t] = sum;
     __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
+    for (int o = 1; o < kOrderThreads; o <<= 1) {
         const uint32_t v = t >= o ? part[t - o] : 0u;
         __syncthreads();
         part[t] += v;
         __syncthreads();
     }
     uint32_t run = part[t] - sum;
-    for (int k = 0; k < per; ++k) {
-        const int i = t * per + k;
-        if (i < nb) {
-            const uint32_t c = hist[i];
-            hist[i] = run;
-            run += c;
+    for (int k = 0; k < per; ++k)
+        if (t * per + k < bins) {
+            first[t * per + k] = run;
+            run += hist[t * per + k];
         }
-    }
+    __syncthreads();
 }
 
 // Each workgroup reserves, per bin, a range of the exact size of its share's count
 // (one global atomic per non-empty bin), then places its queries in it.  Within a
 // bucket the order is whatever the atomics give: results do not depend on it.
-__device__ __forceinline__ void order_scatter(const uint32_t* __restrict__ key, int64_t nq,
+// first: the bins' first places (LDS).
+__device__ __forceinline__ void order_scatter(const uint32_t* __restrict__ key, int64_t nq, int bins, const uint32_t* first,
                                               uint32_t* __restrict__ cursor, uint32_t* __restrict__ order)
 {
     __shared__ uint32_t loc[kOrderMaxBins];
-    for (int b = threadIdx.x; b < kOrderMaxBins; b += blockDim.x) loc[b] = 0u;
+    for (int b = threadIdx.x; b < bins; b += blockDim.x) loc[b] = 0u;
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = i0; i < nq; i += stride) atomicAdd(&loc[key[i]], 1u);
     __syncthreads();
-    for (int b = threadIdx.x; b < kOrderMaxBins; b += blockDim.x)
-        if (loc[b]) loc[b] = atomicAdd(&cursor[b], loc[b]);
+    for (int b = threadIdx.x; b < bins; b += blockDim.x)
+        if (loc[b]) loc[b] = first[b] + atomicAdd(&cursor[b], loc[b]);
     __syncthreads();
     for (int64_t i = i0; i < nq; i += stride) order[atomicAdd(&loc[key[i]], 1u)] = (uint32_t)i;
 }
 
-__global__ void k_order_hist(const pndf_query* __restrict__ q, int64_t nq, int n, int bshift,
-                             uint32_t* __restrict__ key, uint32_t* __restrict__ hist)
+__global__ __launch_bounds__(kOrderThreads) void k_order_hist(OrderArgs o)
 {
-    order_hist(q, nq, n, bshift, key, hist);
+    order_hist(o.q, o.nq, o.n, o.bshift, o.nb, o.bins, o.s2r, o.wide, o.key, o.hist);
 }
 
-__global__ void k_order_scatter(const uint32_t* __restrict__ key, int64_t nq, uint32_t* __restrict__ cursor,
-                                uint32_t* __restrict__ order)
+__global__ __launch_bounds__(kOrderThreads) void k_order_scatter(OrderArgs o)
 {
-    order_scatter(key, nq, cursor, order);
+    __shared__ uint32_t first[kOrderMaxBins];
+    order_scan(o.hist, o.bins, first);
+    if (o.narrow && blockIdx.x == 0 && threadIdx.x == 0) *o.narrow = first[o.nb];
+    order_scatter(o.key, o.nq, o.bins, first, o.hist + o.bins, o.order);
 }
 
 // The same two passes for a persistent plan, reading the batch from its control
 // block (so the launch graph needs no per-run arguments for them).
-__global__ void k_porder_hist(const QueueCtl* ctl, int n, int bshift, uint32_t* __restrict__ key,
-                              uint32_t* __restrict__ hist)
+__global__ __launch_bounds__(kOrderThreads) void k_porder_hist(const QueueCtl* ctl, int n, int bshift, int nb,
+                                                               uint32_t* __restrict__ key, uint32_t* __restrict__ hist)
 {
-    order_hist(ctl->q, ctl->nq, n, bshift, key, hist);
+    order_hist(ctl->q, ctl->nq, n, bshift, nb, nb, 0.f, 0.f, key, hist);
 }
 
-__global__ void k_porder_scatter(const QueueCtl* ctl, const uint32_t* __restrict__ key,
-                                 uint32_t* __restrict__ cursor, uint32_t* __restrict__ order)
+__global__ __launch_bounds__(kOrderThreads) void k_porder_scatter(const QueueCtl* ctl, int nb,
+                                                                  const uint32_t* __restrict__ key,
+                                                                  uint32_t* __restrict__ hist, uint32_t* __restrict__ order)
 {
-    order_scatter(key, ctl->nq, cursor, order);
+    __shared__ uint32_t first[kOrderMaxBins];
+    order_scan(hist, nb, first);
+    order_scatter(key, ctl->nq, nb, first, hist + nb, order);
 }
 
 }  // namespace
@@ -1332,38 +1678,53 @@ void order_shape(int logn, int* nb, int* bshift)
     *bshift = logn - bits;
 }
 
-// Workgroups (of 256) of the histogram and scatter passes: about 16k queries each,
-// at most 256 (one per compute unit), so the LDS counts absorb most atomics.
+// Workgroups of the histogram and scatter passes: 4 queries a thread in small batches
+// (64 x 64 buckets and one workgroup per 16384 queries took 65 us of a 16384-query
+// tile's 253), at most one workgroup per compute unit.
 static unsigned order_blocks(int64_t nq)
 {
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (nq + 16383) / 16384));
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (nq + 4095) / 4096));
 }
 
-// The four passes of the spatial order into buf = order[nq] | key[nq] | hist[nb]
-// (the histogram is cleared by a kernel, never a memset node).
-static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq, uint32_t* buf, hipStream_t s)
+// The three passes of the spatial order into buf = order[nq] | key[nq] | hist[2 bins] |
+// narrow (the counters are cleared by a kernel, never a memset node).
+static size_t order_words(int nb, bool tiles) { return (size_t)(tiles ? 4 : 2) * nb + 1; }
+
+static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, TileCtl* ctl, uint32_t* buf,
+                               const uint32_t** narrow, hipStream_t s)
 {
-    int nb, bshift;
-    order_shape(H.logn, &nb, &bshift);
-    uint32_t* key = buf + nq;
-    uint32_t* hist = key + nq;
+    OrderArgs o{};
+    order_shape(H.logn, &o.nb, &o.bshift);
+    o.q = q;
+    o.nq = nq;
+    o.n = H.n;
+    o.bins = ctl ? 2 * o.nb : o.nb;
+    o.s2r = s2r;
+    o.wide = (float)(1 << kTileLevel);
+    o.order = buf;
+    o.key = buf + nq;
+    o.hist = o.key + nq;
+    o.ctl = ctl;
+    o.narrow = ctl ? o.hist + 2 * o.bins : nullptr;
+    if (narrow) *narrow = o.narrow;
     const unsigned g = order_blocks(nq);
-    hipLaunchKernelGGL(k_order_zero, dim3(16), dim3(256), 0, s, hist, nb);
-    hipLaunchKernelGGL(k_order_hist, dim3(g), dim3(256), 0, s, q, nq, H.n, bshift, key, hist);
-    hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(1024), 0, s, hist, nb);
-    hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(256), 0, s, key, nq, hist, buf);
+    hipLaunchKernelGGL(k_order_zero, dim3(8), dim3(kOrderThreads), 0, s, o);
+    hipLaunchKernelGGL(k_order_hist, dim3(g), dim3(kOrderThreads), 0, s, o);
+    hipLaunchKernelGGL(k_order_scatter, dim3(g), dim3(kOrderThreads), 0, s, o);
     return hipGetLastError();
 }
 
-hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, uint32_t** order, hipStream_t s)
+hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, const TileWork& T, uint32_t** order,
+                      const uint32_t** narrow, hipStream_t s)
 {
     *order = nullptr;
+    *narrow = nullptr;
     int nb, bshift;
     order_shape(H.logn, &nb, &bshift);
-    uint32_t* buf = nullptr;  // order[nq] | key[nq] | hist[nb]
-    hipError_t e = hipMallocAsync((void**)&buf, sizeof(uint32_t) * (2 * (size_t)nq + nb), s);
+    uint32_t* buf = nullptr;  // order[nq] | key[nq] | counters
+    hipError_t e = hipMallocAsync((void**)&buf, sizeof(uint32_t) * (2 * (size_t)nq + order_words(nb, T.ctl != nullptr)), s);
     if (e != hipSuccess) return e;
-    e = order_passes(H, q, nq, buf, s);
+    e = order_passes(H, q, nq, s2r, T.ctl, buf, narrow, s);
     if (e != hipSuccess) {
         (void)hipFreeAsync(buf, s);
         return e;
@@ -1378,7 +1739,7 @@ hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, uint32_
 // address is looked up once per device; host code uses that address, never the
 // array's name.  Every call on a GPU shares it, so calls that overlap on one GPU
 // race.
-static __device__ __align__(256) uint32_t scratch[2 * kStaticOrderQueries + 4096];
+static __device__ __align__(256) uint32_t scratch[2 * kStaticOrderQueries + 2 * 4096 + 64];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -1408,9 +1769,47 @@ hipError_t make_order_static(const HierDev& H, const pndf_query* q, int64_t nq, 
     int nb, bshift;
     order_shape(H.logn, &nb, &bshift);
     if (nb > 4096) return hipErrorInvalidValue;
-    e = order_passes(H, q, nq, buf, s);
+    e = order_passes(H, q, nq, 0.f, nullptr, buf, nullptr, s);
     if (e == hipSuccess) *order = buf;
     return e;
+}
+
+void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s)
+{
+    *w = TileWork{};
+    if (!has_tiles(H.logn)) return;
+    const int64_t chunk = std::min(kTileChunk, launch_chunk()), slots = std::min(nq, chunk);
+    w->round = (uint32_t)chunk;
+    w->tiles = 1 << (2 * (H.logn - kTileLevel));
+    // twice every tile of every query (the segments fill unevenly), up to kTileItems for
+    // a whole chunk; the rest is evaluated where it was found
+    const int64_t items = std::min<int64_t>(2 * slots * w->tiles, kTileItems / kTileChunk * chunk);
+    w->segcap = (uint32_t)((items + kTileSegs - 1) / kTileSegs);
+    const size_t n = (size_t)w->segcap * kTileSegs;
+    size_t off = (sizeof(TileCtl) + 255) & ~(size_t)255;
+    const size_t raw = off;
+    off += 8 * n;
+    const size_t srt = off;
+    off += 8 * n;
+    const size_t acc = off;
+    off += 48 * (size_t)slots;
+    const size_t set = off;
+    off += sizeof(QuerySetup) * (size_t)slots;
+    char* buf = nullptr;
+    if (hipMallocAsync((void**)&buf, off, s) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    w->ctl = reinterpret_cast<TileCtl*>(buf);
+    w->raw = reinterpret_cast<unsigned long long*>(buf + raw);
+    w->items = reinterpret_cast<unsigned long long*>(buf + srt);
+    w->acc = reinterpret_cast<unsigned long long*>(buf + acc);
+    w->setup = reinterpret_cast<QuerySetup*>(buf + set);
+}
+
+void free_tiles(const TileWork& w, hipStream_t s)
+{
+    if (w.ctl) (void)hipFreeAsync(w.ctl, s);
 }
 
 void free_order(uint32_t* order, hipStream_t s)
@@ -1474,35 +1873,30 @@ int persist_resident_blocks(const HierDev& H, const PersistPlan& P)
 
 
 
-// Kernel-node parameters of the three order passes (spatial order of the batch).
-static void order_params(PersistPlan& P, hipKernelNodeParams* hist, hipKernelNodeParams* scan,
-                         hipKernelNodeParams* scat)
+// Kernel-node parameters of the two order passes (spatial order of the batch; the
+// reset node clears their counters).
+static void order_params(PersistPlan& P, hipKernelNodeParams* hist, hipKernelNodeParams* scat)
 {
     P.hargs[0] = &P.ctl;
     P.hargs[1] = &P.on;
     P.hargs[2] = &P.order_bshift;
-    P.hargs[3] = &P.okey;
-    P.hargs[4] = &P.ohist;
-    P.sargs[0] = &P.ohist;
-    P.sargs[1] = &P.order_nb;
+    P.hargs[3] = &P.order_nb;
+    P.hargs[4] = &P.okey;
+    P.hargs[5] = &P.ohist;
     P.cargs[0] = &P.ctl;
-    P.cargs[1] = &P.okey;
-    P.cargs[2] = &P.ohist;
-    P.cargs[3] = &P.order;
+    P.cargs[1] = &P.order_nb;
+    P.cargs[2] = &P.okey;
+    P.cargs[3] = &P.ohist;
+    P.cargs[4] = &P.order;
     *hist = hipKernelNodeParams{};
     hist->func = (void*)k_porder_hist;
     hist->gridDim = dim3(order_blocks(P.max_nq));
-    hist->blockDim = dim3(256);
+    hist->blockDim = dim3(kOrderThreads);
     hist->kernelParams = P.hargs;
-    *scan = hipKernelNodeParams{};
-    scan->func = (void*)k_order_scan;
-    scan->gridDim = dim3(1);
-    scan->blockDim = dim3(1024);
-    scan->kernelParams = P.sargs;
     *scat = hipKernelNodeParams{};
     scat->func = (void*)k_porder_scatter;
     scat->gridDim = dim3(order_blocks(P.max_nq));
-    scat->blockDim = dim3(256);
+    scat->blockDim = dim3(kOrderThreads);
     scat->kernelParams = P.cargs;
 }
 
@@ -1532,8 +1926,8 @@ void persist_prepare(const HierDev& H, PersistPlan& P)
 hipError_t persist_graph_build(const HierDev& H, PersistPlan& P)
 {
     persist_prepare(H, P);
-    hipKernelNodeParams ohist{}, oscan{}, oscat{};
-    if (P.order) order_params(P, &ohist, &oscan, &oscat);
+    hipKernelNodeParams ohist{}, oscat{};
+    if (P.order) order_params(P, &ohist, &oscat);
     reset_params(P, nullptr, 0, nullptr);
     P.wargs[0] = &P.H;
     P.wargs[1] = &P.pa;
@@ -1555,13 +1949,12 @@ hipError_t persist_graph_build(const HierDev& H, PersistPlan& P)
     fin.kernelParams = P.fargs;
     fin.extra = nullptr;
     hipError_t e = hipGraphCreate(&P.graph, 0);
-    hipGraphNode_t nw = nullptr, nf = nullptr, nh = nullptr, ns = nullptr, nc = nullptr;
+    hipGraphNode_t nw = nullptr, nf = nullptr, nh = nullptr, nc = nullptr;
     if (e == hipSuccess) e = hipGraphAddKernelNode(&P.reset_node, P.graph, nullptr, 0, &P.reset);
     hipGraphNode_t before_work = P.reset_node;
     if (P.order) {
         if (e == hipSuccess) e = hipGraphAddKernelNode(&nh, P.graph, &P.reset_node, 1, &ohist);
-        if (e == hipSuccess) e = hipGraphAddKernelNode(&ns, P.graph, &nh, 1, &oscan);
-        if (e == hipSuccess) e = hipGraphAddKernelNode(&nc, P.graph, &ns, 1, &oscat);
+        if (e == hipSuccess) e = hipGraphAddKernelNode(&nc, P.graph, &nh, 1, &oscat);
         before_work = nc;
     }
     if (e == hipSuccess) e = hipGraphAddKernelNode(&nw, P.graph, &before_work, 1, &work);
@@ -1583,11 +1976,10 @@ hipError_t persist_run(PersistPlan& P, const pndf_query* q, long long nq, float*
     hipLaunchKernelGGL(k_persist_reset, P.reset.gridDim, P.reset.blockDim, 0, s, P.ctl, P.acc, P.fexp,
                        q, nq, out, P.epoch, P.ohist, P.order_nb);
     if (P.order) {
-        hipLaunchKernelGGL(k_porder_hist, dim3(order_blocks(P.max_nq)), dim3(256), 0, s, P.ctl, P.on,
-                           P.order_bshift, P.okey, P.ohist);
-        hipLaunchKernelGGL(k_order_scan, dim3(1), dim3(1024), 0, s, P.ohist, P.order_nb);
-        hipLaunchKernelGGL(k_porder_scatter, dim3(order_blocks(P.max_nq)), dim3(256), 0, s, P.ctl, P.okey,
-                           P.ohist, P.order);
+        hipLaunchKernelGGL(k_porder_hist, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.ctl, P.on,
+                           P.order_bshift, P.order_nb, P.okey, P.ohist);
+        hipLaunchKernelGGL(k_porder_scatter, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.ctl, P.order_nb,
+                           P.okey, P.ohist, P.order);
     }
     const size_t lds = sizeof(uint32_t) * 4 * wave_lds_words(P.H.L, P.tau > 0.f);
     void* args[] = {&P.H, &P.pa};

@@ -557,6 +557,32 @@ __global__ void k_residual_pairs(HierDev H, int level, float2* __restrict__ em)
     em[idx] = make_float2(H.clu_e[idx], kids);
 }
 
+// Largest residuals kTileDepth and kTileSpan levels beneath each node of a level
+// from kTileLevel up (HierDev::tile_e), one workgroup per node.
+__global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, int level, float2* __restrict__ te)
+{
+    __shared__ float red[256];
+    const int64_t t = blockIdx.x;
+    float m[2];
+    for (int k = 0; k < 2; ++k) {
+        const int down = min(k ? kTileSpan : kTileDepth, level - 1);  // (residuals start at level 1)
+        const int per = 1 << (2 * down);
+        const float* e = H.clu_e + level_offset(H.logn, level - down) + per * t;
+        float v = 0.f;
+        for (int i = threadIdx.x; i < per; i += 256) v = fmaxf(v, e[i]);
+        red[threadIdx.x] = v;
+        for (int o = 128; o > 0; o >>= 1) {
+            __syncthreads();
+            if ((int)threadIdx.x < o) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + o]);
+        }
+        __syncthreads();
+        m[k] = red[0];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0)
+        te[level_offset(H.logn, level) - level_offset(H.logn, kTileLevel) + t] = make_float2(m[0], m[1]);
+}
+
 hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
 {
     const HierDev& H = h->dev;
@@ -633,6 +659,11 @@ hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
     for (int level = 1; level <= H.L && err == hipSuccess && h->cluster; ++level) {
         const int64_t m = (int64_t)(n >> level) * (n >> level);
         hipLaunchKernelGGL(k_residual_pairs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, H, level, h->clu_em);
+        err = hipGetLastError();
+    }
+    for (int level = kTileLevel; level <= H.L && err == hipSuccess && h->cluster && has_tiles(H.logn); ++level) {
+        const int64_t m = (int64_t)(n >> level) * (n >> level);
+        hipLaunchKernelGGL(k_tile_residuals, dim3((unsigned)m), dim3(256), 0, s, H, level, h->tile_e);
         err = hipGetLastError();
     }
     if (err == hipSuccess) err = hipStreamSynchronize(s);

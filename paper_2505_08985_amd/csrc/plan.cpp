@@ -125,7 +125,7 @@ pndf_status pndf_plan_create(const pndf_hier* h, int64_t max_nq, const pndf_eval
     if (e == hipSuccess && !(o.flags & PNDF_EVAL_INPUT_ORDER)) {
         // workers take the queries in spatial (Morton bucket) order
         order_shape(h->dev.logn, &P.order_nb, &P.order_bshift);
-        e = hipMalloc(&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + (size_t)P.order_nb));
+        e = hipMalloc(&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + 2 * (size_t)P.order_nb));
     }
     // flags start at 0; the first run publishes with epoch 1
     if (e == hipSuccess) e = hipMemsetAsync(P.flags, 0, sizeof(unsigned) * P.capacity, (hipStream_t)stream);

@@ -106,6 +106,8 @@ struct HierDev {
     // alone) holds NaN, so the record carries the clamp bits (clamp_bits)
     const float4* clu_t;
     const float* clu_e;     // e^l per node
+    const float2* tile_e;   // maps with tiles: per node of level kTileLevel and above (packed like the others, from
+                            // level kTileLevel on) the largest e^l kTileDepth and kTileSpan levels beneath
     const float2* clu_det;  // cluster triangle Jacobians (lower, upper), eps when clamped
     const QuadRec* quad;    // level-1 leaf records (Morton order)
     uint32_t nodes;         // nodes of all levels
@@ -217,7 +219,7 @@ struct PersistPlan {
     unsigned long long* tasks = nullptr;
     unsigned int* flags = nullptr;
     unsigned long long capacity = 0;
-    uint32_t* order = nullptr;  // order[max_nq] | key[max_nq] | hist[order_nb] (nullptr: input order)
+    uint32_t* order = nullptr;  // order[max_nq] | key[max_nq] | counters[2 order_nb] (nullptr: input order)
     int order_nb = 0, order_bshift = 0;
     long long max_nq = 0;
     int blocks = 0, split_level = 1;
@@ -241,9 +243,8 @@ struct PersistPlan {
     void* rargs[9];
     void* wargs[2];
     void* fargs[3];
-    void* hargs[5];  // order passes: histogram, scan, scatter
-    void* sargs[2];
-    void* cargs[4];
+    void* hargs[6];  // order passes: histogram, scatter
+    void* cargs[5];
 };
 
 // Fill the device arguments of a plan whose buffers are allocated.
@@ -279,6 +280,7 @@ struct pndf_hier {
     uint4* oct_k = nullptr;
     uint4* oct_c = nullptr;       // 3 x nodes (kOctSub, kOctOwn, kOctKids)
     float2* clu_em = nullptr;
+    float2* tile_e = nullptr;
     float4* bbox_clu = nullptr;   // box of the node's own cluster triangles (float32)
     float4* clu_n = nullptr;      // the fitted normals as float32 (exported; the kernels read clu_t)
     float4* clu_t = nullptr;
@@ -302,6 +304,51 @@ hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s);
 // Row-major copy of a Morton-ordered per-node array of `words` 32-bit words per node.
 hipError_t export_rowmajor(const void* src, void* dst, int m, int words, hipStream_t s);
 
+struct QuerySetup;
+
+// Tiled evaluation of wide footprints.  The nodes of level kTileLevel (256 x 256
+// texels) are tiles: everything the descent reads beneath one is about 3.7 MB, the
+// size of an XCD's L2.  The spatial order puts the queries that enter above that
+// level last; k_tile_emit descends them to it and leaves their surviving tiles as
+// items, the items are sorted by tile, and the waves of an XCD work through
+// neighbouring items, so that a tile's nodes come from memory about once per launch
+// instead of once per query.  An item holds the place of its query and the list item
+// (Morton code and flags) of its node, with the node's level.
+//
+// Under the cut the descent ends higher up and a tile may hold a few nodes only,
+// while an item costs about 700 vector instructions before its first useful one.  So
+// a node above the tile level becomes an item as a whole when all nodes kTileSpan
+// levels beneath it are under the cut (its part of the hierarchy is then as large as
+// a tile's at most), and a node all of whose descendants kTileDepth levels down are
+// under it is evaluated on the spot.  Measured (spans 7, 8, 9, 11; one item a tile of
+// level 8 otherwise): 2^21 queries at 8192^2, tau = 1e-3: 130, 98, 94, 106 ms (97
+// untiled); 60001 queries of sigma 4 to 1024 on the 4096^2 scratched map, tau = 1e-4:
+// 158 -> 47 ms at any span, L2 misses 7.7e9 -> 4e7, the vector ALU then always busy.
+constexpr int kTileLevel = 8;
+constexpr int kTileDepth = 3, kTileSpan = 9;
+constexpr int kTileSegs = 64;                        // item segments, each with a counter of its own
+constexpr int kMaxTiles = 1 << (2 * (13 - kTileLevel));
+constexpr int64_t kTileChunk = (int64_t)1 << 19;     // wide queries per round
+constexpr int64_t kTileItems = (int64_t)1 << 24;     // items per round
+// Maps with tiles: below 1024^2 there are fewer than 16 and the caches hold the map.
+__host__ __device__ inline bool has_tiles(int logn) { return logn >= kTileLevel + 2; }
+struct TileCtl {
+    struct alignas(128) Count {
+        uint32_t v;
+    } seg[kTileSegs], qclaim[8], claim[8];           // items written per segment; queries, items claimed per XCD's share
+    alignas(128) uint32_t total;                     // items after sorting
+    alignas(128) uint32_t hist[kMaxTiles], cursor[kMaxTiles];
+};
+struct TileWork {
+    TileCtl* ctl;                   // nullptr: evaluate every query as a whole
+    unsigned long long* raw;        // kTileSegs segments of segcap items
+    unsigned long long* items;      // sorted by tile
+    unsigned long long* acc;        // per wide query: six 32-bit limbs of its exact sum, each in a 64-bit word
+    QuerySetup* setup;              // per wide query
+    uint32_t segcap, round;         // room of a segment; wide queries per round
+    int tiles;                      // tiles of the map
+};
+
 struct EvalArgs {
     const pndf_query* q;
     const uint32_t* order;     // optional processing order (query index per slot)
@@ -315,6 +362,8 @@ struct EvalArgs {
     float tau;
     float s2r;
     int kernel;                // PNDF_KERNEL_*
+    const uint32_t* narrow;    // with tiles: slots from *narrow on hold the wide queries
+    TileWork tile;
 };
 hipError_t launch_eval(const HierDev& H, const EvalArgs& a, int algo, hipStream_t s);
 
@@ -348,7 +397,10 @@ hipError_t launch_projected_area(const HierDev& H, const ProjArgs& a, hipStream_
 
 // Spatial processing order of a batch: queries bucketed by the Morton code of their
 // centre cell (64 x 64 buckets over the torus), stream-ordered workspace.
-hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, uint32_t** order, hipStream_t s);
+// With tiles the wide queries come last and *narrow counts the others (device memory
+// of the same allocation), else *narrow is nullptr.
+hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, const TileWork& T, uint32_t** order,
+                      const uint32_t** narrow, hipStream_t s);
 // The same in the library's static per-GPU workspace (no allocation), for batches of
 // at most kStaticOrderQueries queries; the order must not be freed.
 constexpr int64_t kStaticOrderQueries = (int64_t)1 << 22;
@@ -356,6 +408,10 @@ hipError_t make_order_static(const HierDev& H, const pndf_query* q, int64_t nq, 
 // Bucket count and coordinate shift of the spatial order for a map of side 2^logn.
 void order_shape(int logn, int* nb, int* bshift);
 void free_order(uint32_t* order, hipStream_t s);
+// Workspace of the tiled evaluation for batches of nq queries (one allocation,
+// stream-ordered); w->ctl stays nullptr where it does not pay or there is no memory.
+void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s);
+void free_tiles(const TileWork& w, hipStream_t s);
 
 // ---------------------------------------------------------------- device side
 #if defined(__HIPCC__)
@@ -383,21 +439,28 @@ struct QuerySetup {
     bool valid;
 };
 
+// Validity and support half-widths of one query (the other fields are not set).
+__device__ __forceinline__ QuerySetup setup_support(const pndf_query& qr, float s2r)
+{
+    QuerySetup q;
+    const float lim = 16777216.0f;
+    bool ok = isfinite(qr.x) && isfinite(qr.y) && isfinite(qr.sx) && isfinite(qr.sy) &&
+              isfinite(qr.hx) && isfinite(qr.hy) && qr.sx > 0.f && qr.sy > 0.f;
+    q.rx = __fmul_rn(s2r, qr.sx);
+    q.ry = __fmul_rn(s2r, qr.sy);
+    q.valid = ok && fabsf(qr.x) <= lim && fabsf(qr.y) <= lim && q.rx <= lim && q.ry <= lim;
+    return q;
+}
+
 // Support box, entry level and kernel constants of one query (see pndf.h).
 __device__ inline QuerySetup setup_query(const pndf_query& qr, float s2r, float tau, int L,
                                          float eps, int kernel)
 {
-    QuerySetup q;
+    QuerySetup q = setup_support(qr, s2r);
+    const bool ok = q.valid;
+    const float rx = q.rx, ry = q.ry;
     q.kernel = kernel;
     q.x = qr.x; q.y = qr.y; q.hx = qr.hx; q.hy = qr.hy;
-    const float lim = 16777216.0f;
-    bool ok = isfinite(qr.x) && isfinite(qr.y) && isfinite(qr.sx) && isfinite(qr.sy) &&
-              isfinite(qr.hx) && isfinite(qr.hy) && qr.sx > 0.f && qr.sy > 0.f;
-    float rx = __fmul_rn(s2r, qr.sx), ry = __fmul_rn(s2r, qr.sy);
-    ok = ok && fabsf(qr.x) <= lim && fabsf(qr.y) <= lim && rx <= lim && ry <= lim;
-    q.valid = ok;
-    q.rx = rx;
-    q.ry = ry;
     q.hkey = half_key(__half_as_ushort(__float2half_rn(qr.hx))) |
              (half_key(__half_as_ushort(__float2half_rn(qr.hy))) << 16);
     const double hu = (double)qr.hx + (double)qr.hy, hv = (double)qr.hx - (double)qr.hy;

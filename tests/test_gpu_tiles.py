@@ -1,0 +1,78 @@
+"""Tiled evaluation of wide footprints: on maps with tiles an ordered batch (wide
+queries descend to the tiles, which are evaluated tile by tile) gives the bits of the
+same batch in input order (every query as a whole), for narrow, wide and invalid
+queries, every footprint kernel, and when rounds are short and the items do not fit."""
+import numpy as np
+import pytest
+
+from conftest import gpu_available
+
+pytestmark = [pytest.mark.gpu,
+              pytest.mark.skipif(not gpu_available(), reason="needs a HIP device")]
+
+
+def queries(n, count, seed, lo, hi):
+    rng = np.random.default_rng(seed)
+    q = np.empty((count, 6), np.float32)
+    q[:, :2] = rng.uniform(-n, 2 * n, (count, 2))
+    q[:, 2] = np.exp(rng.uniform(np.log(lo), np.log(hi), count))
+    q[:, 3] = q[:, 2] * np.exp(rng.uniform(-0.7, 0.7, count))
+    r, t = 0.3 * np.sqrt(rng.uniform(size=count)), rng.uniform(0, 2 * np.pi, count)
+    q[:, 4], q[:, 5] = r * np.cos(t), r * np.sin(t)
+    return q
+
+
+@pytest.fixture(scope="module", params=["powerlaw", "scratched"])
+def hier(request):
+    import torch
+    import workloads
+    import paper_2505_08985_amd as P
+    kw = {} if request.param == "powerlaw" else dict(scratches=1200, flakes=3000)
+    nrm = workloads.make_map(request.param, 1024, 41, **kw)
+    return P.build_hierarchy(P.build_mesh(torch.from_numpy(nrm).cuda()), cluster=True)
+
+
+# (no wide query; the threshold sigma = 256 / 3 between both; all wide, up to 4 maps)
+@pytest.mark.parametrize("lo,hi,count", [(0.5, 20.0, 4096), (60.0, 110.0, 4200), (90.0, 1300.0, 4097)])
+@pytest.mark.parametrize("tau", [0.0, 1e-4, 3e-2])
+def test_tiles_change_no_bit(hier, tau, lo, hi, count):
+    import torch
+    import paper_2505_08985_amd as P
+    q = queries(1024, count, 5, lo, hi)
+    q[7, 2] = np.nan
+    q[8, 2] = -1.0
+    q[9, 0] = np.inf
+    q[10, 2:4] = 3e7
+    q[11, :2] = 2e7
+    tq = torch.from_numpy(q).cuda()
+    a = P.eval_batch(hier, tq, tau=tau)
+    b = P.eval_batch(hier, tq, tau=tau, input_order=True)
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+    assert bool((a > 0).any()) and int(torch.isnan(a).sum()) == 5
+
+
+@pytest.mark.parametrize("kernel", ["disk", "box"])
+@pytest.mark.parametrize("tau", [0.0, 1e-3])
+def test_tiles_footprint_kernels(hier, kernel, tau):
+    import torch
+    import paper_2505_08985_amd as P
+    tq = torch.from_numpy(queries(1024, 4099, 9, 20.0, 700.0)).cuda()
+    a = P.eval_batch(hier, tq, tau=tau, kernel=kernel, sigma_to_r=1.5)
+    b = P.eval_batch(hier, tq, tau=tau, kernel=kernel, sigma_to_r=1.5, input_order=True)
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+# rounds of 1000 queries; rounds of 8, whose segments (4 items) a query's items overflow
+@pytest.mark.parametrize("chunk,count", [(1000, 4500), (8, 4096)])
+@pytest.mark.parametrize("tau", [0.0, 1e-4])
+def test_tiles_rounds_and_overflow(hier, monkeypatch, tau, chunk, count):
+    import torch
+    import paper_2505_08985_amd as P
+    q = queries(1024, count, 13, 1.0, 20.0)
+    q[::7] = queries(1024, len(q[::7]), 15, 90.0, 500.0)
+    tq = torch.from_numpy(q).cuda()
+    b = P.eval_batch(hier, tq, tau=tau, input_order=True)
+    monkeypatch.setenv("PNDF_LAUNCH_CHUNK", str(chunk))
+    for _ in range(2):
+        a = P.eval_batch(hier, tq, tau=tau)
+        assert torch.equal(a.view(torch.int32), b.view(torch.int32))
