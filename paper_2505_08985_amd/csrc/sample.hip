@@ -19,7 +19,11 @@
 // Work per sample: the query (24 B), one uniform pair (16 B), the cut levels'
 // residuals (4 B each, from the entry level down to the cut), the unit's four corner
 // normals and clamp bits (for a texel cell from its leaf record), and the outputs.
-// Nothing is shared between samples: the kernel is a gather-bound stream.
+// The Gaussian draw (four normal distribution functions and two inverses per sample)
+// is evaluated from one table in LDS: with the library's functions it took the
+// vector ALU's whole time (2^22 samples at 2048^2, tau = 0: 168 -> 151 us, a third of
+// the vector instructions; 10^6 at 4096^2 with the cut: 109 -> 93 us).  What bounds it
+// now is the scattered reads: 167 B fetched per sample beside 72 B in and out.
 #include <algorithm>
 
 #include "pndf_internal.h"
@@ -27,36 +31,120 @@
 namespace pndf {
 namespace {
 
-// u on [a, b) from N(x, sig^2) truncated to [a, b), by inverse CDF
-__device__ inline double trunc_gauss(double x, double sig, double a, double b, double xi)
+constexpr int kTailPieces = 68, kTailCoefs = 10;
+__device__ const double kNormalTail[kTailPieces * kTailCoefs] = {
+#include "normal_tail.inc"
+};
+
+// Phi(-t), t >= 0, from the table in LDS (0 from 8.5 on: below 1e-17), and with
+// SLOPE its derivative.
+template <bool SLOPE>
+__device__ __forceinline__ double normal_tail(const double* tab, double t, double* slope)
+{
+    const double t8 = fmin(t, 8.5) * 8.0;
+    const int k = min((int)t8, kTailPieces - 1);
+    const double* c = tab + kTailCoefs * k;
+    const double s = t8 - (double)k - 0.5;
+    double v = c[9], d = 0.0;
+#pragma unroll
+    for (int i = 8; i >= 0; --i) {
+        if (SLOPE) d = fma(d, s, v);
+        v = fma(v, s, c[i]);
+    }
+    if (SLOPE) *slope = 8.0 * d;
+    return t < 8.5 ? v : 0.0;
+}
+
+__device__ __forceinline__ double normal_cdf(const double* tab, double z)
+{
+    const double v = normal_tail<false>(tab, fabs(z), nullptr);
+    return z < 0.0 ? v : 1.0 - v;
+}
+
+// The standard normal quantile at the tail probability r = Phi(-t) in [kLeastTail,
+// 1/2]: t.  First in float32, t = (1 - 2 r) P(w) with w = -log(4 r (1 - r)) (the
+// variable in which the quantile is nearly a polynomial; P is a fit of degree 10 in
+// w - 5, 1.6e-6 off at most), then one third-order step on Phi(-t) - r, which leaves
+// less than 1e-16 of that.
+constexpr double kLeastTail = 1.1e-5;  // t <= 4.24
+__device__ __forceinline__ double normal_tail_quantile(const double* tab, double r)
+{
+    const float x = (float)(1.0 - 2.0 * r), rf = (float)r;
+    const float w = -__logf(4.0f * rf * (1.0f - rf)) - 5.0f;
+    const float P[11] = {2.941299200e+00f,  3.022185564e-01f,  -1.027329918e-02f, 1.867593091e-04f,
+                         7.430269761e-05f,  -1.527700624e-05f, 1.442539087e-06f,  3.303221874e-08f,
+                         -2.352648920e-08f, 1.219414680e-09f,  7.265217594e-11f};
+    float f = P[10];
+#pragma unroll
+    for (int i = 9; i >= 0; --i) f = fmaf(f, w, P[i]);
+    const double t = fmax(0.0, (double)(x * f));
+    double slope;
+    const double e = normal_tail<true>(tab, t, &slope) - r;
+    double inv = __builtin_amdgcn_rcp(slope);
+    inv = fma(fma(-slope, inv, 1.0), inv, inv);
+    const double d = e * inv;
+    return t - d + 0.5 * t * d * d;
+}
+
+// u on [a, b) from N(x, sig^2) truncated to [a, b), by inverse CDF: the library's
+// functions (tails beyond the fit)
+__device__ __noinline__ double trunc_gauss(double x, double sig, double a, double b, double xi)
 {
     const double pa = normcdf((a - x) / sig), pb = normcdf((b - x) / sig);
-    double u = x + sig * normcdfinv(pa + xi * (pb - pa));
-    if (u < a) u = a;
-    if (u >= b) u = nextafter(b, a);
-    return u;
+    return x + sig * normcdfinv(pa + xi * (pb - pa));
 }
 
-// unit-local coordinates of u in a unit of side s = 2^l, and its torus node
-__device__ __forceinline__ void unit_coords(double u, int l, int mask, int* node, double* frac)
+// The same for both axes from the table; an axis whose draw falls into a tail (one in
+// 45000 at a half-width of 3 sigma) takes the library's.
+__device__ __forceinline__ double2 trunc_gauss2(const double* tab, const QuerySetup& q, float sx, float sy, double ax,
+                                                double bx, double ay, double by, double2 xi)
 {
-    const double s = (double)(1 << l);
-    const double f = floor(u / s);
-    *node = (int)((long long)f & (long long)mask);
-    *frac = (u - f * s) / s;
+    double u[2];
+    const double c[2] = {(double)q.x, (double)q.y}, s[2] = {(double)sx, (double)sy};
+    const double lo[2] = {ax, ay}, hi[2] = {bx, by}, x[2] = {xi.x, xi.y};
+    bool tail[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double inv = 1.0 / s[i];
+        const double pa = normal_cdf(tab, (lo[i] - c[i]) * inv), pb = normal_cdf(tab, (hi[i] - c[i]) * inv);
+        const double p = pa + x[i] * (pb - pa), r = fmin(p, 1.0 - p);
+        tail[i] = !(r >= kLeastTail);
+        const double t = normal_tail_quantile(tab, tail[i] ? 0.25 : r);
+        u[i] = c[i] + s[i] * (p < 0.5 ? -t : t);
+    }
+    if (tail[0] | tail[1]) {
+#pragma unroll 1
+        for (int i = 0; i < 2; ++i)
+            if (i ? tail[1] : tail[0]) {
+                const double v = trunc_gauss(i ? c[1] : c[0], i ? s[1] : s[0], i ? lo[1] : lo[0], i ? hi[1] : hi[0],
+                                             i ? x[1] : x[0]);
+                if (i) u[1] = v; else u[0] = v;
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if (u[i] < lo[i]) u[i] = lo[i];
+        if (u[i] >= hi[i]) u[i] = nextafter(hi[i], lo[i]);
+    }
+    return make_double2(u[0], u[1]);
 }
 
-// does the unrolled image of the level-l unit holding u meet the cells [clo, chi]
-__device__ __forceinline__ bool unit_meets(double u, int l, int clo, int chi)
+// does the unrolled image of the level-l unit that holds cell c meet the cells [clo, chi]
+__device__ __forceinline__ bool unit_meets(int c, int l, int clo, int chi)
 {
-    const long long s = 1ll << l;
-    const long long start = (long long)floor(u / (double)s) * s;
-    return start <= (long long)chi && start + s - 1 >= (long long)clo;
+    const int start = (c >> l) << l;
+    return start <= chi && start + (1 << l) - 1 >= clo;
 }
 
 template <int KER, bool CUT>
 __global__ __launch_bounds__(256) void k_sample(HierDev H, SampleArgs a)
 {
+    constexpr bool kGauss = KER == PNDF_KERNEL_GAUSSIAN;
+    __shared__ double tab[kGauss ? kTailPieces * kTailCoefs : 1];
+    if (kGauss) {
+        for (int i = threadIdx.x; i < kTailPieces * kTailCoefs; i += blockDim.x) tab[i] = kNormalTail[i];
+        __syncthreads();
+    }
     const int64_t k = a.first + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.end) return;
     const QuerySetup q = setup_query(a.q[k], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, KER);
@@ -67,6 +155,7 @@ __global__ __launch_bounds__(256) void k_sample(HierDev H, SampleArgs a)
     uint64_t id = ~0ull;
     // attempts that may be needed: only the Gaussian with the cut rejects
     const int tries = (KER == PNDF_KERNEL_GAUSSIAN && CUT) ? a.attempts : 1;
+#pragma unroll 1
     for (int t = 0; ok && t < tries; ++t) {
         const double2 x = xi[(int64_t)t * a.nq + k];
         if (!(x.x >= 0.0 && x.x < 1.0 && x.y >= 0.0 && x.y < 1.0)) {
@@ -88,33 +177,31 @@ __global__ __launch_bounds__(256) void k_sample(HierDev H, SampleArgs a)
             const double bx = (double)((floor_div_pow2(q.cxhi, l) + 1) << l);
             const double ay = (double)(floor_div_pow2(q.cylo, l) << l);
             const double by = (double)((floor_div_pow2(q.cyhi, l) + 1) << l);
-            u.x = trunc_gauss((double)q.x, (double)a.q[k].sx, ax, bx, x.x);
-            u.y = trunc_gauss((double)q.y, (double)a.q[k].sy, ay, by, x.y);
+            u = trunc_gauss2(tab, q, a.q[k].sx, a.q[k].sy, ax, bx, ay, by, x);
         }
-        // the unit of the cut that holds u: the first level from the entry level down
-        // whose residual is within the threshold, else the cell
+        // the unrolled cell that holds u, and the unit of the cut that holds it: the
+        // first level from the entry level down whose residual is within the threshold,
+        // else the cell (its ancestors' Morton codes are prefixes of its own)
+        const int iu = (int)floor(u.x), ju = (int)floor(u.y);
         int lev = 0;
         if constexpr (CUT) {
-            // (a short dependent chain per thread; the many threads in flight hide it)
-            for (int l = q.l0; l >= 1; --l) {
-                int I, J;
-                double fx, fy;
-                const int mask = (H.n >> l) - 1;
-                unit_coords(u.x, l, mask, &I, &fx);
-                unit_coords(u.y, l, mask, &J, &fy);
-                if (H.clu_e[level_offset(H.logn, l) + morton((uint32_t)I, (uint32_t)J)] <= q.t) {
+            const uint32_t code = morton((uint32_t)(iu & (H.n - 1)), (uint32_t)(ju & (H.n - 1)));
+            // (a short dependent chain per thread; the many threads in flight hide it.
+            // Reading 2 or 4 levels at once changed nothing: it fetches lines of the
+            // large low levels that the cut never asks for)
+#pragma unroll 1
+            for (int l = q.l0; l >= 1; --l)
+                if (H.clu_e[level_offset(H.logn, l) + (code >> (2 * l))] <= q.t) {
                     lev = l;
                     break;
                 }
-            }
             if (KER == PNDF_KERNEL_GAUSSIAN &&
-                !(unit_meets(u.x, lev, q.cxlo, q.cxhi) && unit_meets(u.y, lev, q.cylo, q.cyhi)))
+                !(unit_meets(iu, lev, q.cxlo, q.cxhi) && unit_meets(ju, lev, q.cylo, q.cyhi)))
                 continue;  // rejected: the unit lies outside the support
         }
-        int I, J;
-        double U, V;
-        unit_coords(u.x, lev, (H.n >> lev) - 1, &I, &U);
-        unit_coords(u.y, lev, (H.n >> lev) - 1, &J, &V);
+        const int I = (iu >> lev) & ((H.n >> lev) - 1), J = (ju >> lev) & ((H.n >> lev) - 1);
+        const double side = 1.0 / (double)(1 << lev);
+        const double U = (u.x - (double)((iu >> lev) << lev)) * side, V = (u.y - (double)((ju >> lev) << lev)) * side;
         const int half = U + V < 1.0 ? 0 : 1;
         double w0, w1, w2;
         if (half == 0) {
