@@ -7,9 +7,124 @@
 #include <string>
 #include <vector>
 
+#include <chrono>
+#include <map>
+#include <mutex>
+
 #include "pndf_internal.h"
 
 namespace pndf {
+
+namespace {
+
+struct Blocks {
+    struct Kept {
+        void* p;
+        size_t size;
+        int dev;
+        std::chrono::steady_clock::time_point since;
+    };
+    std::mutex mu;
+    std::vector<Kept> kept;                            // oldest first
+    std::map<void*, std::pair<size_t, int>> used;      // size and device of every block handed out
+};
+
+// (never destroyed: handles may outlive the library's static objects)
+Blocks& blocks()
+{
+    static Blocks* b = new Blocks;
+    return *b;
+}
+
+// Give back the kept blocks that match; called with the lock held.
+template <typename Pred>
+void blocks_drop(Blocks& b, Pred match)
+{
+    size_t out = 0;
+    for (size_t i = 0; i < b.kept.size(); ++i) {
+        if (match(b.kept[i]))
+            (void)hipFree(b.kept[i].p);
+        else
+            b.kept[out++] = b.kept[i];
+    }
+    b.kept.resize(out);
+}
+
+void blocks_expire(Blocks& b)
+{
+    const auto now = std::chrono::steady_clock::now();
+    blocks_drop(b, [&](const Blocks::Kept& k) {
+        return std::chrono::duration<double>(now - k.since).count() > kBlockKeepSeconds;
+    });
+}
+
+}  // namespace
+
+hipError_t block_alloc(size_t bytes, void** p)
+{
+    *p = nullptr;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    Blocks& b = blocks();
+    std::lock_guard<std::mutex> lock(b.mu);
+    blocks_expire(b);
+    // the smallest kept block that holds it without wasting more than an eighth
+    size_t best = b.kept.size();
+    for (size_t i = 0; i < b.kept.size(); ++i) {
+        const Blocks::Kept& k = b.kept[i];
+        if (k.dev == dev && k.size >= bytes && k.size <= bytes + bytes / 8 &&
+            (best == b.kept.size() || k.size < b.kept[best].size))
+            best = i;
+    }
+    if (best < b.kept.size()) {
+        *p = b.kept[best].p;
+        b.used[*p] = {b.kept[best].size, dev};
+        b.kept.erase(b.kept.begin() + (long)best);
+        return hipSuccess;
+    }
+    e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory && !b.kept.empty()) {
+        (void)hipGetLastError();
+        blocks_drop(b, [](const Blocks::Kept&) { return true; });
+        e = hipMalloc(p, bytes);
+    }
+    if (e == hipSuccess) b.used[*p] = {bytes, dev};
+    return e;
+}
+
+void block_free(void* p)
+{
+    if (!p) return;
+    Blocks& b = blocks();
+    std::lock_guard<std::mutex> lock(b.mu);
+    const auto it = b.used.find(p);
+    if (it == b.used.end()) return;
+    const size_t size = it->second.first;
+    const int dev = it->second.second;
+    b.used.erase(it);
+    blocks_expire(b);
+    int cur = 0;
+    size_t avail = 0, total = 0;
+    bool keep = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess);
+    keep = keep && hipDeviceSynchronize() == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess &&
+           size <= total / kBlockKeepShare;
+    if (cur != dev) (void)hipSetDevice(cur);
+    if (!keep) {
+        (void)hipGetLastError();  // (a refused synchronisation is not the caller's error)
+        (void)hipFree(p);
+        return;
+    }
+    // the oldest ones make room
+    size_t held = size;
+    for (const Blocks::Kept& k : b.kept) held += k.dev == dev ? k.size : 0;
+    blocks_drop(b, [&](const Blocks::Kept& k) {
+        if (k.dev != dev || held <= total / kBlockKeepShare) return false;
+        held -= k.size;
+        return true;
+    });
+    b.kept.push_back({p, size, dev, std::chrono::steady_clock::now()});
+}
 
 static thread_local std::string g_last_error;
 
@@ -91,9 +206,7 @@ static void mesh_release(pndf_mesh* m)
 {
     if (!m) return;
     if (m->refs.fetch_sub(1) == 1) {
-        (void)hipFree(m->nrm);
-        (void)hipFree(m->deg);
-        (void)hipFree(m->det);
+        block_free(m->mem);
         delete m;
     }
 }
@@ -170,16 +283,23 @@ pndf_status pndf_build_mesh(const float* normals, int32_t n, float eps, void* st
     (void)hipGetDevice(&m->device);
     const size_t np = (size_t)(n + 1) * (n + 1), nc = (size_t)n * n;
     unsigned* d_flag = nullptr;
-    hipError_t e = hipMalloc(&m->nrm, sizeof(float2) * np);
-    if (e == hipSuccess) e = hipMalloc(&m->deg, nc);
-    if (e == hipSuccess) e = hipMalloc(&m->det, sizeof(float2) * nc);
-    if (e == hipSuccess) e = hipMalloc(&d_flag, sizeof(unsigned));
+    Arena mem;
+    auto layout = [&] {
+        mem.size = 0;
+        mem.place(&m->nrm, np);
+        mem.place(&m->deg, nc);
+        mem.place(&m->det, nc);
+        mem.place(&d_flag, 1);
+    };
+    layout();
+    hipError_t e = block_alloc(mem.size, &m->mem);
+    mem.base = (char*)m->mem;
+    if (e == hipSuccess) layout();
     if (e == hipSuccess) e = hipMemsetAsync(d_flag, 0, sizeof(unsigned), s);
     if (e == hipSuccess) e = launch_build_mesh(normals, n, eps, m->nrm, m->deg, m->det, d_flag, s);
     unsigned flag = 0;
     if (e == hipSuccess) e = hipMemcpyAsync(&flag, d_flag, sizeof(unsigned), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    (void)hipFree(d_flag);
     if (e != hipSuccess) {
         mesh_release(m);
         return hip_fail(e, "pndf_build_mesh");
@@ -236,20 +356,27 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
     int64_t nodes = 0;
     for (int l = 1; l <= m->L; ++l) nodes += (int64_t)(m->n >> l) * (m->n >> l);
     h->nodes = nodes;
-    hipError_t e = hipMalloc(&h->bbox, sizeof(float4) * nodes);
-    if (e == hipSuccess) e = hipMalloc(&h->oct_k, sizeof(uint4) * nodes);
-    if (e == hipSuccess) e = hipMalloc(&h->quad, sizeof(QuadRec) * (size_t)(m->n >> 1) * (size_t)(m->n >> 1));
-    if (cluster) {
-        if (e == hipSuccess) e = hipMalloc(&h->bbox_all, sizeof(float4) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->clu_n, sizeof(float4) * 2 * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->clu_e, sizeof(float) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->clu_det, sizeof(float2) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->clu_t, sizeof(float4) * 2 * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->bbox_clu, sizeof(float4) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->oct_c, sizeof(uint4) * 3 * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->clu_em, sizeof(float2) * nodes);
-        if (e == hipSuccess) e = hipMalloc(&h->tile_e, sizeof(float2) * 2 * kMaxTiles);
-    }
+    Arena mem;
+    auto layout = [&] {
+        mem.size = 0;
+        mem.place(&h->bbox, nodes);
+        mem.place(&h->oct_k, nodes);
+        mem.place(&h->quad, (size_t)(m->n >> 1) * (size_t)(m->n >> 1));
+        if (!cluster) return;
+        mem.place(&h->bbox_all, nodes);
+        mem.place(&h->clu_n, 2 * nodes);
+        mem.place(&h->clu_e, nodes);
+        mem.place(&h->clu_det, nodes);
+        mem.place(&h->clu_t, 2 * nodes);
+        mem.place(&h->bbox_clu, nodes);
+        mem.place(&h->oct_c, 3 * nodes);
+        mem.place(&h->clu_em, nodes);
+        mem.place(&h->tile_e, 2 * kMaxTiles);
+    };
+    layout();
+    hipError_t e = block_alloc(mem.size, &h->mem);
+    mem.base = (char*)h->mem;
+    if (e == hipSuccess) layout();
     fill_view(h);
     if (e == hipSuccess) e = build_hierarchy_levels(h, (hipStream_t)stream);
     if (e != hipSuccess) {
@@ -267,18 +394,7 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
 void pndf_destroy_hierarchy(pndf_hier* h)
 {
     if (!h) return;
-    (void)hipFree(h->bbox);
-    (void)hipFree(h->quad);
-    (void)hipFree(h->bbox_all);
-    (void)hipFree(h->clu_n);
-    (void)hipFree(h->clu_e);
-    (void)hipFree(h->clu_det);
-    (void)hipFree(h->clu_t);
-    (void)hipFree(h->bbox_clu);
-    (void)hipFree(h->oct_k);
-    (void)hipFree(h->oct_c);
-    (void)hipFree(h->clu_em);
-    (void)hipFree(h->tile_e);
+    block_free(h->mem);
     mesh_release(h->mesh);
     delete h;
 }
@@ -302,21 +418,22 @@ pndf_status pndf_hier_export_level(const pndf_hier* h, int32_t level, float* d_b
         return invalid("hierarchy has no clusters");
     hipStream_t s = (hipStream_t)stream;
     const int64_t off = level_offset(h->dev.logn, level);
-    const size_t m = (size_t)(h->mesh->n >> level) * (h->mesh->n >> level);
-    hipError_t e = hipSuccess;
-    const int side = h->mesh->n >> level;
-    (void)m;
-    auto cp = [&](void* dst, const void* src, int words) {
-        if (dst && e == hipSuccess) e = export_rowmajor(src, dst, side, words, s);
+    ExportArgs x;
+    auto add = [&](void* dst, const void* src, int words) {
+        if (!dst) return;
+        x.src[x.count] = (const uint32_t*)src;
+        x.dst[x.count] = (uint32_t*)dst;
+        x.words[x.count++] = words;
     };
-    cp(d_bbox, h->bbox + off, 4);
+    add(d_bbox, h->bbox + off, 4);
     if (h->cluster) {
-        cp(d_bbox_all, h->bbox_all + off, 4);
-        cp(d_bbox_clu, h->bbox_clu + off, 4);
-        cp(d_clu_n, h->clu_n + 2 * off, 8);
-        cp(d_clu_e, h->clu_e + off, 1);
-        cp(d_clu_det, h->clu_det + off, 2);
+        add(d_bbox_all, h->bbox_all + off, 4);
+        add(d_bbox_clu, h->bbox_clu + off, 4);
+        add(d_clu_n, h->clu_n + 2 * off, 8);
+        add(d_clu_e, h->clu_e + off, 1);
+        add(d_clu_det, h->clu_det + off, 2);
     }
+    const hipError_t e = export_rowmajor(x, h->mesh->n >> level, s);
     return e == hipSuccess ? PNDF_OK : hip_fail(e, "pndf_hier_export_level");
 }
 

@@ -24,6 +24,8 @@
 // int w |r|^2 = (w / 24) (sum |r_k|^2 + |sum r_k|^2) from its vertex values), a sum
 // of non-negative terms, instead of the difference C + tr(N*^T B) / 2 of large
 // numbers.
+#include <algorithm>
+
 #include "pndf_internal.h"
 
 namespace pndf {
@@ -71,8 +73,8 @@ __device__ __forceinline__ void half_basis(int hp, double U, double V, double mu
 // Add the statistics S of half hc of child (di, dj) (side 1/2 of the parent) to
 // half hp of the parent.  Child lower vertices (in parent-normalised coordinates):
 // (di, dj)/2, (di + 1, dj)/2, (di, dj + 1)/2; upper: (di + 1, dj + 1)/2,
-// (di, dj + 1)/2, (di + 1, dj)/2.  Called with literal arguments, so Lam folds
-// into constants.
+// (di, dj + 1)/2, (di + 1, dj)/2.  Called with literal arguments Lam folds into
+// constants.
 __device__ __forceinline__ void add_child(int di, int dj, int hc, int hp, const double* S, double* P)
 {
     const double x0 = 0.5 * di, x1 = 0.5 * (di + 1), y0 = 0.5 * dj, y1 = 0.5 * (dj + 1);
@@ -277,8 +279,24 @@ __device__ __forceinline__ uint4 oct_union4(const uint4* c)
     return oct_union(oct_union(c[0], c[1]), oct_union(c[2], c[3]));
 }
 
+// The arrays that the build writes, all levels packed, and one level's part of them.
+struct BuildDev {
+    uint4* oct_k;
+    uint4* oct_c;
+    float4* bbox;
+    float4* bbox_all;
+    float4* bbox_clu;
+    float4* clu_n;
+    float4* clu_t;
+    float* clu_e;
+    float2* clu_det;
+    double* nfit;      // FP64 fits of levels kFitLevel and above (workspace)
+    double* stat[2];   // half statistics of even and odd levels from 2 up (workspace)
+};
+constexpr int kFitLevel = 3;
+
 struct LevelOut {
-    uint4* oct_k;    // octagons of this level (HierDev::oct_k and the three of oct_c)
+    uint4* oct_k;
     uint4* oct_s;
     uint4* oct_o;
     uint4* oct_u;
@@ -289,21 +307,40 @@ struct LevelOut {
     float4* clu_t;
     float* clu_e;
     float2* clu_det;
+    double* nfit;      // nullptr below kFitLevel
+    double* stat;
 };
+
+__device__ __forceinline__ LevelOut level_out(const HierDev& H, const BuildDev& B, int level)
+{
+    const int64_t off = level_offset(H.logn, level);
+    LevelOut o;
+    o.oct_k = B.oct_k + off;
+    o.oct_s = B.oct_c + (int64_t)kOctSub * H.nodes + off;
+    o.oct_o = B.oct_c + (int64_t)kOctOwn * H.nodes + off;
+    o.oct_u = B.oct_c + (int64_t)kOctKids * H.nodes + off;
+    o.bbox = B.bbox + off;
+    o.bbox_all = B.bbox_all + off;
+    o.bbox_clu = B.bbox_clu + off;
+    o.clu_n = B.clu_n + 2 * off;
+    o.clu_t = B.clu_t + 2 * off;
+    o.clu_e = B.clu_e + off;
+    o.clu_det = B.clu_det + off;
+    o.nfit = level >= kFitLevel ? B.nfit + 8 * (off - level_offset(H.logn, kFitLevel)) : nullptr;
+    o.stat = B.stat[level & 1];
+    return o;
+}
 
 // Store the fitted normals of node idx (level side s): float32 normals, the cluster
 // triangles' Jacobians and clamp decisions (FP64 from the stored float32 normals, as
-// the evaluation uses them) with the test record that carries them, the FP64 normals
-// for the residual pass; returns the octagon of the cluster triangles.
-__device__ Oct store_cluster(const HierDev& H, const LevelOut& o, int64_t idx, int s, const double N[4][2],
-                                double* __restrict__ nfit)
+// the evaluation uses them) with the test record that carries them; returns the
+// octagon of the cluster triangles.
+__device__ __forceinline__ Oct store_cluster(const HierDev& H, const LevelOut& o, int64_t idx, int s, const double N[4][2])
 {
     float2 f[4];
     for (int k = 0; k < 4; ++k) f[k] = make_float2((float)N[k][0], (float)N[k][1]);
     o.clu_n[2 * idx] = make_float4(f[0].x, f[0].y, f[1].x, f[1].y);
     o.clu_n[2 * idx + 1] = make_float4(f[2].x, f[2].y, f[3].x, f[3].y);
-    double* nf = nfit + 8 * idx;
-    for (int k = 0; k < 4; ++k) { nf[2 * k] = N[k][0]; nf[2 * k + 1] = N[k][1]; }
     const double s2 = (double)s * (double)s;
     const double dl = jac64(f[0], f[1], f[2]) / s2;
     const double du = jac64(f[3], f[2], f[1]) / s2;
@@ -323,38 +360,100 @@ __device__ Oct store_cluster(const HierDev& H, const LevelOut& o, int64_t idx, i
     return b;
 }
 
-// Level 1: every node takes its 2 x 2 cells (8 fine triangles), writes its leaf
-// record, box and half statistics, and solves its fit.  Thread index = Morton code.
-__global__ void k_level1(HierDev H, LevelOut o, QuadRec* __restrict__ quad, double* __restrict__ stat,
-                         double* __restrict__ nfit, int cluster)
+// Weights of a record's 8 fine triangles (w / 24): cell c4, lower then upper.
+__device__ __forceinline__ void record_weights(const float2 tx[9], double eps, double w[8])
 {
-    const int m = H.n >> 1;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)m * m) return;
+#pragma unroll
+    for (int c4 = 0; c4 < 4; ++c4) {
+        const int k = 3 * (c4 >> 1) + (c4 & 1);
+        w[2 * c4] = fine_weight(jac64(tx[k], tx[k + 1], tx[k + 3]), eps) / 24.0;
+        w[2 * c4 + 1] = fine_weight(jac64(tx[k + 4], tx[k + 3], tx[k + 1]), eps) / 24.0;
+    }
+}
+
+// Residual of a level-1 record (its 8 fine triangles) against the fit N of its
+// ancestor of side `side`, the record's corner at cells (li, lj) of it.  The
+// interpolant (lower triangle N0 (1 - U - V) + N1 U + N2 V, upper N3 (U + V - 1) +
+// N2 (1 - U) + N1 (1 - V)) is linear but for its crease,
+//   N0 + (N1 - N0) U + (N2 - N0) V + (N0 - N1 - N2 + N3) max(0, U + V - 1),
+// so a corner takes two additions and a product per component.
+__device__ __forceinline__ double record_residual(const float2 tx[9], const double w[8], const double* N, int side, int li,
+                                                  int lj)
+{
+    const double inv = 1.0 / side;
+    const double bx = (N[2] - N[0]) * inv, by = (N[3] - N[1]) * inv, cx = (N[4] - N[0]) * inv, cy = (N[5] - N[1]) * inv;
+    const double dx = (N[0] - N[2] - N[4] + N[6]) * inv, dy = (N[1] - N[3] - N[5] + N[7]) * inv;
+    const double ax = N[0] + bx * li + cx * lj, ay = N[1] + by * li + cy * lj;
+    const int over = li + lj - side;
+    // row by row, so that two rows of corner residuals are live at a time
+    double rx[6], ry[6];
+    auto row = [&](int y, int at) {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            const double m = (double)max(0, over + x + y);
+            rx[at + x] = (double)tx[3 * y + x].x - (ax + bx * x + cx * y + dx * m);
+            ry[at + x] = (double)tx[3 * y + x].y - (ay + by * x + cy * y + dy * m);
+        }
+    };
+    row(0, 0);
+    double r = 0.0;
+#pragma unroll
+    for (int dj = 0; dj < 2; ++dj) {
+        row(dj + 1, 3);
+#pragma unroll
+        for (int di = 0; di < 2; ++di) {
+            const int k = di;
+            const int tri[2][3] = {{k, k + 1, k + 3}, {k + 4, k + 3, k + 1}};
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int p = tri[h][0], q = tri[h][1], s = tri[h][2];
+                const double sx = rx[p] + rx[q] + rx[s], sy = ry[p] + ry[q] + ry[s];
+                const double qq = rx[p] * rx[p] + ry[p] * ry[p] + rx[q] * rx[q] + ry[q] * ry[q] + rx[s] * rx[s] +
+                                  ry[s] * ry[s] + sx * sx + sy * sy;
+                r += w[2 * (2 * dj + di) + h] * qq;
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            rx[x] = rx[3 + x];
+            ry[x] = ry[3 + x];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    return r;
+}
+
+// A level-1 node t (Morton code) from its 2 x 2 cells (8 fine triangles): leaf record,
+// boxes and octagons; with clusters its half statistics (lo, up), fit and residual.
+// Returns its corners in tx and its triangles' weights in wgt.
+__device__ __forceinline__ void level1_node(const HierDev& H, const LevelOut& o, QuadRec* __restrict__ quad, int64_t t,
+                                            int cluster, float2 tx[9], double wgt[8], double* lo, double* up)
+{
     const int I = (int)morton_compact((uint32_t)t), J = (int)morton_compact((uint32_t)t >> 1);
     const int w = H.n + 1;
-    float2 tx[9];
+    uint8_t dg4[4];
     {
         QuadRec r;
         for (int y = 0; y < 3; ++y)
             for (int x = 0; x < 3; ++x) tx[3 * y + x] = r.t[3 * y + x] = H.nrm[(int64_t)(2 * J + y) * w + 2 * I + x];
         for (int dj = 0; dj < 2; ++dj)
-            for (int di = 0; di < 2; ++di) r.deg[2 * dj + di] = H.deg[(int64_t)(2 * J + dj) * H.n + 2 * I + di];
+            for (int di = 0; di < 2; ++di)
+                dg4[2 * dj + di] = r.deg[2 * dj + di] = H.deg[(int64_t)(2 * J + dj) * H.n + 2 * I + di];
         r.pad = 0;
         quad[t] = r;
     }
     Oct box = empty_oct();
-    for (int dj = 0; dj < 2; ++dj)
-        for (int di = 0; di < 2; ++di) {
-            const int k = 3 * dj + di;
-            const float2 n0 = tx[k], n1 = tx[k + 1], n2 = tx[k + 3], n3 = tx[k + 4];
-            const uint8_t dg = H.deg[(int64_t)(2 * J + dj) * H.n + 2 * I + di];
-            const float cx = 0.5f * (n1.x + n2.x), cy = 0.5f * (n1.y + n2.y);
-            if (dg & 1) oct_add_eqtri(box, cx, cy, H.rho);
-            else { oct_add(box, n0.x, n0.y); oct_add(box, n1.x, n1.y); oct_add(box, n2.x, n2.y); }
-            if (dg & 2) oct_add_eqtri(box, cx, cy, H.rho);
-            else { oct_add(box, n3.x, n3.y); oct_add(box, n2.x, n2.y); oct_add(box, n1.x, n1.y); }
-        }
+#pragma unroll
+    for (int c4 = 0; c4 < 4; ++c4) {
+        const int k = 3 * (c4 >> 1) + (c4 & 1);
+        const float2 n0 = tx[k], n1 = tx[k + 1], n2 = tx[k + 3], n3 = tx[k + 4];
+        const uint8_t dg = dg4[c4];
+        const float cx = 0.5f * (n1.x + n2.x), cy = 0.5f * (n1.y + n2.y);
+        if (dg & 1) oct_add_eqtri(box, cx, cy, H.rho);
+        else { oct_add(box, n0.x, n0.y); oct_add(box, n1.x, n1.y); oct_add(box, n2.x, n2.y); }
+        if (dg & 2) oct_add_eqtri(box, cx, cy, H.rho);
+        else { oct_add(box, n3.x, n3.y); oct_add(box, n2.x, n2.y); oct_add(box, n1.x, n1.y); }
+    }
     o.bbox[t] = box.b;
     const uint4 map_keys = oct_keys(box);
     o.oct_k[t] = map_keys;
@@ -362,7 +461,6 @@ __global__ void k_level1(HierDev H, LevelOut o, QuadRec* __restrict__ quad, doub
     const double eps = (double)H.eps;
     // the 8 fine triangles (cell c4 = di + 2 dj: lower (n0, n1, n2), upper (n3, n2, n1))
     // gathered into the node's halves
-    double lo[kStat] = {0}, up[kStat] = {0};
 #pragma unroll
     for (int c4 = 0; c4 < 4; ++c4) {
         const int k = 3 * (c4 >> 1) + (c4 & 1);
@@ -373,11 +471,9 @@ __global__ void k_level1(HierDev H, LevelOut o, QuadRec* __restrict__ quad, doub
         fine_stats(fine_weight(jac64(n3, n2, n1), eps), n3, n2, n1, F);
         add_child(c4 & 1, c4 >> 1, 1, c4 == 0 ? 0 : 1, F, c4 == 0 ? lo : up);
     }
-    double* M = stat + t * (2 * kStat);
-    for (int k = 0; k < kStat; ++k) { M[k] = lo[k]; M[kStat + k] = up[k]; }
     double N[4][2];
     solve_cluster(lo, up, N);
-    const Oct own = store_cluster(H, o, t, 2, N, nfit);
+    const Oct own = store_cluster(H, o, t, 2, N);
     const uint4 own_keys = oct_keys(own);
     float4 cb = own.b;
     o.bbox_clu[t] = cb;
@@ -387,168 +483,250 @@ __global__ void k_level1(HierDev H, LevelOut o, QuadRec* __restrict__ quad, doub
     o.oct_s[t] = oct_union(own_keys, map_keys);
     // (a level-1 node's children are cells: never asked for, excludes nothing)
     o.oct_u[t] = make_uint4(0u, 0xffffffffu, 0u, 0xffffffffu);
+    record_weights(tx, eps, wgt);
+    o.clu_e[t] = (float)record_residual(tx, wgt, &N[0][0], 2, 0, 0);
 }
 
-// Level l >= 2 from level l-1 (co: its arrays): boxes and octagons are unions of the
-// children's, half statistics gathered from the children's.  Thread index = Morton code; the children of node
-// t are 4t + (di + 2 dj).
-__global__ void k_level_up(HierDev H, int level, LevelOut o, const float4* __restrict__ cbox,
-                           const float4* __restrict__ cbox_all, LevelOut co, const double* __restrict__ cstat,
-                           double* __restrict__ stat, double* __restrict__ nfit, int cluster)
+// Level-1 nodes alone, one per thread (without clusters, or on the 2 x 2 map).
+__global__ __launch_bounds__(128) void k_level1(HierDev H, BuildDev B, QuadRec* __restrict__ quad, int cluster)
 {
-    const int m = H.n >> level;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)m * m) return;
-    const int64_t c00 = 4 * t;
-    float4 box = cbox[c00];
-    box_union(box, cbox[c00 + 1]);
-    box_union(box, cbox[c00 + 2]);
-    box_union(box, cbox[c00 + 3]);
-    o.bbox[t] = box;
-    o.oct_k[t] = oct_union4(co.oct_k + c00);
-    if (!cluster) return;
+    const int64_t m = H.n >> 1, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= m * m) return;
     double lo[kStat] = {0}, up[kStat] = {0};
-    gather_children([&](int c4, int h) { return cstat + (c00 + c4) * (2 * kStat) + h * kStat; }, lo, up);
-    double* M = stat + t * (2 * kStat);
-    for (int k = 0; k < kStat; ++k) { M[k] = lo[k]; M[kStat + k] = up[k]; }
-    double N[4][2];
+    float2 tx[9];
+    double wgt[8];
+    level1_node(H, level_out(H, B, 1), quad, t, cluster, tx, wgt, lo, up);
+}
+
+// Fit, boxes and octagons of node t of a level above 1 from its half statistics and
+// its children's boxes (co: their level).
+__device__ __forceinline__ void finish_node(const HierDev& H, const LevelOut& o, const LevelOut& co, int64_t t, int level,
+                                            const double* lo, const double* up, double N[4][2])
+{
+    const int64_t c00 = 4 * t;
     solve_cluster(lo, up, N);
-    const Oct own = store_cluster(H, o, t, 1 << level, N, nfit);
+    const Oct own = store_cluster(H, o, t, 1 << level, N);
     const uint4 own_keys = oct_keys(own);
     o.oct_o[t] = own_keys;
     o.oct_s[t] = oct_union(own_keys, oct_union4(co.oct_s + c00));
     o.oct_u[t] = oct_union4(co.oct_o + c00);
     float4 cb = own.b;
     o.bbox_clu[t] = cb;
-    box_union(cb, cbox_all[c00]);
-    box_union(cb, cbox_all[c00 + 1]);
-    box_union(cb, cbox_all[c00 + 2]);
-    box_union(cb, cbox_all[c00 + 3]);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) box_union(cb, co.bbox_all[c00 + c]);
     o.bbox_all[t] = cb;
 }
 
-// The cluster interpolant of a node at node-normalised (U, V): lower triangle
-// N0 (1 - U - V) + N1 U + N2 V, upper N3 (U + V - 1) + N2 (1 - U) + N1 (1 - V)
-// (continuous across the diagonal).
-__device__ __forceinline__ double2 cluster_field(const double* N, double U, double V)
+__device__ __forceinline__ void union_boxes(const LevelOut& o, const LevelOut& co, int64_t t)
 {
-    if (U + V <= 1.0) {
-        const double a = 1.0 - U - V;
-        return make_double2(N[0] * a + N[2] * U + N[4] * V, N[1] * a + N[3] * U + N[5] * V);
+    const int64_t c00 = 4 * t;
+    float4 box = co.bbox[c00];
+#pragma unroll
+    for (int c = 1; c < 4; ++c) box_union(box, co.bbox[c00 + c]);
+    o.bbox[t] = box;
+    o.oct_k[t] = oct_union4(co.oct_k + c00);
+}
+
+// Levels 1 and 2 with clusters, one level-1 node per thread and its parents by a
+// quarter of the workgroup: the level-1 statistics pass through LDS (at 2048^2 they
+// are 218 MB to write and to read again, and the fits 67 MB, of the 512 MB that a
+// level-1 pass wrote), and both levels' residuals are integrated here, from corners
+// that are still in registers.  (One level-2 node per thread, its children in turn,
+// takes 308 registers: one wave per SIMD, 269 us at 2048^2; this way 183 us; the
+// separate passes over both levels took 421.)
+constexpr int kLow = 128;
+__global__ __launch_bounds__(kLow) void k_levels12(HierDev H, BuildDev B, QuadRec* __restrict__ quad)
+{
+    __shared__ double st[kLow][2 * kStat + 1];  // (odd stride: no bank conflicts)
+    __shared__ double fit[kLow / 4][8];
+    const int64_t m1 = (int64_t)(H.n >> 1) * (H.n >> 1), t = (int64_t)blockIdx.x * kLow + threadIdx.x;
+    const LevelOut o1 = level_out(H, B, 1), o2 = level_out(H, B, 2);
+    float2 tx[9];
+    double wgt[8];
+    if (t < m1) {
+        double lo[kStat] = {0}, up[kStat] = {0};
+        level1_node(H, o1, quad, t, 1, tx, wgt, lo, up);
+        for (int k = 0; k < kStat; ++k) {
+            st[threadIdx.x][k] = lo[k];
+            st[threadIdx.x][kStat + k] = up[k];
+        }
     }
-    const double a = U + V - 1.0, b = 1.0 - U, c = 1.0 - V;
-    return make_double2(N[6] * a + N[4] * b + N[2] * c, N[7] * a + N[5] * b + N[3] * c);
+    __threadfence_block();
+    __syncthreads();
+    const int64_t p = (int64_t)blockIdx.x * (kLow / 4) + threadIdx.x;
+    if (threadIdx.x < kLow / 4 && 4 * p < m1) {
+        double lo[kStat] = {0}, up[kStat] = {0};
+        gather_children([&](int c4, int h) { return &st[4 * threadIdx.x + c4][h * kStat]; }, lo, up);
+        double* M = o2.stat + p * (2 * kStat);
+        for (int k = 0; k < kStat; ++k) { M[k] = lo[k]; M[kStat + k] = up[k]; }
+        union_boxes(o2, o1, p);
+        double N[4][2];
+        finish_node(H, o2, o1, p, 2, lo, up, N);
+        for (int k = 0; k < 4; ++k) { fit[threadIdx.x][2 * k] = N[k][0]; fit[threadIdx.x][2 * k + 1] = N[k][1]; }
+    }
+    __syncthreads();
+    double r = 0.0;
+    const int c4 = threadIdx.x & 3;
+    if (t < m1) r = record_residual(tx, wgt, fit[threadIdx.x >> 2], 4, 2 * (c4 & 1), 2 * (c4 >> 1));
+    r += __shfl_xor(r, 1);
+    r += __shfl_xor(r, 2);
+    if (c4 == 0 && t < m1) o2.clu_e[t >> 2] = (float)r;
+}
+
+// Node t of level >= 2 from the level below: boxes and octagons are unions of the
+// children's, half statistics gathered from theirs.
+__device__ __forceinline__ void level_up_node(const HierDev& H, const BuildDev& B, int level, int64_t t, int cluster)
+{
+    const LevelOut o = level_out(H, B, level), co = level_out(H, B, level - 1);
+    const int64_t c00 = 4 * t;
+    union_boxes(o, co, t);
+    if (!cluster) return;
+    double lo[kStat] = {0}, up[kStat] = {0};
+    gather_children([&](int c4, int h) { return co.stat + (c00 + c4) * (2 * kStat) + h * kStat; }, lo, up);
+    double* M = o.stat + t * (2 * kStat);
+    for (int k = 0; k < kStat; ++k) { M[k] = lo[k]; M[kStat + k] = up[k]; }
+    double N[4][2];
+    finish_node(H, o, co, t, level, lo, up, N);
+    double* nf = o.nfit + 8 * t;
+    for (int k = 0; k < 4; ++k) { nf[2 * k] = N[k][0]; nf[2 * k + 1] = N[k][1]; }
+}
+
+__global__ __launch_bounds__(64) void k_level_up(HierDev H, BuildDev B, int level, int cluster)
+{
+    const int64_t m = H.n >> level, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < m * m) level_up_node(H, B, level, t, cluster);
+}
+
+// The levels of at most kTopNodes nodes, one after the other in one workgroup (a
+// launch each took longer than their work).
+constexpr int kTopNodes = 256;
+__global__ __launch_bounds__(kTopNodes) void k_level_top(HierDev H, BuildDev B, int first, int cluster)
+{
+    for (int level = first; level <= H.L; ++level) {
+        const int m = H.n >> level;
+        if ((int)threadIdx.x < m * m) level_up_node(H, B, level, threadIdx.x, cluster);
+        __threadfence_block();
+        __syncthreads();
+    }
 }
 
 constexpr int kResidBlock = 256;  // leaf records per block of the residual pass (a level-5 node)
 
-// Residual of level `level`: thread t (a level-1 record, Morton order) integrates the
-// residual of its 8 fine triangles against the FP64 fit of its level-`level`
-// ancestor t >> 2 (level - 1).  The 4^(level - 1) records of a node are consecutive:
-// up to a whole block they are summed by a fixed LDS tree and stored as e^l; above,
-// each block leaves a partial sum for k_resid_sum.  Deterministic.
-__global__ __launch_bounds__(kResidBlock) void k_resid(HierDev H, int level, const double* __restrict__ nfit,
-                                                       float* __restrict__ clu_e, double* __restrict__ part)
+// Residuals of levels kFitLevel and above, all in one pass: thread t (a level-1
+// record, Morton order) integrates the residual of its 8 fine triangles against the
+// FP64 fits of its ancestors t >> 2 (level - 1).  The 4^(level - 1) records of a node
+// are consecutive: up to a whole block they are summed by a fixed tree and stored as
+// e^l; above, each block leaves a partial sum per level for k_resid_sum.
+// Deterministic.  (A pass per level read the records and formed the weights, eight
+// divisions, anew each time: 56 us a level at 2048^2, 614 in all; now 106 us.)
+__global__ __launch_bounds__(kResidBlock) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_resid(HierDev H, BuildDev B, double* __restrict__ part)
 {
-    __shared__ double red[kResidBlock];
+    __shared__ double red[kMaxLevels + 1][kResidBlock / 64];
     const int64_t m1 = (int64_t)(H.n >> 1) * (H.n >> 1);
     const int64_t t = (int64_t)blockIdx.x * kResidBlock + threadIdx.x;
-    const int sh = 2 * (level - 1);
-    double r = 0.0;
+    float2 tx[9];
+    double wgt[8];
     if (t < m1) {
-        const int64_t node = t >> sh;
-        const double* N = nfit + 8 * node;
-        const int side = 1 << level;
-        const double inv = 1.0 / side;
-        const int li = (2 * (int)morton_compact((uint32_t)t)) & (side - 1);
-        const int lj = (2 * (int)morton_compact((uint32_t)t >> 1)) & (side - 1);
         const float4* rec = reinterpret_cast<const float4*>(H.quad + t);
         const float4 a = rec[0], b = rec[1], c = rec[2], d = rec[3], e = rec[4];
-        const float2 tx[9] = {make_float2(a.x, a.y), make_float2(a.z, a.w), make_float2(b.x, b.y),
-                              make_float2(b.z, b.w), make_float2(c.x, c.y), make_float2(c.z, c.w),
-                              make_float2(d.x, d.y), make_float2(d.z, d.w), make_float2(e.x, e.y)};
-        double rx[9], ry[9];
+        tx[0] = make_float2(a.x, a.y); tx[1] = make_float2(a.z, a.w); tx[2] = make_float2(b.x, b.y);
+        tx[3] = make_float2(b.z, b.w); tx[4] = make_float2(c.x, c.y); tx[5] = make_float2(c.z, c.w);
+        tx[6] = make_float2(d.x, d.y); tx[7] = make_float2(d.z, d.w); tx[8] = make_float2(e.x, e.y);
+        record_weights(tx, (double)H.eps, wgt);
+    }
+    const int ci = 2 * (int)morton_compact((uint32_t)t), cj = 2 * (int)morton_compact((uint32_t)t >> 1);
+#pragma unroll 1
+    for (int level = kFitLevel; level <= H.L; ++level) {
+        const int sh = 2 * (level - 1), side = 1 << level;
+        double r = 0.0;
+        // (a block lies in one node from level 5 up: its fit through the scalar cache)
+        const int64_t node = sh >= 8 ? ((int64_t)blockIdx.x * kResidBlock) >> sh : t >> sh;
+        const double* N = B.nfit + 8 * (level_offset(H.logn, level) - level_offset(H.logn, kFitLevel) + node);
+        if (t < m1) r = record_residual(tx, wgt, N, side, ci & (side - 1), cj & (side - 1));
+        const int group = sh >= 6 ? 64 : 1 << sh;
 #pragma unroll
-        for (int y = 0; y < 3; ++y)
-#pragma unroll
-            for (int x = 0; x < 3; ++x) {
-                const double2 f = cluster_field(N, (li + x) * inv, (lj + y) * inv);
-                rx[3 * y + x] = (double)tx[3 * y + x].x - f.x;
-                ry[3 * y + x] = (double)tx[3 * y + x].y - f.y;
-            }
-        const double eps = (double)H.eps;
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) {
-            const int k = 3 * (c4 >> 1) + (c4 & 1);
-            const int tri[2][3] = {{k, k + 1, k + 3}, {k + 4, k + 3, k + 1}};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int p = tri[h][0], q = tri[h][1], s = tri[h][2];
-                const double wgt = fine_weight(jac64(tx[p], tx[q], tx[s]), eps);
-                const double sx = rx[p] + rx[q] + rx[s], sy = ry[p] + ry[q] + ry[s];
-                const double qq = rx[p] * rx[p] + ry[p] * ry[p] + rx[q] * rx[q] + ry[q] * ry[q] + rx[s] * rx[s] +
-                                  ry[s] * ry[s] + sx * sx + sy * sy;
-                r += (wgt / 24.0) * qq;
-            }
+        for (int st = 1; st < 64; st <<= 1)
+            if (st < group) r += __shfl_xor(r, st);
+        float* e = B.clu_e + level_offset(H.logn, level);
+        if (sh <= 6) {
+            if ((threadIdx.x & (group - 1)) == 0 && t < m1) e[t >> sh] = (float)r;
+            continue;
         }
+        if ((threadIdx.x & 63) == 0) red[level][threadIdx.x >> 6] = r;
     }
-    if (sh == 0) {
-        if (t < m1) clu_e[t] = (float)r;
-        return;
-    }
-    red[threadIdx.x] = r;
-    const int group = sh >= 8 ? kResidBlock : 1 << sh;
-    for (int st = 1; st < group; st <<= 1) {
-        __syncthreads();
-        if ((threadIdx.x & (2 * st - 1)) == 0) red[threadIdx.x] += red[threadIdx.x + st];
-    }
-    if (group < kResidBlock || sh == 8) {
-        if ((threadIdx.x & (group - 1)) == 0 && t < m1) clu_e[t >> sh] = (float)red[threadIdx.x];
-    } else if (threadIdx.x == 0) {
-        part[blockIdx.x] = red[0];
+    __syncthreads();
+    const int level = 5 + (int)threadIdx.x;
+    if (level <= H.L) {
+        const double s = (red[level][0] + red[level][1]) + (red[level][2] + red[level][3]);
+        if (level == 5) B.clu_e[level_offset(H.logn, 5) + blockIdx.x] = (float)s;
+        else part[(int64_t)(level - 6) * gridDim.x + blockIdx.x] = s;
     }
 }
 
-// e^l of nodes larger than a block of the residual pass: the sum of the node's
-// `per` consecutive block partials, in order.
-__global__ void k_resid_sum(const double* __restrict__ part, int64_t nodes, int64_t per, float* __restrict__ clu_e)
+// The level and the node of entry i of the levels from `first` up, packed.
+__device__ __forceinline__ int packed_level(const HierDev& H, int first, int64_t i, int64_t* node)
 {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nodes) return;
-    double s = 0.0;
-    for (int64_t i = 0; i < per; ++i) s += part[k * per + i];
-    clu_e[k] = (float)s;
+    int level = first;
+    const int64_t off = level_offset(H.logn, first);
+    while (level < H.L && i + off >= level_offset(H.logn, level + 1)) ++level;
+    *node = i + off - level_offset(H.logn, level);
+    return level;
 }
 
-__global__ void k_export_rowmajor(const uint32_t* __restrict__ src, uint32_t* __restrict__ dst, int m,
-                                  int words)
+// e^l of the nodes larger than a block of the residual pass (levels 6 and above), one
+// workgroup per node: the sum of the node's consecutive block partials in a fixed
+// order.
+__global__ __launch_bounds__(256) void k_resid_sum(HierDev H, BuildDev B, const double* __restrict__ part, int64_t rblocks)
+{
+    __shared__ double red[256];
+    int64_t k;
+    const int level = packed_level(H, 6, blockIdx.x, &k);
+    const int64_t per = (int64_t)1 << (2 * (level - 5));
+    const double* p = part + (level - 6) * rblocks + k * per;
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < per; i += 256) s += p[i];
+    red[threadIdx.x] = s;
+    for (int o = 128; o > 0; o >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    }
+    if (threadIdx.x == 0) B.clu_e[level_offset(H.logn, level) + k] = (float)red[0];
+}
+
+// Row-major copies of up to kExports per-node arrays of one level in one launch.
+__global__ void k_export_rowmajor(ExportArgs x, int m)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= (int64_t)m * m) return;
     const uint32_t I = (uint32_t)(k % m), J = (uint32_t)(k / m);
-    const uint32_t* a = src + (int64_t)morton(I, J) * words;
-    uint32_t* b = dst + k * words;
-    for (int w = 0; w < words; ++w) b[w] = a[w];
+    const int64_t c = (int64_t)morton(I, J);
+    for (int i = 0; i < x.count; ++i) {
+        const int words = x.words[i];
+        const uint32_t* a = x.src[i] + c * words;
+        uint32_t* b = x.dst[i] + k * words;
+        for (int w = 0; w < words; ++w) b[w] = a[w];
+    }
 }
 
 }  // namespace
 
-hipError_t export_rowmajor(const void* src, void* dst, int m, int words, hipStream_t s)
+hipError_t export_rowmajor(const ExportArgs& x, int m, hipStream_t s)
 {
+    if (x.count == 0) return hipSuccess;
     const int64_t cnt = (int64_t)m * m;
-    hipLaunchKernelGGL(k_export_rowmajor, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s,
-                       (const uint32_t*)src, (uint32_t*)dst, m, words);
+    hipLaunchKernelGGL(k_export_rowmajor, dim3((unsigned)((cnt + 255) / 256)), dim3(256), 0, s, x, m);
     return hipGetLastError();
 }
 
-// e^l and the largest e^l of the four children side by side (HierDev::clu_em) of one
-// level: an expansion reads its four children's in one 32 B segment.
-__global__ void k_residual_pairs(HierDev H, int level, float2* __restrict__ em)
+// e^l and the largest e^l of the four children side by side (HierDev::clu_em): an
+// expansion reads its four children's in one 32 B segment.
+__global__ void k_residual_pairs(HierDev H, float2* __restrict__ em, float2* __restrict__ te)
 {
-    const int64_t m = (int64_t)(H.n >> level) * (H.n >> level);
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= m) return;
-    const int64_t idx = level_offset(H.logn, level) + t;
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx < 2 * kMaxTiles) te[idx] = make_float2(0.f, 0.f);  // (for k_tile_residuals)
+    if (idx >= (int64_t)H.nodes) return;
+    int64_t t;
+    const int level = packed_level(H, 1, idx, &t);
     float kids = INFINITY;
     if (level >= 2) {
         const float* ce = H.clu_e + level_offset(H.logn, level - 1) + 4 * t;
@@ -557,118 +735,86 @@ __global__ void k_residual_pairs(HierDev H, int level, float2* __restrict__ em)
     em[idx] = make_float2(H.clu_e[idx], kids);
 }
 
-// Largest residuals kTileDepth and kTileSpan levels beneath each node of a level
-// from kTileLevel up (HierDev::tile_e), one workgroup per node.
-__global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, int level, float2* __restrict__ te)
+// Largest residuals kTileDepth and kTileSpan levels beneath each node of the levels
+// from kTileLevel up (HierDev::tile_e, cleared before): one workgroup per node and
+// part of kTilePart values (the top nodes look over 4^9), the parts' maxima by atomic
+// maximum (the values are not negative, so their bits compare like them).
+constexpr int kTilePart = 16384;
+__global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, float2* __restrict__ te)
 {
     __shared__ float red[256];
-    const int64_t t = blockIdx.x;
-    float m[2];
+    int64_t t;
+    const int level = packed_level(H, kTileLevel, blockIdx.x, &t);
     for (int k = 0; k < 2; ++k) {
         const int down = min(k ? kTileSpan : kTileDepth, level - 1);  // (residuals start at level 1)
-        const int per = 1 << (2 * down);
+        const int per = 1 << (2 * down), first = blockIdx.y * kTilePart, last = min(per, first + kTilePart);
+        if (first >= last) continue;
         const float* e = H.clu_e + level_offset(H.logn, level - down) + per * t;
         float v = 0.f;
-        for (int i = threadIdx.x; i < per; i += 256) v = fmaxf(v, e[i]);
+#pragma unroll 8
+        for (int i = first + (int)threadIdx.x; i < last; i += 256) v = fmaxf(v, e[i]);
         red[threadIdx.x] = v;
         for (int o = 128; o > 0; o >>= 1) {
             __syncthreads();
             if ((int)threadIdx.x < o) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + o]);
         }
-        __syncthreads();
-        m[k] = red[0];
+        if (threadIdx.x == 0) atomicMax(reinterpret_cast<unsigned*>(te) + 2 * blockIdx.x + k, __float_as_uint(red[0]));
         __syncthreads();
     }
-    if (threadIdx.x == 0)
-        te[level_offset(H.logn, level) - level_offset(H.logn, kTileLevel) + t] = make_float2(m[0], m[1]);
 }
 
 hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
 {
     const HierDev& H = h->dev;
-    const int n = H.n;
-    const int64_t m1 = (int64_t)(n >> 1) * (n >> 1);
+    const int n = H.n, cluster = h->cluster;
+    const int64_t m1 = (int64_t)(n >> 1) * (n >> 1), m2 = (int64_t)(n >> 2) * (n >> 2), m3 = (int64_t)(n >> 3) * (n >> 3);
     const int64_t rblocks = (m1 + kResidBlock - 1) / kResidBlock;
-    // workspace (cluster fits only): half statistics of two consecutive levels, the
-    // FP64 normals of the current level, block partials of the residual pass
-    double* stat[2] = {nullptr, nullptr};
-    double* nfit = nullptr;
+    const int64_t fits = H.L >= kFitLevel ? h->nodes - level_offset(H.logn, kFitLevel) : 0;
+    BuildDev B{h->oct_k, h->oct_c, h->bbox, h->bbox_all, h->bbox_clu, h->clu_n, h->clu_t, h->clu_e, h->clu_det, nullptr, {}};
+    // workspace (cluster fits only), one allocation: half statistics of even and odd
+    // levels from 2 up, FP64 fits, block partials of the residual pass
+    double* work = nullptr;
     double* part = nullptr;
     hipError_t err = hipSuccess;
-    auto release = [&]() {
-        (void)hipFree(stat[0]);
-        (void)hipFree(stat[1]);
-        (void)hipFree(nfit);
-        (void)hipFree(part);
-    };
-    if (h->cluster) {
-        const int64_t m2 = n >= 4 ? (int64_t)(n >> 2) * (n >> 2) : 1;
-        err = hipMalloc(&stat[0], sizeof(double) * 2 * kStat * m1);
-        if (err == hipSuccess) err = hipMalloc(&stat[1], sizeof(double) * 2 * kStat * m2);
-        if (err == hipSuccess) err = hipMalloc(&nfit, sizeof(double) * 8 * m1);
-        if (err == hipSuccess) err = hipMalloc(&part, sizeof(double) * rblocks);
-        if (err != hipSuccess) {
-            release();
-            return err;
+    if (cluster && H.L >= 2) {
+        const int upper = H.L > 5 ? H.L - 5 : 0;
+        err = block_alloc(sizeof(double) * (size_t)(2 * kStat * (m2 + m3) + 8 * fits + upper * rblocks), (void**)&work);
+        if (err != hipSuccess) return err;
+        B.stat[0] = work;
+        B.stat[1] = work + 2 * kStat * m2;
+        B.nfit = B.stat[1] + 2 * kStat * m3;
+        part = B.nfit + 8 * fits;
+    }
+    int level = 2;
+    if (cluster && H.L >= 2) {
+        hipLaunchKernelGGL(k_levels12, dim3((unsigned)((m1 + kLow - 1) / kLow)), dim3(kLow), 0, s, H, B, h->quad);
+        level = 3;
+    } else {
+        hipLaunchKernelGGL(k_level1, dim3((unsigned)((m1 + 127) / 128)), dim3(128), 0, s, H, B, h->quad, cluster);
+    }
+    for (; level <= H.L && (int64_t)(n >> level) * (n >> level) > kTopNodes; ++level) {
+        const int64_t m = (int64_t)(n >> level) * (n >> level);
+        hipLaunchKernelGGL(k_level_up, dim3((unsigned)((m + 63) / 64)), dim3(64), 0, s, H, B, level, cluster);
+    }
+    if (level <= H.L) hipLaunchKernelGGL(k_level_top, dim3(1), dim3(kTopNodes), 0, s, H, B, level, cluster);
+    if (cluster) {
+        if (H.L >= kFitLevel)
+            hipLaunchKernelGGL(k_resid, dim3((unsigned)rblocks), dim3(kResidBlock), 0, s, H, B, part);
+        if (H.L >= 6)
+            hipLaunchKernelGGL(k_resid_sum, dim3((unsigned)(h->nodes - level_offset(H.logn, 6))), dim3(256), 0, s, H, B, part,
+                               rblocks);
+        hipLaunchKernelGGL(k_residual_pairs, dim3((unsigned)((std::max<int64_t>(h->nodes, 2 * kMaxTiles) + 255) / 256)), dim3(256), 0, s, H, h->clu_em,
+                           h->tile_e);
+        if (has_tiles(H.logn)) {
+            const unsigned parts = std::max(1u, (1u << (2 * kTileSpan)) / kTilePart);
+            hipLaunchKernelGGL(k_tile_residuals, dim3((unsigned)(h->nodes - level_offset(H.logn, kTileLevel)), parts), dim3(256),
+                               0, s, H, h->tile_e);
         }
     }
-    auto out_for = [&](int level) {
-        LevelOut o;
-        const int64_t off = level_offset(H.logn, level);
-        o.bbox = h->bbox + off;
-        o.oct_k = h->oct_k + off;
-        o.oct_s = h->cluster ? h->oct_c + kOctSub * h->nodes + off : nullptr;
-        o.oct_o = h->cluster ? h->oct_c + kOctOwn * h->nodes + off : nullptr;
-        o.oct_u = h->cluster ? h->oct_c + kOctKids * h->nodes + off : nullptr;
-        o.bbox_all = h->cluster ? h->bbox_all + off : nullptr;
-        o.bbox_clu = h->cluster ? h->bbox_clu + off : nullptr;
-        o.clu_n = h->cluster ? h->clu_n + 2 * off : nullptr;
-        o.clu_e = h->cluster ? h->clu_e + off : nullptr;
-        o.clu_t = h->cluster ? h->clu_t + 2 * off : nullptr;
-        o.clu_det = h->cluster ? h->clu_det + off : nullptr;
-        return o;
-    };
-    auto residual = [&](int level) {
-        // (runs before the next level's fit overwrites nfit: one stream)
-        float* e = h->clu_e + level_offset(H.logn, level);
-        hipLaunchKernelGGL(k_resid, dim3((unsigned)rblocks), dim3(kResidBlock), 0, s, H, level, nfit, e, part);
-        const int sh = 2 * (level - 1);
-        if (sh > 8) {
-            const int64_t nodes = (int64_t)(n >> level) * (n >> level);
-            const int64_t per = ((int64_t)1 << sh) / kResidBlock;
-            hipLaunchKernelGGL(k_resid_sum, dim3((unsigned)((nodes + 63) / 64)), dim3(64), 0, s, part, nodes, per, e);
-        }
-        return hipGetLastError();
-    };
-    const int bs = 128;
-    hipLaunchKernelGGL(k_level1, dim3((unsigned)((m1 + bs - 1) / bs)), dim3(bs), 0, s, H, out_for(1),
-                       h->quad, stat[0], nfit, h->cluster);
     err = hipGetLastError();
-    if (err == hipSuccess && h->cluster) err = residual(1);
-    for (int level = 2; level <= H.L && err == hipSuccess; ++level) {
-        const int64_t m = (int64_t)(n >> level) * (n >> level);
-        const int64_t coff = level_offset(H.logn, level - 1);
-        const double* cs = stat[(level - 2) & 1];
-        double* os = stat[(level - 1) & 1];
-        hipLaunchKernelGGL(k_level_up, dim3((unsigned)((m + bs - 1) / bs)), dim3(bs), 0, s, H,
-                           level, out_for(level), h->bbox + coff,
-                           h->cluster ? h->bbox_all + coff : nullptr, out_for(level - 1), cs, os, nfit, h->cluster);
-        err = hipGetLastError();
-        if (err == hipSuccess && h->cluster) err = residual(level);
-    }
-    for (int level = 1; level <= H.L && err == hipSuccess && h->cluster; ++level) {
-        const int64_t m = (int64_t)(n >> level) * (n >> level);
-        hipLaunchKernelGGL(k_residual_pairs, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, H, level, h->clu_em);
-        err = hipGetLastError();
-    }
-    for (int level = kTileLevel; level <= H.L && err == hipSuccess && h->cluster && has_tiles(H.logn); ++level) {
-        const int64_t m = (int64_t)(n >> level) * (n >> level);
-        hipLaunchKernelGGL(k_tile_residuals, dim3((unsigned)m), dim3(256), 0, s, H, level, h->tile_e);
-        err = hipGetLastError();
-    }
-    if (err == hipSuccess) err = hipStreamSynchronize(s);
-    release();
-    return err;
+    const hipError_t sync = hipStreamSynchronize(s);
+    block_free(work);
+    return err == hipSuccess ? sync : err;
 }
 
 }  // namespace pndf
