@@ -97,8 +97,9 @@ typedef struct pndf_eval_opts {
 } pndf_eval_opts;
 
 /* Batches of 4096 or more queries are processed in a spatial order (Morton buckets
- * of the footprint centres) for cache locality; results do not depend on the order.
- * This flag keeps the caller's order instead. */
+ * of the footprint centres) for cache locality, and on maps of 1024^2 and more the
+ * wide ones among them (support half-width above 256 texels) tile by tile; results do
+ * not depend on either.  This flag keeps the caller's order and whole queries. */
 enum { PNDF_EVAL_INPUT_ORDER = 1 };
 
 typedef struct pndf_hier_opts {
@@ -279,7 +280,10 @@ const char* pndf_last_error(void);
  * query's terms are summed exactly (192-bit fixed point), so the result is
  * bit-identical to pndf_eval_batch whatever the split, the schedule or the batch
  * composition.  The launch sequence (reset, spatial order, workers, finalize) is
- * instantiated once as a HIP graph and replayed per batch.
+ * instantiated once as a HIP graph and replayed per batch.  On maps of 1024^2 and
+ * more, with the spatial order, queries wider than 256 texels are evaluated tile by
+ * tile instead (as pndf_eval_batch does), in further launches of the same sequence;
+ * the statistics below count the workers' queries alone.
  */
 typedef struct pndf_plan pndf_plan;
 

@@ -987,6 +987,16 @@ __global__ __launch_bounds__(64) void k_eval_plain(HierDev H, EvalArgs a)
 // tiles.  Claims shrink towards the end of a share.
 constexpr unsigned kTileWaves = 256 * 24;  // 24 waves per compute unit are resident
 
+// A plan's kernels read the batch from its control block.
+__device__ __forceinline__ void batch_args(EvalArgs& a)
+{
+    if (a.batch) {
+        a.q = a.batch->q;
+        a.nq = a.batch->nq;
+        a.out = a.batch->out;
+    }
+}
+
 struct Claim {
     uint32_t at, end;
 };
@@ -1025,6 +1035,7 @@ template <bool CUT, int KER>
 __global__ __launch_bounds__(64) void k_tile_emit(HierDev H, EvalArgs a)
 {
     extern __shared__ uint32_t lds[];
+    batch_args(a);
     const TileWork& T = a.tile;
     const int lane = lane_id();
     const int64_t first = (int64_t)*a.narrow + a.slot0;
@@ -1164,6 +1175,7 @@ __global__ __launch_bounds__(256) void k_tile_scatter(TileWork T)
 // last thing of a round, so it clears the control block for the next one.
 __global__ __launch_bounds__(256) void k_tile_finish(EvalArgs a)
 {
+    batch_args(a);
     const int t = blockIdx.x * 256 + threadIdx.x;
     tile_reset(a.tile.ctl, t);
     const int64_t first = (int64_t)*a.narrow + a.slot0;
@@ -1205,7 +1217,7 @@ __device__ __forceinline__ void acc_atomic_add(Fix192* dst, const Fix192& v)
 }
 
 __global__ void k_persist_reset(QueueCtl* ctl, Fix192* acc, int* fexp, const pndf_query* q,
-                                long long nq, float* out, unsigned epoch, uint32_t* hist, int nb)
+                                long long nq, float* out, unsigned epoch, uint32_t* hist, int nb, TileCtl* tiles)
 {
     const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     for (long long i = t; i < nq; i += (long long)gridDim.x * blockDim.x) {
@@ -1216,6 +1228,8 @@ __global__ void k_persist_reset(QueueCtl* ctl, Fix192* acc, int* fexp, const pnd
     }
     if (hist)
         for (long long i = t; i < 2 * nb; i += (long long)gridDim.x * blockDim.x) hist[i] = 0;
+    if (tiles)
+        for (long long i = t; i < kMaxTiles; i += (long long)gridDim.x * blockDim.x) tile_reset(tiles, (int)i);
     if (t == 0) {
         for (int x = 0; x < kXcds; ++x) ctl->qhead[x].v = 0;
         ctl->head = 0;
@@ -1289,7 +1303,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     uint32_t* lists = lds + (size_t)wave * wave_lds_words(H.L, CUT);
     QueueCtl* ctl = pa.Q.ctl;
-    const long long nq = ctl->nq;
+    const long long nall = ctl->nq, nq = pa.narrow ? (long long)*pa.narrow : nall;  // (the wide ones run tiled)
     const pndf_query* qs = ctl->q;
     const unsigned epoch = ctl->epoch;
     // worker waves per XCD (block b runs on XCD b mod 8)
@@ -1408,7 +1422,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 const int wl = (int)((word >> 26) & 0x3fu);
                 const uint64_t wm = word & 0x3ffffffu;
                 ok = 1;
-                if (wq >= nq || wl < 1 || wl > H.L || wm >= (uint64_t)(H.n >> wl) * (uint64_t)(H.n >> wl)) {
+                if (wq >= nall || wl < 1 || wl > H.L || wm >= (uint64_t)(H.n >> wl) * (uint64_t)(H.n >> wl)) {
                     atomicOr(&ctl->error, 4u);
                     ok = 0;
                 }
@@ -1476,27 +1490,6 @@ __global__ void k_persist_finalize(const QueueCtl* ctl, const Fix192* acc, const
     }
 }
 
-// The wide queries of a batch, in rounds (their number is known on the
-// device only: a round without any costs its five launches).
-template <bool CUT, int KER>
-hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s)
-{
-    const size_t lds = sizeof(uint32_t) * wave_lds_words(H.L, CUT);
-    for (int64_t off = 0; off < a.nq; off += a.tile.round) {
-        a.slot0 = off;
-        hipLaunchKernelGGL((k_tile_emit<CUT, KER>), dim3((unsigned)std::min<int64_t>(kTileWaves, a.nq - off)), dim3(64), lds,
-                           s, H, a);
-        hipLaunchKernelGGL(k_tile_hist, dim3(kTileSegs * kTileParts), dim3(256), 0, s, a.tile);
-        hipLaunchKernelGGL(k_tile_scatter, dim3(kTileSegs * kTileParts), dim3(256), 0, s, a.tile);
-        hipLaunchKernelGGL((k_eval_tiles<CUT, KER>), dim3(kTileWaves), dim3(64), lds, s, H, a);
-        const unsigned fin = (unsigned)std::max<int64_t>(kMaxTiles / 256, std::min<int64_t>(1024, (a.nq - off + 255) / 256));
-        hipLaunchKernelGGL(k_tile_finish, dim3(fin), dim3(256), 0, s, a);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
 // Launches cover at most launch_chunk() queries (grid dimensions stay far below
 // 2^32 work-items).
 template <int MODE, int KER>
@@ -1521,8 +1514,6 @@ hipError_t launch_mode(const HierDev& H, const EvalArgs& a0, int algo, hipStream
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (MODE == kModeValue && a0.narrow)
-        return a0.tau > 0.f ? launch_tiles<true, KER>(H, a0, s) : launch_tiles<false, KER>(H, a0, s);
     return hipSuccess;
 }
 
@@ -1536,20 +1527,6 @@ hipError_t launch_kernel(const HierDev& H, const EvalArgs& a, int algo, hipStrea
 
 // ------------------------------------------------------------ query order
 constexpr int kOrderBits = 6;  // 64 x 64 buckets
-
-// With tiles, buckets [nb, 2 nb) hold the wide queries (half-width above `wide`), so
-// they come last in the same spatial order.
-struct OrderArgs {
-    const pndf_query* q;
-    int64_t nq;
-    int n, bshift, nb, bins;   // bins = 2 nb with tiles, else nb
-    float s2r, wide;
-    uint32_t* key;
-    uint32_t* hist;            // bins counters, then bins cursors
-    uint32_t* order;
-    uint32_t* narrow;          // number of queries that are not wide (nullptr without tiles)
-    TileCtl* ctl;
-};
 
 __global__ void k_order_zero(OrderArgs o)
 {
@@ -1641,7 +1618,8 @@ __device__ __forceinline__ void order_scatter(const uint32_t* __restrict__ key, 
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_hist(OrderArgs o)
 {
-    order_hist(o.q, o.nq, o.n, o.bshift, o.nb, o.bins, o.s2r, o.wide, o.key, o.hist);
+    const pndf_query* q = o.batch ? o.batch->q : o.q;
+    order_hist(q, o.batch ? o.batch->nq : o.nq, o.n, o.bshift, o.nb, o.bins, o.s2r, o.wide, o.key, o.hist);
 }
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(OrderArgs o)
@@ -1649,24 +1627,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(OrderArgs o)
     __shared__ uint32_t first[kOrderMaxBins];
     order_scan(o.hist, o.bins, first);
     if (o.narrow && blockIdx.x == 0 && threadIdx.x == 0) *o.narrow = first[o.nb];
-    order_scatter(o.key, o.nq, o.bins, first, o.hist + o.bins, o.order);
-}
-
-// The same two passes for a persistent plan, reading the batch from its control
-// block (so the launch graph needs no per-run arguments for them).
-__global__ __launch_bounds__(kOrderThreads) void k_porder_hist(const QueueCtl* ctl, int n, int bshift, int nb,
-                                                               uint32_t* __restrict__ key, uint32_t* __restrict__ hist)
-{
-    order_hist(ctl->q, ctl->nq, n, bshift, nb, nb, 0.f, 0.f, key, hist);
-}
-
-__global__ __launch_bounds__(kOrderThreads) void k_porder_scatter(const QueueCtl* ctl, int nb,
-                                                                  const uint32_t* __restrict__ key,
-                                                                  uint32_t* __restrict__ hist, uint32_t* __restrict__ order)
-{
-    __shared__ uint32_t first[kOrderMaxBins];
-    order_scan(hist, nb, first);
-    order_scatter(key, ctl->nq, nb, first, hist + nb, order);
+    order_scatter(o.key, o.batch ? o.batch->nq : o.nq, o.bins, first, o.hist + o.bins, o.order);
 }
 
 }  // namespace
@@ -1688,14 +1649,10 @@ static unsigned order_blocks(int64_t nq)
 
 // The three passes of the spatial order into buf = order[nq] | key[nq] | hist[2 bins] |
 // narrow (the counters are cleared by a kernel, never a memset node).
-static size_t order_words(int nb, bool tiles) { return (size_t)(tiles ? 4 : 2) * nb + 1; }
-
-static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, TileCtl* ctl, uint32_t* buf,
-                               const uint32_t** narrow, hipStream_t s)
+static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, TileCtl* ctl, uint32_t* buf)
 {
     OrderArgs o{};
     order_shape(H.logn, &o.nb, &o.bshift);
-    o.q = q;
     o.nq = nq;
     o.n = H.n;
     o.bins = ctl ? 2 * o.nb : o.nb;
@@ -1706,6 +1663,14 @@ static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq
     o.hist = o.key + nq;
     o.ctl = ctl;
     o.narrow = ctl ? o.hist + 2 * o.bins : nullptr;
+    return o;
+}
+
+static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, TileCtl* ctl, uint32_t* buf,
+                               const uint32_t** narrow, hipStream_t s)
+{
+    OrderArgs o = order_args(H, nq, s2r, ctl, buf);
+    o.q = q;
     if (narrow) *narrow = o.narrow;
     const unsigned g = order_blocks(nq);
     hipLaunchKernelGGL(k_order_zero, dim3(8), dim3(kOrderThreads), 0, s, o);
@@ -1774,10 +1739,10 @@ hipError_t make_order_static(const HierDev& H, const pndf_query* q, int64_t nq, 
     return e;
 }
 
-void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s)
+static size_t tiles_layout(const HierDev& H, int64_t nq, char* base, TileWork* w)
 {
     *w = TileWork{};
-    if (!has_tiles(H.logn)) return;
+    if (!has_tiles(H.logn)) return 0;
     const int64_t chunk = std::min(kTileChunk, launch_chunk()), slots = std::min(nq, chunk);
     w->round = (uint32_t)chunk;
     w->tiles = 1 << (2 * (H.logn - kTileLevel));
@@ -1785,26 +1750,35 @@ void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s)
     // a whole chunk; the rest is evaluated where it was found
     const int64_t items = std::min<int64_t>(2 * slots * w->tiles, kTileItems / kTileChunk * chunk);
     w->segcap = (uint32_t)((items + kTileSegs - 1) / kTileSegs);
-    const size_t n = (size_t)w->segcap * kTileSegs;
-    size_t off = (sizeof(TileCtl) + 255) & ~(size_t)255;
-    const size_t raw = off;
-    off += 8 * n;
-    const size_t srt = off;
-    off += 8 * n;
-    const size_t acc = off;
-    off += 48 * (size_t)slots;
-    const size_t set = off;
-    off += sizeof(QuerySetup) * (size_t)slots;
-    char* buf = nullptr;
-    if (hipMallocAsync((void**)&buf, off, s) != hipSuccess) {
+    Arena mem;
+    mem.base = base;
+    mem.place(&w->ctl, 1);
+    mem.place(&w->raw, (size_t)w->segcap * kTileSegs);
+    mem.place(&w->items, (size_t)w->segcap * kTileSegs);
+    mem.place(&w->acc, 6 * (size_t)slots);
+    mem.place(&w->setup, (size_t)slots);
+    return mem.size;
+}
+
+size_t tiles_bytes(const HierDev& H, int64_t nq)
+{
+    TileWork w;
+    return tiles_layout(H, nq, nullptr, &w);
+}
+
+void tiles_place(const HierDev& H, int64_t nq, void* base, TileWork* w) { tiles_layout(H, nq, static_cast<char*>(base), w); }
+
+void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s)
+{
+    *w = TileWork{};
+    const size_t bytes = tiles_bytes(H, nq);
+    void* buf = nullptr;
+    if (!bytes) return;
+    if (hipMallocAsync(&buf, bytes, s) != hipSuccess) {
         (void)hipGetLastError();
         return;
     }
-    w->ctl = reinterpret_cast<TileCtl*>(buf);
-    w->raw = reinterpret_cast<unsigned long long*>(buf + raw);
-    w->items = reinterpret_cast<unsigned long long*>(buf + srt);
-    w->acc = reinterpret_cast<unsigned long long*>(buf + acc);
-    w->setup = reinterpret_cast<QuerySetup*>(buf + set);
+    tiles_place(H, nq, buf, w);
 }
 
 void free_tiles(const TileWork& w, hipStream_t s)
@@ -1817,12 +1791,15 @@ void free_order(uint32_t* order, hipStream_t s)
     if (order) (void)hipFreeAsync(order, s);
 }
 
+static hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s);
+
 hipError_t launch_eval(const HierDev& H, const EvalArgs& a, int algo, hipStream_t s)
 {
     if (a.nq <= 0) return hipSuccess;
     if (a.offsets) return launch_kernel<kModeRecord>(H, a, algo, s);
     if (a.counts) return launch_kernel<kModeCount>(H, a, algo, s);
-    return launch_kernel<kModeValue>(H, a, algo, s);
+    const hipError_t e = launch_kernel<kModeValue>(H, a, algo, s);
+    return e == hipSuccess && a.narrow ? launch_tiles(H, a, s) : e;
 }
 
 // ---------------------------------------------------------------- persistent
@@ -1842,7 +1819,8 @@ static void reset_params(PersistPlan& P, const pndf_query* q, long long nq, floa
     P.rargs[5] = &P.rout;
     P.rargs[6] = &P.epoch;
     P.rargs[7] = &P.ohist;
-    P.rargs[8] = &P.order_nb;
+    P.rargs[8] = &P.order_bins;
+    P.rargs[9] = &P.tile.ctl;
     P.reset.func = (void*)k_persist_reset;
     P.reset.gridDim = dim3((unsigned)std::min<long long>(1024, (P.max_nq + 255) / 256 + 1));
     P.reset.blockDim = dim3(256);
@@ -1873,31 +1851,56 @@ int persist_resident_blocks(const HierDev& H, const PersistPlan& P)
 
 
 
-// Kernel-node parameters of the two order passes (spatial order of the batch; the
-// reset node clears their counters).
-static void order_params(PersistPlan& P, hipKernelNodeParams* hist, hipKernelNodeParams* scat)
+// The tile kernels for a plan's or call's cut setting and footprint kernel.
+struct TileFuncs {
+    void *emit, *tiles;
+};
+static TileFuncs tile_funcs(bool cut, int kernel)
 {
-    P.hargs[0] = &P.ctl;
-    P.hargs[1] = &P.on;
-    P.hargs[2] = &P.order_bshift;
-    P.hargs[3] = &P.order_nb;
-    P.hargs[4] = &P.okey;
-    P.hargs[5] = &P.ohist;
-    P.cargs[0] = &P.ctl;
-    P.cargs[1] = &P.order_nb;
-    P.cargs[2] = &P.okey;
-    P.cargs[3] = &P.ohist;
-    P.cargs[4] = &P.order;
-    *hist = hipKernelNodeParams{};
-    hist->func = (void*)k_porder_hist;
-    hist->gridDim = dim3(order_blocks(P.max_nq));
-    hist->blockDim = dim3(kOrderThreads);
-    hist->kernelParams = P.hargs;
-    *scat = hipKernelNodeParams{};
-    scat->func = (void*)k_porder_scatter;
-    scat->gridDim = dim3(order_blocks(P.max_nq));
-    scat->blockDim = dim3(kOrderThreads);
-    scat->kernelParams = P.cargs;
+    if (kernel == PNDF_KERNEL_BOX)
+        return cut ? TileFuncs{(void*)k_tile_emit<true, PNDF_KERNEL_BOX>, (void*)k_eval_tiles<true, PNDF_KERNEL_BOX>}
+                   : TileFuncs{(void*)k_tile_emit<false, PNDF_KERNEL_BOX>, (void*)k_eval_tiles<false, PNDF_KERNEL_BOX>};
+    if (kernel == PNDF_KERNEL_DISK)
+        return cut ? TileFuncs{(void*)k_tile_emit<true, PNDF_KERNEL_DISK>, (void*)k_eval_tiles<true, PNDF_KERNEL_DISK>}
+                   : TileFuncs{(void*)k_tile_emit<false, PNDF_KERNEL_DISK>, (void*)k_eval_tiles<false, PNDF_KERNEL_DISK>};
+    return cut ? TileFuncs{(void*)k_tile_emit<true, PNDF_KERNEL_GAUSSIAN>, (void*)k_eval_tiles<true, PNDF_KERNEL_GAUSSIAN>}
+               : TileFuncs{(void*)k_tile_emit<false, PNDF_KERNEL_GAUSSIAN>, (void*)k_eval_tiles<false, PNDF_KERNEL_GAUSSIAN>};
+}
+
+// The five launches of one round of wide queries (arguments a, kernels f); `add`
+// launches a kernel or appends it to a graph: add(function, grid, block, LDS bytes,
+// arguments).
+template <typename Add>
+static hipError_t tile_round(const HierDev& H, EvalArgs& a, const TileFuncs& f, Add add)
+{
+    const size_t lds = sizeof(uint32_t) * wave_lds_words(H.L, a.tau > 0.f);
+    const int64_t left = a.nq - a.slot0;
+    void* both[] = {(void*)&H, (void*)&a};
+    void* tile[] = {(void*)&a.tile};
+    void* all[] = {(void*)&a};
+    const dim3 sort(kTileSegs * kTileParts), b64(64), b256(256);
+    const unsigned fin = (unsigned)std::max<int64_t>(kMaxTiles / 256, std::min<int64_t>(1024, (left + 255) / 256));
+    hipError_t e = add(f.emit, dim3((unsigned)std::min<int64_t>(kTileWaves, left)), b64, lds, both);
+    if (e == hipSuccess) e = add((void*)k_tile_hist, sort, b256, 0, tile);
+    if (e == hipSuccess) e = add((void*)k_tile_scatter, sort, b256, 0, tile);
+    if (e == hipSuccess) e = add(f.tiles, dim3(kTileWaves), b64, lds, both);
+    if (e == hipSuccess) e = add((void*)k_tile_finish, dim3(fin), b256, 0, all);
+    return e;
+}
+
+// The wide queries of a batch, in rounds (their number is known on the device only: a
+// round without any costs its five launches).
+static hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s)
+{
+    const TileFuncs f = tile_funcs(a.tau > 0.f, a.kernel);
+    for (int64_t off = 0; off < a.nq; off += a.tile.round) {
+        a.slot0 = off;
+        const hipError_t e = tile_round(H, a, f, [&](void* fn, dim3 g, dim3 b, size_t lds, void** args) {
+            return hipLaunchKernel(fn, g, b, args, lds, s);
+        });
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 void persist_prepare(const HierDev& H, PersistPlan& P)
@@ -1915,19 +1918,27 @@ void persist_prepare(const HierDev& H, PersistPlan& P)
     P.pa.kernel = P.kernel;
     P.pa.split_level = P.split_level;
     P.pa.wait_ticks = P.wait_ticks;
-    P.okey = P.ohist = nullptr;
-    if (P.order) {
-        P.okey = P.order + P.max_nq;
-        P.ohist = P.okey + P.max_nq;
+    P.ohist = nullptr;
+    P.pa.narrow = nullptr;
+    P.targs.clear();
+    if (!P.order) return;
+    P.oargs = order_args(H, P.max_nq, P.s2r, P.tile.ctl, P.order);
+    P.oargs.batch = P.ctl;
+    P.ohist = P.oargs.hist;
+    P.order_bins = P.oargs.bins;
+    P.pa.narrow = P.oargs.narrow;
+    if (!P.tile.ctl) return;
+    for (int64_t off = 0; off < P.max_nq; off += P.tile.round) {
+        EvalArgs a{nullptr, P.order, P.max_nq, off,     0,     nullptr,  nullptr,     nullptr,
+                   nullptr, nullptr, P.tau,    P.s2r, P.kernel, P.pa.narrow, P.tile};
+        a.batch = P.ctl;
+        P.targs.push_back(a);
     }
-    P.on = H.n;
 }
 
 hipError_t persist_graph_build(const HierDev& H, PersistPlan& P)
 {
     persist_prepare(H, P);
-    hipKernelNodeParams ohist{}, oscat{};
-    if (P.order) order_params(P, &ohist, &oscat);
     reset_params(P, nullptr, 0, nullptr);
     P.wargs[0] = &P.H;
     P.wargs[1] = &P.pa;
@@ -1949,16 +1960,33 @@ hipError_t persist_graph_build(const HierDev& H, PersistPlan& P)
     fin.kernelParams = P.fargs;
     fin.extra = nullptr;
     hipError_t e = hipGraphCreate(&P.graph, 0);
-    hipGraphNode_t nw = nullptr, nf = nullptr, nh = nullptr, nc = nullptr;
     if (e == hipSuccess) e = hipGraphAddKernelNode(&P.reset_node, P.graph, nullptr, 0, &P.reset);
-    hipGraphNode_t before_work = P.reset_node;
+    hipGraphNode_t last = P.reset_node;
+    auto chain = [&](const hipKernelNodeParams& p) {
+        hipGraphNode_t node = nullptr;
+        const hipError_t r = hipGraphAddKernelNode(&node, P.graph, &last, 1, &p);
+        last = node;
+        return r;
+    };
+    auto add = [&](void* fn, dim3 g, dim3 b, size_t lds, void** args) {
+        hipKernelNodeParams p{};
+        p.func = fn;
+        p.gridDim = g;
+        p.blockDim = b;
+        p.sharedMemBytes = (unsigned)lds;
+        p.kernelParams = args;
+        return chain(p);
+    };
+    P.hargs[0] = &P.oargs;
     if (P.order) {
-        if (e == hipSuccess) e = hipGraphAddKernelNode(&nh, P.graph, &P.reset_node, 1, &ohist);
-        if (e == hipSuccess) e = hipGraphAddKernelNode(&nc, P.graph, &nh, 1, &oscat);
-        before_work = nc;
+        const dim3 g(order_blocks(P.max_nq)), b(kOrderThreads);
+        if (e == hipSuccess) e = add((void*)k_order_hist, g, b, 0, P.hargs);
+        if (e == hipSuccess) e = add((void*)k_order_scatter, g, b, 0, P.hargs);
     }
-    if (e == hipSuccess) e = hipGraphAddKernelNode(&nw, P.graph, &before_work, 1, &work);
-    if (e == hipSuccess) e = hipGraphAddKernelNode(&nf, P.graph, &nw, 1, &fin);
+    if (e == hipSuccess) e = chain(work);
+    if (e == hipSuccess) e = chain(fin);  // (writes zeros for the wide queries, which the tiles then overwrite)
+    const TileFuncs f = tile_funcs(P.tau > 0.f, P.kernel);
+    for (size_t r = 0; r < P.targs.size() && e == hipSuccess; ++r) e = tile_round(P.H, P.targs[r], f, add);
     if (e == hipSuccess) e = hipGraphInstantiate(&P.exec, P.graph, nullptr, nullptr, 0);
     return e;
 }
@@ -1974,19 +2002,23 @@ hipError_t persist_run(PersistPlan& P, const pndf_query* q, long long nq, float*
         return e;
     }
     hipLaunchKernelGGL(k_persist_reset, P.reset.gridDim, P.reset.blockDim, 0, s, P.ctl, P.acc, P.fexp,
-                       q, nq, out, P.epoch, P.ohist, P.order_nb);
+                       q, nq, out, P.epoch, P.ohist, P.order_bins, P.tile.ctl);
     if (P.order) {
-        hipLaunchKernelGGL(k_porder_hist, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.ctl, P.on,
-                           P.order_bshift, P.order_nb, P.okey, P.ohist);
-        hipLaunchKernelGGL(k_porder_scatter, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.ctl, P.order_nb,
-                           P.okey, P.ohist, P.order);
+        hipLaunchKernelGGL(k_order_hist, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.oargs);
+        hipLaunchKernelGGL(k_order_scatter, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.oargs);
     }
     const size_t lds = sizeof(uint32_t) * 4 * wave_lds_words(P.H.L, P.tau > 0.f);
     void* args[] = {&P.H, &P.pa};
-    const hipError_t e = hipLaunchKernel(persist_func(P), dim3((unsigned)P.blocks), dim3(256), args, lds, s);
+    hipError_t e = hipLaunchKernel(persist_func(P), dim3((unsigned)P.blocks), dim3(256), args, lds, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_persist_finalize, P.reset.gridDim, dim3(256), 0, s, P.ctl, P.acc, P.fexp);
-    return hipGetLastError();
+    e = hipGetLastError();
+    const TileFuncs f = tile_funcs(P.tau > 0.f, P.kernel);
+    for (size_t r = 0; r < P.targs.size() && e == hipSuccess; ++r)
+        e = tile_round(P.H, P.targs[r], f, [&](void* fn, dim3 g, dim3 b, size_t l, void** x) {
+            return hipLaunchKernel(fn, g, b, x, l, s);
+        });
+    return e;
 }
 
 }  // namespace pndf

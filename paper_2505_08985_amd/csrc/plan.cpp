@@ -53,6 +53,7 @@ static void plan_free(pndf_plan* p)
     (void)hipFree(P.tasks);
     (void)hipFree(P.flags);
     (void)hipFree(P.order);
+    (void)hipFree(P.tile_mem);
     delete p;
 }
 
@@ -125,7 +126,14 @@ pndf_status pndf_plan_create(const pndf_hier* h, int64_t max_nq, const pndf_eval
     if (e == hipSuccess && !(o.flags & PNDF_EVAL_INPUT_ORDER)) {
         // workers take the queries in spatial (Morton bucket) order
         order_shape(h->dev.logn, &P.order_nb, &P.order_bshift);
-        e = hipMalloc(&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + 2 * (size_t)P.order_nb));
+        // ... and wide footprints run tiled (without the memory for it, as the others)
+        const size_t tiles = tiles_bytes(h->dev, max_nq);
+        if (tiles && hipMalloc(&P.tile_mem, tiles) != hipSuccess) {
+            (void)hipGetLastError();
+            P.tile_mem = nullptr;
+        }
+        if (P.tile_mem) tiles_place(h->dev, max_nq, P.tile_mem, &P.tile);
+        e = hipMalloc(&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + order_words(P.order_nb, P.tile.ctl != nullptr)));
     }
     // flags start at 0; the first run publishes with epoch 1
     if (e == hipSuccess) e = hipMemsetAsync(P.flags, 0, sizeof(unsigned) * P.capacity, (hipStream_t)stream);

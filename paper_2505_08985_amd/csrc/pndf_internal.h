@@ -9,6 +9,7 @@
 #include <atomic>
 #include <cstdint>
 #include <string>
+#include <vector>
 
 #include "../../include/pndf.h"
 
@@ -200,9 +201,72 @@ struct TaskQueue {
     unsigned long long capacity;
 };
 
+struct QuerySetup;
+
+// Tiled evaluation of wide footprints.  The nodes of level kTileLevel (256 x 256
+// texels) are tiles: everything the descent reads beneath one is about 3.7 MB, the
+// size of an XCD's L2.  The spatial order puts the queries that enter above that
+// level last; k_tile_emit descends them to it and leaves their surviving tiles as
+// items, the items are sorted by tile, and the waves of an XCD work through
+// neighbouring items, so that a tile's nodes come from memory about once per launch
+// instead of once per query.  An item holds the place of its query and the list item
+// (Morton code and flags) of its node, with the node's level.
+//
+// Under the cut the descent ends higher up and a tile may hold a few nodes only,
+// while an item costs about 700 vector instructions before its first useful one.  So
+// a node above the tile level becomes an item as a whole when all nodes kTileSpan
+// levels beneath it are under the cut (its part of the hierarchy is then as large as
+// a tile's at most), and a node all of whose descendants kTileDepth levels down are
+// under it is evaluated on the spot.  Measured (spans 7, 8, 9, 11; one item a tile of
+// level 8 otherwise): 2^21 queries at 8192^2, tau = 1e-3: 130, 98, 94, 106 ms (97
+// untiled); 60001 queries of sigma 4 to 1024 on the 4096^2 scratched map, tau = 1e-4:
+// 158 -> 47 ms at any span, L2 misses 7.7e9 -> 4e7, the vector ALU then always busy.
+constexpr int kTileLevel = 8;
+constexpr int kTileDepth = 3, kTileSpan = 9;
+constexpr int kTileSegs = 64;                        // item segments, each with a counter of its own
+constexpr int kMaxTiles = 1 << (2 * (13 - kTileLevel));
+constexpr int64_t kTileChunk = (int64_t)1 << 19;     // wide queries per round
+constexpr int64_t kTileItems = (int64_t)1 << 24;     // items per round
+// Maps with tiles: below 1024^2 there are fewer than 16 and the caches hold the map.
+__host__ __device__ inline bool has_tiles(int logn) { return logn >= kTileLevel + 2; }
+struct TileCtl {
+    struct alignas(128) Count {
+        uint32_t v;
+    } seg[kTileSegs], qclaim[8], claim[8];           // items written per segment; queries, items claimed per XCD's share
+    alignas(128) uint32_t total;                     // items after sorting
+    alignas(128) uint32_t hist[kMaxTiles], cursor[kMaxTiles];
+};
+struct TileWork {
+    TileCtl* ctl;                   // nullptr: evaluate every query as a whole
+    unsigned long long* raw;        // kTileSegs segments of segcap items
+    unsigned long long* items;      // sorted by tile
+    unsigned long long* acc;        // per wide query: six 32-bit limbs of its exact sum, each in a 64-bit word
+    QuerySetup* setup;              // per wide query
+    uint32_t segcap, round;         // room of a segment; wide queries per round
+    int tiles;                      // tiles of the map
+};
+
+struct EvalArgs {
+    const pndf_query* q;
+    const uint32_t* order;     // optional processing order (query index per slot)
+    int64_t nq;
+    int64_t slot0, slots;      // the launch covers processing slots [slot0, slot0 + slots)
+    float* out;
+    uint32_t* counts;          // nullptr unless counting
+    const uint64_t* offsets;   // hit-record pass only
+    uint64_t* ids;
+    float* terms;
+    float tau;
+    float s2r;
+    int kernel;                // PNDF_KERNEL_*
+    const uint32_t* narrow;    // with tiles: slots from *narrow on hold the wide queries
+    TileWork tile;
+    const QueueCtl* batch = nullptr;  // a plan's tile kernels: the batch (q, nq, out) is read from here
+};
 struct PersistArgs {
     TaskQueue Q;
     const uint32_t* order;  // processing order of the queries (nullptr: input order)
+    const uint32_t* narrow; // with tiles: slots from *narrow on hold the wide queries (nullptr: none)
     Fix192* acc;     // per-query exact sums
     int* fexp;       // per-query binary point (written by the query's root task)
     float tau, s2r;
@@ -210,6 +274,23 @@ struct PersistArgs {
     int split_level;      // smallest level whose nodes may be donated (>= 1)
     long long wait_ticks; // give-up bound of a worker's waits, in wall_clock64 ticks
 };
+
+// Arguments of the spatial order's passes.  With tiles, buckets [nb, 2 nb) hold the
+// wide queries (half-width above `wide`), so they come last in the same order.
+struct OrderArgs {
+    const pndf_query* q;
+    int64_t nq;
+    const QueueCtl* batch;     // a plan's passes: q and nq are read from here
+    int n, bshift, nb, bins;   // bins = 2 nb with tiles, else nb
+    float s2r, wide;
+    uint32_t* key;
+    uint32_t* hist;            // bins counters, then bins cursors
+    uint32_t* order;
+    uint32_t* narrow;          // number of queries that are not wide (nullptr without tiles)
+    TileCtl* ctl;
+};
+// 32-bit words of the order's counters (the passes' histogram, cursors and *narrow).
+inline size_t order_words(int nb, bool tiles) { return (size_t)(tiles ? 4 : 2) * nb + 1; }
 
 // Device resources and the instantiated launch graph of a persistent plan.
 struct PersistPlan {
@@ -219,8 +300,11 @@ struct PersistPlan {
     unsigned long long* tasks = nullptr;
     unsigned int* flags = nullptr;
     unsigned long long capacity = 0;
-    uint32_t* order = nullptr;  // order[max_nq] | key[max_nq] | counters[2 order_nb] (nullptr: input order)
-    int order_nb = 0, order_bshift = 0;
+    uint32_t* order = nullptr;  // order[max_nq] | key[max_nq] | order_words(...) counters (nullptr: input order)
+    int order_nb = 0, order_bins = 0, order_bshift = 0;
+    void* tile_mem = nullptr;
+    TileWork tile{};            // wide queries run tiled on maps with tiles (ctl nullptr: none)
+    std::vector<EvalArgs> targs;  // per round: arguments of its tile kernels
     long long max_nq = 0;
     int blocks = 0, split_level = 1;
     long long wait_ticks = 0;
@@ -237,14 +321,12 @@ struct PersistPlan {
     const pndf_query* rq = nullptr;
     long long rnq = 0;
     float* rout = nullptr;
-    uint32_t* okey = nullptr;   // views into `order`
-    uint32_t* ohist = nullptr;
-    int on = 0;
-    void* rargs[9];
+    uint32_t* ohist = nullptr;  // view into `order`
+    void* rargs[10];
     void* wargs[2];
     void* fargs[3];
-    void* hargs[6];  // order passes: histogram, scatter
-    void* cargs[5];
+    OrderArgs oargs{};  // order passes: histogram, scatter
+    void* hargs[1];
 };
 
 // Fill the device arguments of a plan whose buffers are allocated.
@@ -337,67 +419,6 @@ struct ExportArgs {
 };
 hipError_t export_rowmajor(const ExportArgs& x, int m, hipStream_t s);
 
-struct QuerySetup;
-
-// Tiled evaluation of wide footprints.  The nodes of level kTileLevel (256 x 256
-// texels) are tiles: everything the descent reads beneath one is about 3.7 MB, the
-// size of an XCD's L2.  The spatial order puts the queries that enter above that
-// level last; k_tile_emit descends them to it and leaves their surviving tiles as
-// items, the items are sorted by tile, and the waves of an XCD work through
-// neighbouring items, so that a tile's nodes come from memory about once per launch
-// instead of once per query.  An item holds the place of its query and the list item
-// (Morton code and flags) of its node, with the node's level.
-//
-// Under the cut the descent ends higher up and a tile may hold a few nodes only,
-// while an item costs about 700 vector instructions before its first useful one.  So
-// a node above the tile level becomes an item as a whole when all nodes kTileSpan
-// levels beneath it are under the cut (its part of the hierarchy is then as large as
-// a tile's at most), and a node all of whose descendants kTileDepth levels down are
-// under it is evaluated on the spot.  Measured (spans 7, 8, 9, 11; one item a tile of
-// level 8 otherwise): 2^21 queries at 8192^2, tau = 1e-3: 130, 98, 94, 106 ms (97
-// untiled); 60001 queries of sigma 4 to 1024 on the 4096^2 scratched map, tau = 1e-4:
-// 158 -> 47 ms at any span, L2 misses 7.7e9 -> 4e7, the vector ALU then always busy.
-constexpr int kTileLevel = 8;
-constexpr int kTileDepth = 3, kTileSpan = 9;
-constexpr int kTileSegs = 64;                        // item segments, each with a counter of its own
-constexpr int kMaxTiles = 1 << (2 * (13 - kTileLevel));
-constexpr int64_t kTileChunk = (int64_t)1 << 19;     // wide queries per round
-constexpr int64_t kTileItems = (int64_t)1 << 24;     // items per round
-// Maps with tiles: below 1024^2 there are fewer than 16 and the caches hold the map.
-__host__ __device__ inline bool has_tiles(int logn) { return logn >= kTileLevel + 2; }
-struct TileCtl {
-    struct alignas(128) Count {
-        uint32_t v;
-    } seg[kTileSegs], qclaim[8], claim[8];           // items written per segment; queries, items claimed per XCD's share
-    alignas(128) uint32_t total;                     // items after sorting
-    alignas(128) uint32_t hist[kMaxTiles], cursor[kMaxTiles];
-};
-struct TileWork {
-    TileCtl* ctl;                   // nullptr: evaluate every query as a whole
-    unsigned long long* raw;        // kTileSegs segments of segcap items
-    unsigned long long* items;      // sorted by tile
-    unsigned long long* acc;        // per wide query: six 32-bit limbs of its exact sum, each in a 64-bit word
-    QuerySetup* setup;              // per wide query
-    uint32_t segcap, round;         // room of a segment; wide queries per round
-    int tiles;                      // tiles of the map
-};
-
-struct EvalArgs {
-    const pndf_query* q;
-    const uint32_t* order;     // optional processing order (query index per slot)
-    int64_t nq;
-    int64_t slot0, slots;      // the launch covers processing slots [slot0, slot0 + slots)
-    float* out;
-    uint32_t* counts;          // nullptr unless counting
-    const uint64_t* offsets;   // hit-record pass only
-    uint64_t* ids;
-    float* terms;
-    float tau;
-    float s2r;
-    int kernel;                // PNDF_KERNEL_*
-    const uint32_t* narrow;    // with tiles: slots from *narrow on hold the wide queries
-    TileWork tile;
-};
 hipError_t launch_eval(const HierDev& H, const EvalArgs& a, int algo, hipStream_t s);
 
 // One sample of the P-NDF per query (sample.hip).
@@ -444,6 +465,9 @@ void free_order(uint32_t* order, hipStream_t s);
 // Workspace of the tiled evaluation for batches of nq queries (one allocation,
 // stream-ordered); w->ctl stays nullptr where it does not pay or there is no memory.
 void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s);
+// Size of that workspace (0: no tiles), and its layout at `base`.
+size_t tiles_bytes(const HierDev& H, int64_t nq);
+void tiles_place(const HierDev& H, int64_t nq, void* base, TileWork* w);
 void free_tiles(const TileWork& w, hipStream_t s);
 
 // ---------------------------------------------------------------- device side
