@@ -135,6 +135,17 @@ static thread_local std::string g_last_error;
 // lost a quarter of its throughput, though each tile alone ran faster.
 constexpr int64_t kOrderMin = 4096;
 
+// Wavefronts that share a query in a small batch: as many as leave no query waiting for
+// a place (16 per compute unit and query up to 256 queries, 4 up to 1024), where a
+// batch of tiny footprints takes no longer either.  2048^2 power law, tau = 0, sigma 1
+// to 64, 256 queries: 577 us with one wave each, 173 with 4, 70 with 16; 1024 queries:
+// 933, 271, 131; tiny ones (sigma 1 to 4): 256 queries 11, 10, 10 us, 1024 queries 11,
+// 10, 24, 2048 queries 11, 14, 42.
+static int split_waves(int64_t nq)
+{
+    return nq <= 256 ? 16 : (nq <= 1024 ? 4 : 0);
+}
+
 void set_error(const std::string& msg) { g_last_error = msg; }
 
 int64_t launch_chunk()
@@ -519,6 +530,7 @@ pndf_status pndf_eval_batch(const pndf_hier* h, const pndf_query* d_q, int64_t n
         e = make_order(h->dev, d_q, nq, o.sigma_to_r, tile, &order, &narrow, s);
     }
     EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, narrow, tile};
+    if (!order && o.algo != PNDF_ALGO_BRUTE) a.split = split_waves(nq);
     if (e == hipSuccess) e = launch_eval(h->dev, a, o.algo, s);
     free_tiles(tile, s);
     free_order(order, s);
@@ -538,6 +550,7 @@ pndf_status pndf_eval_batch_noalloc(const pndf_hier* h, const pndf_query* d_q, i
     if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER))
         e = make_order_static(h->dev, d_q, nq, &order, s);
     EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, nullptr, {}};
+    if (!order && o.algo != PNDF_ALGO_BRUTE) a.split = split_waves(nq);
     if (e == hipSuccess) e = launch_eval(h->dev, a, o.algo, s);
     return e == hipSuccess ? PNDF_OK : hip_fail(e, "pndf_eval_batch_noalloc");
 }

@@ -469,7 +469,7 @@ struct NodeLists {
     }
 };
 
-enum { kTilesNone = 0, kTilesEmit = 1, kTilesItem = 2 };
+enum { kTilesNone = 0, kTilesEmit = 1, kTilesItem = 2, kTilesSplit = 3 };
 
 // Reserve n items of the wave's segment; the first one's place, or -1 when they do
 // not all fit (what the failed reservation covers is marked unused).  Every lane
@@ -538,7 +538,7 @@ template <int MODE, bool CUT, bool SPAWN, int KER, int TILES = kTilesNone>
 __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, int root_level,
                         bool root_ok, uint32_t root_item, bool roots_tested, int split_level,
                         unsigned long long qidx, const TaskQueue& Q, Acc& acc, Rec& rec,
-                        const TileWork& T = TileWork{})
+                        const TileWork& T = TileWork{}, int lane_level = 0)
 {
     static_assert(!SPAWN || MODE == kModeValue, "donation is only used by value-mode workers");
     const int lane = threadIdx.x & 63;
@@ -565,7 +565,8 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
     } else {
         bool ok = root_ok;
         const uint32_t m = root_item & kCodeMask;
-        const uint32_t idx = (uint32_t)level_offset(H.logn, root_level) + m;
+        const int rl = TILES == kTilesSplit && CUT ? lane_level : root_level;
+        const uint32_t idx = (uint32_t)level_offset(H.logn, rl) + m;
         bool cut = false, kids_cut = false;
         if (CUT && ok) {
             const float2 em = H.clu_em[idx];
@@ -590,7 +591,7 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
         if (ok && !cut) nl.put(root_level, __popcll(bl & ((1ull << lane) - 1ull)), entry);
         if (CUT) {
             const uint64_t bc = __ballot(cut);
-            if (cut) cq[__popcll(bc & ((1ull << lane) - 1ull))] = ((uint32_t)root_level << kCluShift) | m;
+            if (cut) cq[__popcll(bc & ((1ull << lane) - 1ull))] = ((uint32_t)rl << kCluShift) | m;
             cn = __popcll(bc);
         }
         const int tot = __popcll(bl);
@@ -978,6 +979,107 @@ __global__ __launch_bounds__(64) void k_eval_plain(HierDev H, EvalArgs a)
     TaskQueue none{};
     descend<MODE, CUT, false, KER>(H, q, lists, lr, ok, item, false, 0, 0, none, acc, rec);
     finish<MODE>(a, qi, q, acc);
+}
+
+// ------------------------------------------------------------ split
+// Small batches: W wavefronts of one workgroup share a query, so that a picked pixel
+// or a few hundred rays do not wait for single waves' chains of dependent steps.  The
+// roots go down as far as their grid fits W lane grids (8 W' per axis, W' = sqrt(W)),
+// and a wave takes every W'-th row and column of it, which spreads the hits.  A query
+// of half-width kSplitAlone or less is one wave's work: the others leave at once (with
+// them 2048 queries of sigma 1 to 4 took 55 us with 16 waves each, plain 11).
+constexpr float kSplitAlone = 16.f;
+template <int W>
+constexpr int kSplitAxis = W == 16 ? 4 : 2;
+
+// The grid of level-lr nodes over the included cells of one axis: first column
+// (unrolled) and count; all of the torus from column 0.
+__device__ __forceinline__ void split_axis(int clo, int chi, int lr, int M, int* k0, int* nk)
+{
+    *k0 = clo >> lr;
+    *nk = (chi >> lr) - *k0 + 1;
+    if (*nk >= M) {
+        *k0 = 0;
+        *nk = M;
+    }
+}
+
+// Do the grid's columns have each ancestor d levels up once (and not at both ends of
+// the torus)?
+__device__ __forceinline__ bool split_once(int k0, int nk, int d, int M)
+{
+    return ((k0 + nk - 1) >> d) - (k0 >> d) + 1 <= (M >> d);
+}
+
+template <bool CUT, int KER, int W>
+__global__ __launch_bounds__(64 * W) void k_eval_split(HierDev H, EvalArgs a)
+{
+    extern __shared__ uint32_t lds[];
+    __shared__ Fix192 sums[W];
+    const int64_t qi = a.slot0 + blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = lane_id();
+    const QuerySetup u = setup_support(a.q[qi], a.s2r);
+    const bool alone = !(u.valid && fmaxf(u.rx, u.ry) > kSplitAlone);
+    if (alone && wave != 0) return;
+    const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, a.kernel));
+    if (!q.valid) {
+        invalid<kModeValue>(a, qi);
+        return;
+    }
+    constexpr int S = kSplitAxis<W>;
+    int lr = descent_start<CUT>(H, q), kx, nkx, ky, nky;
+    split_axis(q.cxlo, q.cxhi, lr, H.n >> lr, &kx, &nkx);
+    split_axis(q.cylo, q.cyhi, lr, H.n >> lr, &ky, &nky);
+    while (!alone && lr > (CUT ? 1 : 0)) {
+        int x, nx, y, ny;
+        const int M = H.n >> (lr - 1);
+        split_axis(q.cxlo, q.cxhi, lr - 1, M, &x, &nx);
+        split_axis(q.cylo, q.cyhi, lr - 1, M, &y, &ny);
+        if (nx > 8 * S || ny > 8 * S) break;
+        if (CUT && !(split_once(x, nx, q.l0 - lr + 1, M) && split_once(y, ny, q.l0 - lr + 1, M))) break;
+        --lr;
+        kx = x; nkx = nx; ky = y; nky = ny;
+    }
+    const int ca = (lane & 7) * (alone ? 1 : S) + wave % S, cb = (lane >> 3) * (alone ? 1 : S) + wave / S;
+    bool ok = ca < nkx && cb < nky;
+    const int mm = (H.n >> lr) - 1;
+    const uint32_t I = (uint32_t)((kx + ca) & mm), J = (uint32_t)((ky + cb) & mm);
+    uint32_t item = I | (J << 16);
+    int lev = lr;
+    if (lr > 0) {
+        const int side = 1 << lr;
+        const bool inside = axis_inside((int)I * side, side, q.cxlo, q.cxhi, H.logn) &&
+                            axis_inside((int)J * side, side, q.cylo, q.cyhi, H.logn);
+        const uint32_t m = morton(I, J);
+        item = m | (inside ? kInside : 0u);
+        if (CUT) {
+            // the highest ancestor from the entry level down that is under the cut stands
+            // in for its nodes, once: at the first of them that the grid has
+            for (int l = lr + 1; l <= q.l0; ++l) {
+                const int d = l - lr;
+                if (ok && H.clu_em[(uint32_t)level_offset(H.logn, l) + (m >> (2 * d))].x <= q.t) {
+                    lev = l;
+                    item = m >> (2 * d);
+                }
+            }
+            const int d = lev - lr;
+            if (d > 0)
+                ok = ok && kx + ca == max(kx, ((kx + ca) >> d) << d) && ky + cb == max(ky, ((ky + cb) >> d) << d);
+        }
+    }
+    Acc acc;
+    Rec rec{nullptr, nullptr, 0, 0};
+    TaskQueue none{};
+    descend<kModeValue, CUT, false, KER, kTilesSplit>(H, q, lds + wave * wave_lds_words(H.L, CUT), lr, ok, item, false, 0, 0,
+                                                      none, acc, rec, TileWork{}, lev);
+    const Fix192 d = wave_sum_fix(acc.d);
+    if (lane == 0) sums[wave] = d;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Fix192 t = sums[0];
+        for (int w = 1; w < (alone ? 1 : W); ++w) fix_add(t, sums[w]);
+        a.out[qi] = fix_to_float(t, q.fexp);
+    }
 }
 
 // ------------------------------------------------------------ tiles
@@ -1490,6 +1592,17 @@ __global__ void k_persist_finalize(const QueueCtl* ctl, const Fix192* acc, const
     }
 }
 
+template <bool CUT, int KER>
+void launch_split(const HierDev& H, const EvalArgs& a, hipStream_t s)
+{
+    const size_t lds = sizeof(uint32_t) * wave_lds_words(H.L, CUT);
+    const dim3 grid((unsigned)a.slots);
+    if (a.split == 16)
+        hipLaunchKernelGGL((k_eval_split<CUT, KER, 16>), grid, dim3(1024), 16 * lds, s, H, a);
+    else
+        hipLaunchKernelGGL((k_eval_split<CUT, KER, 4>), grid, dim3(256), 4 * lds, s, H, a);
+}
+
 // Launches cover at most launch_chunk() queries (grid dimensions stay far below
 // 2^32 work-items).
 template <int MODE, int KER>
@@ -1503,6 +1616,9 @@ hipError_t launch_mode(const HierDev& H, const EvalArgs& a0, int algo, hipStream
         if (algo == PNDF_ALGO_BRUTE) {
             const unsigned blocks = (unsigned)((a.slots + 3) / 4);
             hipLaunchKernelGGL((k_eval_brute<MODE, KER>), dim3(blocks), dim3(256), 0, s, H, a);
+        } else if (MODE == kModeValue && a.split) {
+            if (a.tau > 0.f) launch_split<true, KER>(H, a, s);
+            else launch_split<false, KER>(H, a, s);
         } else {
             const unsigned blocks = (unsigned)a.slots;
             const size_t lds = sizeof(uint32_t) * wave_lds_words(H.L, a.tau > 0.f);

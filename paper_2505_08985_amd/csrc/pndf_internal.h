@@ -261,6 +261,7 @@ struct EvalArgs {
     int kernel;                // PNDF_KERNEL_*
     const uint32_t* narrow;    // with tiles: slots from *narrow on hold the wide queries
     TileWork tile;
+    int split = 0;                    // wavefronts per query of a small batch (4 or 16; 0: one)
     const QueueCtl* batch = nullptr;  // a plan's tile kernels: the batch (q, nq, out) is read from here
 };
 struct PersistArgs {
