@@ -19,26 +19,30 @@
 //   ellipse piece:   -[A(y)] (F = -sqrt(1 - y^2) there, y decreasing).
 // A triangle with its three vertices in V lies in V (convexity): three segments.
 //
-// Brute force like the paper's implementation: one wavefront per query, lanes over
-// the included cells (two triangles each), FP64 throughout; the lanes' partial
-// sums are reduced in the wave.  V lies right of the line m_x = -w_z (the
-// ellipse's leftmost point), so a triangle left of it adds nothing; a triangle
-// with its three vertices in V takes three segment terms at once (a cell whose two
-// triangles both lie in V five: the shared diagonal once); only the others need
-// clipping, and they wait in a per-wave LDS queue until 64 of them fill a round with
-// one per lane (a lane's clipping would otherwise stall its wave).
+// Brute force like the paper's implementation: one wavefront per query (several in
+// small batches), lanes over the included cells (two triangles each), FP64 throughout;
+// the lanes' partial sums are reduced in the wave.  V lies right of the line
+// m_x = -w_z (the ellipse's leftmost point), so a triangle left of it adds nothing; a
+// triangle with its three vertices in V takes three segment terms at once (a cell
+// whose two triangles both lie in V five: the shared diagonal once), each the
+// trapezoid of its ends and a small correction (segment_short).  The others (4 % of the
+// triangles of a 2048^2 power-law map, 6 % of a scratched one) wait in a per-wave LDS
+// queue until 21 of them fill a round with one edge per lane: a lane's clipping would
+// otherwise stall its wave, and one edge's code instead of three in a row is a third
+// of the instructions to fetch (11000 to 4000) and of the registers (no clipping state in scratch
+// memory).  The pieces of V's boundary, which few edges leave, wait once more, 64 to a
+// round.  The footprint weight at a cell's centroids is a product of two factors that
+// depend on its column and its row alone, formed once per query in LDS.
+// Bound by FP64 vector instructions (82 % of the issue slots): 65536 queries of sigma 1
+// to 8 on the 2048^2 power-law map take 1055 us and 7240 instructions per wavefront,
+// against 1312 us and 10090 with arcsines for every segment, weights per cell and a
+// triangle per lane in the clipping.
 #include <algorithm>
 
 #include "pndf_internal.h"
 
 namespace pndf {
 namespace {
-
-__device__ __forceinline__ double arc_prim(double y)
-{
-    y = fmin(1.0, fmax(-1.0, y));
-    return 0.5 * (asin(y) + y * sqrt(fmax(0.0, 1.0 - y * y)));
-}
 
 __device__ __forceinline__ bool visible(double x, double y, double wz)
 {
@@ -57,6 +61,14 @@ __device__ __forceinline__ double rsqrt_f64(double x)
     return y;
 }
 
+// 1 / x in FP64, x a normal number: the estimate and two Newton steps
+__device__ __forceinline__ double rcp_f64(double x)
+{
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
 // sqrt(z) for 0 <= z <= 1 as z / sqrt(z) (exactly 0 at 0)
 __device__ __forceinline__ double sqrt_unit(double z)
 {
@@ -73,6 +85,37 @@ __device__ __forceinline__ double arc_prim_diff(double a, double b)
     const double ca = sqrt_unit(1.0 - a * a), cb = sqrt_unit(1.0 - b * b);
     const double d = ca * cb + a * b >= 0.0 ? asin(fmin(1.0, fmax(-1.0, b * ca - a * cb))) : asin(b) - asin(a);
     return 0.5 * (d + b * cb - a * ca);
+}
+
+// F dm_y along the segment P -> Q between points inside the unit disk, p and q their
+// m~_z = sqrt(1 - m_x^2 - m_y^2).  With d = Q - P, l = |d|, M = d . (P + Q) / 2 (so
+// that p^2 - q^2 = 2 M), E = l^2 rho^2 = l^2 - (P x Q)^2 and
+// Y = 2 M^2 / (p + q) + l^2 (p + q) / 2, the angle that the segment subtends on its
+// circle of radius rho has the sine z = Y l / E, and the closed form above becomes
+//   d_y / 2 [w_z (P_x + Q_x) - w_l (p + q + (asin(z) / z - 1) Y / l^2)]
+//     = d_y / 2 [w_z (P_x + Q_x) - w_l (p + q + Y (Y / E)^2 C(z^2))],
+// C(u) = (asin(z) / z - 1) / u at u = z^2: the trapezoid rule and its correction, all
+// terms of one sign, without a square root, an arcsine or a cancellation.  C is a fit of
+// degree 8 on [0, 0.1], 1.1e-16 off at most.  *ok is false beyond it (jumps of a
+// scratched map), where the segment is longer than rho (the angle may then pass pi / 2)
+// and where it hugs the circle: the triangle is then left to far_round.
+__device__ __forceinline__ double segment_short(double px, double py, double p, double qx, double qy, double q, double wl,
+                                                double wz, bool* ok)
+{
+    const double dx = qx - px, dy = qy - py, sx = px + qx, sy = py + qy, sp = p + q;
+    const double l2 = dx * dx + dy * dy, c = dy * px - dx * py, E = l2 - c * c;
+    const double M = 0.5 * (dx * sx + dy * sy);
+    const double r = rcp_f64(sp * E);
+    const double Y = 2.0 * M * M * (E * r) + 0.5 * l2 * sp, g = Y * (sp * r), u = g * g * l2;
+    const double C[9] = {0.16666666666666677,  0.074999999999844316, 0.04464285718425845,
+                         0.030381940216166695, 0.022372374707386941, 0.01734661732276873,
+                         0.014066980567147705, 0.010577825252300511, 0.014580819628997006};
+    double f = C[8];
+#pragma unroll
+    for (int i = 7; i >= 0; --i) f = fma(f, u, C[i]);
+    *ok = (sp > 1e-3 && E > 1e-4 * l2 && l2 * l2 <= E && u <= 0.1) || l2 == 0.0;
+    const double v = 0.5 * dy * (wz * sx - wl * (sp + Y * (g * g) * f));
+    return l2 == 0.0 ? 0.0 : v;
 }
 
 // F dm_y along the segment P -> Q
@@ -110,10 +153,8 @@ __device__ inline double boundary_int(double a, double b, double wz)
         const double half = floor(a * 0.5);
         const double stop = fmin(b, 2.0 * half + 2.0);
         const double ya = a - 2.0 * half, yb = stop - 2.0 * half;  // in [0, 2]
-        if (((int)half & 1) == 0)
-            sum += wz * (arc_prim(yb - 1.0) - arc_prim(ya - 1.0));   // circle, y = place - 1
-        else
-            sum += arc_prim(1.0 - ya) - arc_prim(1.0 - yb);         // ellipse, y = 1 - place
+        const bool circ = ((int)half & 1) == 0;  // circle: y = place - 1, ellipse: y = 1 - place
+        sum += (circ ? wz : 1.0) * arc_prim_diff(circ ? ya - 1.0 : 1.0 - yb, circ ? yb - 1.0 : 1.0 - ya);
         a = stop;
     }
     return sum;
@@ -127,44 +168,57 @@ __device__ __forceinline__ void cswap(double& a, double& b)
 }
 
 // parameter interval [t0, t1] of the segment P + t D (t in [0, 1]) inside V;
-// false if empty.  The candidates: the ends, every meeting with the unit circle or
-// the whole ellipse x^2 + wz^2 y^2 = wz^2 (V's boundary crossings are among them,
-// the others only split the segment), and the line x = 0, the ellipse's limit as
-// wz -> 0 (its discriminant is then a difference of equal products and may round
-// below 0).  Unused slots repeat t = 1.  Sorted by a fixed network (registers
-// only); V convex: the visible pieces between consecutive candidates form one
-// interval.
-__device__ inline bool clip_edge(double px, double py, double dx, double dy, double wz, double* t0, double* t1)
+// false if empty.  The candidates: the ends, every meeting with the whole ellipse
+// x^2 + wz^2 y^2 = wz^2 and, with CIRCLE (some end lies outside the unit disk), with
+// the unit circle (V's boundary crossings are among them, the others only split the
+// segment), and the line x = 0, the ellipse's limit as wz -> 0 (its discriminant is
+// then a difference of equal products and may round below 0).  Unused slots repeat
+// t = 1.  Sorted by a fixed network (registers only); V convex: the visible pieces
+// between consecutive candidates form one interval.
+template <bool CIRCLE>
+__device__ __forceinline__ bool clip_edge(double px, double py, double dx, double dy, double wz, double* t0, double* t1)
 {
-    double ts[7] = {0.0, 1.0, 1.0, 1.0, 1.0, 1.0, 1.0};
+    constexpr int N = CIRCLE ? 7 : 5;
+    double ts[N];
+    ts[0] = 0.0;
 #pragma unroll
-    for (int curve = 0; curve < 2; ++curve) {
-        const double ey = curve == 0 ? 1.0 : wz * wz, rhs = curve == 0 ? 1.0 : wz * wz;
+    for (int i = 1; i < N; ++i) ts[i] = 1.0;
+#pragma unroll
+    for (int curve = 0; curve < (CIRCLE ? 2 : 1); ++curve) {
+        const double ey = curve == 1 ? 1.0 : wz * wz, rhs = curve == 1 ? 1.0 : wz * wz;
         const double qa = dx * dx + ey * dy * dy;
         const double qb = 2.0 * (px * dx + ey * py * dy);
         const double qc = px * px + ey * py * py - rhs;
         const double disc = qb * qb - 4.0 * qa * qc;
         if (qa > 0.0 && disc >= 0.0) {
-            const double sq = sqrt(disc);
-            const double ra = (-qb - sq) / (2.0 * qa), rb = (-qb + sq) / (2.0 * qa);
+            const double sq = disc > 1e-200 ? disc * rsqrt_f64(disc) : 0.0, inv = 0.5 * rcp_f64(qa);
+            const double ra = (-qb - sq) * inv, rb = (-qb + sq) * inv;
             ts[2 + 2 * curve] = (ra > 0.0 && ra < 1.0) ? ra : 1.0;
             ts[3 + 2 * curve] = (rb > 0.0 && rb < 1.0) ? rb : 1.0;
         }
     }
     if (dx != 0.0) {
-        const double t = -px / dx;
-        ts[6] = (t > 0.0 && t < 1.0) ? t : 1.0;
+        const double t = -px * rcp_f64(dx);
+        ts[N - 1] = (t > 0.0 && t < 1.0) ? t : 1.0;
     }
-    // sorting network for 7 values
-    cswap(ts[0], ts[6]); cswap(ts[2], ts[3]); cswap(ts[4], ts[5]);
-    cswap(ts[0], ts[2]); cswap(ts[1], ts[4]); cswap(ts[3], ts[6]);
-    cswap(ts[0], ts[1]); cswap(ts[2], ts[5]); cswap(ts[3], ts[4]);
-    cswap(ts[1], ts[2]); cswap(ts[4], ts[6]);
-    cswap(ts[2], ts[3]); cswap(ts[4], ts[5]);
-    cswap(ts[1], ts[2]); cswap(ts[3], ts[4]); cswap(ts[5], ts[6]);
+    if constexpr (CIRCLE) {
+        // sorting network for 7 values
+        cswap(ts[0], ts[6]); cswap(ts[2], ts[3]); cswap(ts[4], ts[5]);
+        cswap(ts[0], ts[2]); cswap(ts[1], ts[4]); cswap(ts[3], ts[6]);
+        cswap(ts[0], ts[1]); cswap(ts[2], ts[5]); cswap(ts[3], ts[4]);
+        cswap(ts[1], ts[2]); cswap(ts[4], ts[6]);
+        cswap(ts[2], ts[3]); cswap(ts[4], ts[5]);
+        cswap(ts[1], ts[2]); cswap(ts[3], ts[4]); cswap(ts[5], ts[6]);
+    } else {
+        // 0 is the least and 1 the greatest already: the three between them
+        cswap(ts[2], ts[3]);
+        cswap(ts[3], ts[4]);
+        cswap(ts[2], ts[3]);
+        ts[1] = ts[2]; ts[2] = ts[3]; ts[3] = ts[4]; ts[4] = 1.0;
+    }
     double lo = 2.0, hi = -1.0;
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
+    for (int i = 0; i + 1 < N; ++i) {
         if (!(ts[i + 1] > ts[i])) continue;
         const double tm = 0.5 * (ts[i] + ts[i + 1]);
         if (visible(px + tm * dx, py + tm * dy, wz)) {
@@ -185,51 +239,6 @@ __device__ __forceinline__ void orient_ccw(double v[6])
         double t = v[2]; v[2] = v[4]; v[4] = t;
         t = v[3]; v[3] = v[5]; v[5] = t;
     }
-}
-
-// integral of (w_l m_x / m~_z + w_z) over (triangle v, canonical frame,
-// counter-clockwise) within V, by clipping
-__device__ inline double triangle_int_clipped(const double v[6], double wl, double wz)
-{
-    double ex[3], ey[3], xx[3], xy[3];  // entry and exit point of each edge
-    bool in[3];
-    bool any = false;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-        const int f = (e + 1) % 3;
-        const double px = v[2 * e], py = v[2 * e + 1], qx = v[2 * f], qy = v[2 * f + 1];
-        double t0, t1;
-        in[e] = clip_edge(px, py, qx - px, qy - py, wz, &t0, &t1);
-        if (in[e]) {
-            ex[e] = t0 == 0.0 ? px : px + t0 * (qx - px);
-            ey[e] = t0 == 0.0 ? py : py + t0 * (qy - py);
-            xx[e] = t1 == 1.0 ? qx : px + t1 * (qx - px);
-            xy[e] = t1 == 1.0 ? qy : py + t1 * (qy - py);
-            any = true;
-        }
-    }
-    if (!any) {
-        // V inside the triangle (it holds the origin, a point of V) or disjoint
-        const bool o0 = v[2] * v[5] - v[3] * v[4] >= 0.0;               // (0, v1, v2)
-        const bool o1 = v[4] * v[1] - v[5] * v[0] >= 0.0;               // (0, v2, v0)
-        const bool o2 = v[0] * v[3] - v[1] * v[2] >= 0.0;               // (0, v0, v1)
-        return (o0 && o1 && o2) ? boundary_int(0.0, 4.0, wz) : 0.0;
-    }
-    double sum = 0.0;
-#pragma unroll
-    for (int e = 0; e < 3; ++e) {
-        if (!in[e]) continue;
-        sum += segment_int(ex[e], ey[e], xx[e], xy[e], wl, wz);
-        int f = (e + 1) % 3;
-        if (!in[f]) f = (f + 1) % 3;
-        if (!in[f]) f = e;
-        if (xx[e] == ex[f] && xy[e] == ey[f]) continue;  // meets the next edge at a vertex
-        const double a = loop_pos(xx[e], xy[e]);
-        double b = loop_pos(ex[f], ey[f]);
-        if (b < a) b += 4.0;
-        sum += boundary_int(a, b, wz);
-    }
-    return sum;
 }
 
 // A triangle of cell (i, j) and its weight k / J: normals in the canonical frame.
@@ -256,26 +265,137 @@ __device__ __forceinline__ void cell_triangle(const HierDev& H, int i, int j, in
     orient_ccw(r);
 }
 
-constexpr int kClipCap = 256;  // queued triangles per wave (a step adds at most 128)
+constexpr int kClipRound = 21;  // triangles of a round: three lanes each
+constexpr int kClipCap = 168;    // queued triangles per wave (a step adds at most 128 to two rests)
+constexpr int kArcCap = 128;     // queued boundary pieces per wave (a round adds at most 63)
 
-template <int KER>
-// One wavefront per workgroup: queries differ in cost by up to 64x (the support
-// grows with sigma^2), and a workgroup of four held its slot until its slowest query
-// ended (7.4 resident waves per CU of the 16 the registers allow; one per workgroup:
-// -18 %).
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_projected_area(HierDev H, ProjArgs a)
+// Triangles that need clipping from the front, those within V with an edge beyond
+// segment_short's range from the back; pieces of V's boundary.
+struct ClipQueue {
+    uint32_t cell[kClipCap];
+    double w[kClipCap];
+    double arc_a[kArcCap], arc_b[kArcCap], arc_w[kArcCap];
+};
+
+// corner `e` of a triangle, its successor at e = 1 .. 3
+__device__ __forceinline__ void edge_of(const double v[6], int e, double* px, double* py, double* qx, double* qy)
 {
-    __shared__ uint32_t clip_cell[kClipCap];
-    __shared__ double clip_w[kClipCap];
+    *px = e == 0 ? v[0] : (e == 1 ? v[2] : v[4]);
+    *py = e == 0 ? v[1] : (e == 1 ? v[3] : v[5]);
+    *qx = e == 0 ? v[2] : (e == 1 ? v[4] : v[0]);
+    *qy = e == 0 ? v[3] : (e == 1 ? v[5] : v[1]);
+}
+
+// The queued triangles [at, at + cnt), all within V, an edge per lane.
+__device__ __forceinline__ double far_round(const HierDev& H, const ClipQueue& Q, int at, int cnt, int lane, double c, double sn,
+                                            double wl, double wz)
+{
+    const int t = (lane * 43) >> 7, e = lane - 3 * t;  // lane / 3 up to 63
+    if (t >= cnt) return 0.0;
+    const uint32_t id = Q.cell[at + t];
+    double v[6], px, py, qx, qy;
+    cell_triangle(H, (int)(id & 0x1fffu), (int)((id >> 13) & 0x1fffu), (int)(id >> 26), c, sn, v);
+    edge_of(v, e, &px, &py, &qx, &qy);
+    return Q.w[at + t] * segment_int(px, py, qx, qy, wl, wz);
+}
+
+// Integral of (w_l m_x / m~_z + w_z) over V within the queued triangles [at, at + cnt),
+// an edge per lane: the edge clipped to V adds its segment, and where it does not end
+// on the next edge's start the piece of V's boundary between them is queued (at *na), as
+// few edges have one.  Returns this lane's share.
+__device__ __forceinline__ double clip_round(const HierDev& H, ClipQueue& Q, int at, int cnt, int lane, double c, double sn,
+                                             double wl, double wz, int* na)
+{
+    const int t = (lane * 43) >> 7, e = lane - 3 * t;  // lane / 3 up to 63
+    const bool on = t < cnt;
+    const uint32_t id = Q.cell[at + (on ? t : 0)];
+    const double w = Q.w[at + (on ? t : 0)];
+    double v[6], px, py, qx, qy;
+    cell_triangle(H, (int)(id & 0x1fffu), (int)((id >> 13) & 0x1fffu), (int)(id >> 26), c, sn, v);
+    edge_of(v, e, &px, &py, &qx, &qy);
+    double t0 = 0.0, t1 = 0.0;
+    // (the same for the wave: normal maps seldom reach the unit circle)
+    const bool circle = __ballot(px * px + py * py > 1.0) != 0ull;
+    const bool in = on && (circle ? clip_edge<true>(px, py, qx - px, qy - py, wz, &t0, &t1)
+                                  : clip_edge<false>(px, py, qx - px, qy - py, wz, &t0, &t1));
+    const double ex = t0 == 0.0 ? px : px + t0 * (qx - px), ey = t0 == 0.0 ? py : py + t0 * (qy - py);
+    const double xx = t1 == 1.0 ? qx : px + t1 * (qx - px), xy = t1 == 1.0 ? qy : py + t1 * (qy - py);
+    const uint32_t ins = (uint32_t)(__ballot(in) >> (3 * t)) & 7u;
+    // the next edge in V
+    int f = e == 2 ? 0 : e + 1;
+    if (!((ins >> f) & 1u)) f = f == 2 ? 0 : f + 1;
+    if (!((ins >> f) & 1u)) f = e;
+    const double fx = __shfl(ex, 3 * t + f), fy = __shfl(ey, 3 * t + f);
+    double sum = 0.0, a = 0.0, b = 0.0;
+    bool arc = false;
+    if (in) {
+        sum = w * segment_int(ex, ey, xx, xy, wl, wz);
+        arc = !(xx == fx && xy == fy);  // else it meets the next edge at a vertex
+        a = loop_pos(xx, xy);
+        b = loop_pos(fx, fy);
+        if (b < a) b += 4.0;
+    } else if (on && ins == 0u && e == 0) {
+        // V inside the triangle (it holds the origin, a point of V) or disjoint
+        arc = v[2] * v[5] - v[3] * v[4] >= 0.0 && v[4] * v[1] - v[5] * v[0] >= 0.0 && v[0] * v[3] - v[1] * v[2] >= 0.0;
+        b = 4.0;
+    }
+    const uint64_t m = __ballot(arc);
+    if (arc) {
+        const int k = *na + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        Q.arc_a[k] = a;
+        Q.arc_b[k] = b;
+        Q.arc_w[k] = w;
+    }
+    *na += (int)__popcll(m);
+    return sum;
+}
+
+constexpr int kAxisCells = 320;  // columns plus rows whose footprint factors fit the LDS table
+
+// Footprint factor of one axis at the centroid of a cell's lower (h = 0) or upper
+// triangle, summed over the included images (the product of both axes' factors and
+// norm is the weight of hit_weight).
+template <int KER>
+__device__ inline double axis_weight(const QuerySetup& q, int axis, int start, int h, int logn)
+{
+    const double uoff = h ? 1.0 - 1.0 / 3.0 : 1.0 / 3.0;
+    const float x = axis ? q.y : q.x;
+    const int clo = axis ? q.cylo : q.cxlo, chi = axis ? q.cyhi : q.cxhi;
+    if constexpr (KER == PNDF_KERNEL_BOX) {
+        return box_axis(x, axis ? q.ry : q.rx, start, 1, uoff, clo, chi, logn);
+    } else {
+        const double k = axis ? q.ky : q.kx, base = (double)start + uoff - (double)x;
+        const int p0 = ceil_div_pow2(clo - start, logn), p1 = floor_div_pow2(chi - start, logn);
+        double g = 0.0;
+        for (int p = p0; p <= p1; ++p) {
+            const double d = base + (double)p * (double)(1 << logn);
+            g += exp2(-(d * d * k));
+        }
+        return g;
+    }
+}
+
+// One wavefront per workgroup in large batches: queries differ in cost by up to 64x
+// (the support grows with sigma^2), and a workgroup of four queries held its slot until
+// its slowest one ended (one per workgroup: -18 %).  In small batches W wavefronts share
+// a query's cells.  Three wavefronts per SIMD: at four (128 registers) the segments
+// spill and the same work takes 1316 us, at two 1350 us.
+template <int KER, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_projected_area(HierDev H, ProjArgs a)
+{
+    __shared__ ClipQueue queues[W];
+    __shared__ double axis[KER == PNDF_KERNEL_DISK ? 1 : 2 * kAxisCells];
+    __shared__ double sums[W];
     if ((int64_t)blockIdx.x >= a.nq) return;
     const int64_t qi = a.order ? (int64_t)a.order[blockIdx.x] : (int64_t)blockIdx.x;
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    ClipQueue& Q = queues[wave];
     const pndf_query qr = a.q[qi];
     const QuerySetup q = uniform_query(setup_query(qr, a.s2r, 0.f, H.L, H.eps, KER));
     const double wx = qr.hx, wy = qr.hy;
     const double wl2 = wx * wx + wy * wy;
     if (!q.valid || !(wl2 <= 1.0)) {
-        if (lane == 0) {
+        if (threadIdx.x == 0) {
             a.P[qi] = __int_as_float(0x7fc00000);
             if (a.lambda) a.lambda[qi] = __int_as_float(0x7fc00000);
         }
@@ -287,24 +407,47 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
     const int spanx = q.cxhi - q.cxlo + 1, spany = q.cyhi - q.cylo + 1;
     const int nx = spanx >= n ? n : spanx, ny = spany >= n ? n : spany;
     const int total = nx * ny;
+    const bool table = KER != PNDF_KERNEL_DISK && nx + ny <= kAxisCells;
+    if (table) {
+        // x factors (times the norm) of the lower and the upper centroids, then y's
+        for (int i = threadIdx.x; i < 2 * (nx + ny); i += 64 * W) {
+            const int ax = i >= 2 * nx, k = ax ? i - 2 * nx : i, m = ax ? ny : nx, h = k >= m, cell = h ? k - m : k;
+            const int at = ax ? (spany >= n ? cell : ((q.cylo + cell) & msk)) : (spanx >= n ? cell : ((q.cxlo + cell) & msk));
+            axis[i] = axis_weight<KER>(q, ax, at, h, H.logn) * (ax ? 1.0 : q.norm);
+        }
+        if (W == 1) wave_sync();
+        else __syncthreads();
+    }
     double acc = 0.0;
-    int qn = 0;  // queued triangles (wave-uniform)
-    for (int base = 0; base < total || qn > 0; base += 64) {
-        uint32_t clip = 0;          // bit h: this lane's triangle h needs clipping
+    int qn = 0, nf = 0, na = 0;  // queued triangles (front, back) and boundary pieces (wave-uniform)
+    // this lane's cell, column ca and row cb of the included ones, and its stride
+    constexpr int step = 64 * W;
+    int ca = (wave * 64 + lane) % nx, cb = (wave * 64 + lane) / nx;
+    const int da = step % nx, db = step / nx;
+    for (int base = wave * 64; base < total; base += step) {
+        uint32_t clip = 0, far = 0;  // bit h: this lane's triangle h needs clipping, the long form
         double kw[2] = {0.0, 0.0};
         uint32_t cell = 0;
         const int idx = base + lane;
         if (idx < total) {
-            const int ca = idx % nx, cb = idx / nx;
             const int i = spanx >= n ? ca : ((q.cxlo + ca) & msk);
             const int j = spany >= n ? cb : ((q.cylo + cb) & msk);
             cell = (uint32_t)i | ((uint32_t)j << 13);
             const float2 dd = H.det[(int64_t)j * n + i];
+            const uint8_t deg = H.deg[(int64_t)j * n + i];
             // kernel at the uv centroid over the included images, divided by J
             double kh[2];
-            kh[0] = hit_term<KER>(q, i, j, 0, 0, 1.0 / 3.0, 1.0 / 3.0, dd.x, H.logn);
-            kh[1] = hit_term<KER>(q, i, j, 0, 1, 1.0 / 3.0, 1.0 / 3.0, dd.y, H.logn);
-            if ((H.deg[(int64_t)j * n + i] & 3u) == 0u) {
+            if (table) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double J = (double)(h ? dd.y : dd.x);
+                    kh[h] = axis[h * nx + ca] * axis[2 * nx + h * ny + cb] * rcp_f64(J);
+                }
+            } else {
+                kh[0] = hit_term<KER>(q, i, j, 0, 0, 1.0 / 3.0, 1.0 / 3.0, dd.x, H.logn);
+                kh[1] = hit_term<KER>(q, i, j, 0, 1, 1.0 / 3.0, 1.0 / 3.0, dd.y, H.logn);
+            }
+            if ((deg & 3u) == 0u) {
                 // both halves regular: lower (n0, n1, n2) and upper (n3, n2, n1) share the
                 // diagonal n1 -> n2, which the upper runs backwards.  The corners are rotated
                 // once; a triangle's CCW boundary integral is its orientation sign times
@@ -313,14 +456,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 const int wdt = n + 1;
                 const float2* p = H.nrm + (int64_t)j * wdt + i;
                 const float2 nn[4] = {p[0], p[1], p[wdt], p[wdt + 1]};
-                double x[4], y[4];
+                double x[4], y[4], mz[4];
                 bool vis[4], left[4];
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     x[k] = c * (double)nn[k].x + sn * (double)nn[k].y;
                     y[k] = -sn * (double)nn[k].x + c * (double)nn[k].y;
+                    const double r2 = x[k] * x[k] + y[k] * y[k];
                     vis[k] = visible(x[k], y[k], wz);
                     left[k] = x[k] < -wz;
+                    mz[k] = sqrt_unit(fmax(0.0, 1.0 - r2));
                 }
                 const double sl = (x[1] - x[0]) * (y[2] - y[0]) - (y[1] - y[0]) * (x[2] - x[0]) < 0.0 ? -1.0 : 1.0;
                 const double su = (x[2] - x[3]) * (y[1] - y[3]) - (y[2] - y[3]) * (x[1] - x[3]) < 0.0 ? -1.0 : 1.0;
@@ -328,45 +473,38 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
                 const bool up_live = kh[1] != 0.0 && !(left[3] && left[2] && left[1]);
                 const bool lo_full = lo_live && vis[0] && vis[1] && vis[2];
                 const bool up_full = up_live && vis[3] && vis[2] && vis[1];
-                double wd = 0.0;
-                if (lo_full) {
-                    acc += kh[0] * sl * (segment_int(x[0], y[0], x[1], y[1], wl, wz) +
-                                         segment_int(x[2], y[2], x[0], y[0], wl, wz));
-                    wd += kh[0] * sl;
-                }
-                if (up_full) {
-                    acc += kh[1] * su * (segment_int(x[3], y[3], x[2], y[2], wl, wz) +
-                                         segment_int(x[1], y[1], x[3], y[3], wl, wz));
-                    wd -= kh[1] * su;
-                }
-                if (wd != 0.0) acc += wd * segment_int(x[1], y[1], x[2], y[2], wl, wz);
-                if (lo_live && !lo_full) {
-                    clip |= 1u;
-                    kw[0] = kh[0];
-                }
-                if (up_live && !up_full) {
-                    clip |= 2u;
-                    kw[1] = kh[1];
-                }
-            } else {
-                // a clamped half (its replacement triangle): each triangle on its own
+                bool lo_ok = lo_full, up_ok = up_full;
+                if (lo_full || up_full) {
+                    // edges 0 -> 1, 2 -> 0 (lower), 3 -> 2, 1 -> 3 (upper), 1 -> 2 (both)
+                    constexpr int from[5] = {0, 2, 3, 1, 1}, to[5] = {1, 0, 2, 3, 2};
+                    double v[5];
+                    bool ok[5];
 #pragma unroll
-                for (int half = 0; half < 2; ++half) {
-                    const double kj = kh[half];
-                    if (kj == 0.0) continue;
-                    double r[6];
-                    cell_triangle(H, i, j, half, c, sn, r);
-                    if (r[0] < -wz && r[2] < -wz && r[4] < -wz) continue;  // left of V
-                    if (visible(r[0], r[1], wz) && visible(r[2], r[3], wz) && visible(r[4], r[5], wz)) {
-                        acc += kj * (segment_int(r[0], r[1], r[2], r[3], wl, wz) +
-                                     segment_int(r[2], r[3], r[4], r[5], wl, wz) +
-                                     segment_int(r[4], r[5], r[0], r[1], wl, wz));
-                    } else {
-                        clip |= 1u << half;
-                        kw[half] = kj;
+                    for (int e = 0; e < 5; ++e) {
+                        const int f = from[e], t = to[e];
+                        v[e] = segment_short(x[f], y[f], mz[f], x[t], y[t], mz[t], wl, wz, &ok[e]);
                     }
+                    lo_ok = lo_full && ok[0] && ok[1] && ok[4];
+                    up_ok = up_full && ok[2] && ok[3] && ok[4];
+                    if (lo_ok) acc += kh[0] * sl * (v[0] + v[4] + v[1]);
+                    if (up_ok) acc += kh[1] * su * (v[2] - v[4] + v[3]);
                 }
+                clip = (lo_live && !lo_full ? 1u : 0u) | (up_live && !up_full ? 2u : 0u);
+                far = (lo_full && !lo_ok ? 1u : 0u) | (up_full && !up_ok ? 2u : 0u);
+                kw[0] = kh[0];
+                kw[1] = kh[1];
+            } else {
+                // a clamped half: its replacement triangle
+                clip = (kh[0] != 0.0 ? 1u : 0u) | (kh[1] != 0.0 ? 2u : 0u);
+                kw[0] = kh[0];
+                kw[1] = kh[1];
             }
+        }
+        ca += da;
+        cb += db;
+        if (ca >= nx) {
+            ca -= nx;
+            ++cb;
         }
         // queue the triangles that need clipping (lane order)
         int tot;
@@ -375,27 +513,54 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4, 8))) void
 #pragma unroll
         for (int half = 0; half < 2; ++half)
             if (clip & (1u << half)) {
-                clip_cell[at] = cell | ((uint32_t)half << 26);
-                clip_w[at] = kw[half];
+                Q.cell[at] = cell | ((uint32_t)half << 26);
+                Q.w[at] = kw[half];
                 ++at;
             }
         qn += tot;
+        if (__ballot(far != 0u) != 0ull) {
+            at = kClipCap - 1 - nf - wave_prefix_small(__popc(far), &tot);
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+                if (far & (1u << half)) {
+                    Q.cell[at] = cell | ((uint32_t)half << 26);
+                    Q.w[at] = kw[half];
+                    --at;
+                }
+            nf += tot;
+        }
         wave_sync();
         // full rounds, and at the end whatever is left
-        while (qn >= 64 || (qn > 0 && base + 64 >= total)) {
-            const int cnt = min(qn, 64);
-            qn -= cnt;
-            if (lane < cnt) {
-                const uint32_t e = clip_cell[qn + lane];
-                double r[6];
-                cell_triangle(H, (int)(e & 0x1fffu), (int)((e >> 13) & 0x1fffu), (int)(e >> 26), c, sn, r);
-                acc += clip_w[qn + lane] * triangle_int_clipped(r, wl, wz);
+        const bool last = base + step >= total;
+        const int least = last ? 1 : kClipRound;
+        while (nf >= least) {
+            const int cnt = min(nf, kClipRound);
+            acc += far_round(H, Q, kClipCap - nf, cnt, lane, c, sn, wl, wz);
+            nf -= cnt;
+        }
+        while (qn >= least || (last && na > 0)) {
+            if (qn >= least) {
+                const int cnt = min(qn, kClipRound);
+                qn -= cnt;
+                acc += clip_round(H, Q, qn, cnt, lane, c, sn, wl, wz, &na);
+                wave_sync();
             }
-            wave_sync();
+            if (na >= 64 || (last && qn == 0)) {
+                const int cnt = min(na, 64);
+                na -= cnt;
+                if (lane < cnt) acc += Q.arc_w[na + lane] * boundary_int(Q.arc_a[na + lane], Q.arc_b[na + lane], wz);
+                wave_sync();
+            }
         }
     }
-    const double P = wave_sum_f64(acc);
-    if (lane == 0) {
+    double P = wave_sum_f64(acc);
+    if (W > 1) {
+        if (lane == 0) sums[wave] = P;
+        __syncthreads();
+        P = sums[0];
+        for (int w = 1; w < W; ++w) P += sums[w];
+    }
+    if (threadIdx.x == 0) {
         a.P[qi] = (float)P;
         if (a.lambda) a.lambda[qi] = (float)(P / wz - 1.0);
     }
@@ -433,49 +598,69 @@ __global__ void k_cost_hist(const pndf_query* __restrict__ q, int64_t nq, float 
     if (threadIdx.x < kCostBins && loc[threadIdx.x]) atomicAdd(&hist[threadIdx.x], loc[threadIdx.x]);
 }
 
-// exclusive scan of the 64 counters, one wavefront
-__global__ void k_cost_scan(uint32_t* hist)
-{
-    const int t = threadIdx.x;
-    uint32_t v = hist[t], run = v;
-    for (int o = 1; o < kCostBins; o <<= 1) {
-        const uint32_t u = __shfl_up(run, o);
-        if (t >= o) run += u;
-    }
-    hist[t] = run - v;
-}
-
-__global__ void k_cost_scatter(const uint32_t* __restrict__ key, int64_t nq, uint32_t* __restrict__ cursor,
+// hist: the counters, then the cursors within the classes
+__global__ void k_cost_scatter(const uint32_t* __restrict__ key, int64_t nq, uint32_t* __restrict__ hist,
                                uint32_t* __restrict__ order)
 {
-    __shared__ uint32_t loc[kCostBins];
-    if (threadIdx.x < kCostBins) loc[threadIdx.x] = 0u;
+    __shared__ uint32_t loc[kCostBins], first[kCostBins];
+    uint32_t* cursor = hist + kCostBins;
+    if (threadIdx.x < kCostBins) {
+        // the classes' first places, an exclusive scan by one wavefront
+        const uint32_t v = hist[threadIdx.x];
+        uint32_t run = v;
+        for (int o = 1; o < kCostBins; o <<= 1) {
+            const uint32_t u = __shfl_up(run, o);
+            if ((int)threadIdx.x >= o) run += u;
+        }
+        first[threadIdx.x] = run - v;
+        loc[threadIdx.x] = 0u;
+    }
     __syncthreads();
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = i0; i < nq; i += stride) atomicAdd(&loc[key[i]], 1u);
     __syncthreads();
-    if (threadIdx.x < kCostBins && loc[threadIdx.x]) loc[threadIdx.x] = atomicAdd(&cursor[threadIdx.x], loc[threadIdx.x]);
+    if (threadIdx.x < kCostBins && loc[threadIdx.x]) loc[threadIdx.x] = first[threadIdx.x] + atomicAdd(&cursor[threadIdx.x], loc[threadIdx.x]);
     __syncthreads();
     for (int64_t i = i0; i < nq; i += stride) order[atomicAdd(&loc[key[i]], 1u)] = (uint32_t)i;
 }
 
 __global__ void k_cost_zero(uint32_t* hist)
 {
-    if (threadIdx.x < kCostBins) hist[threadIdx.x] = 0u;
+    if (threadIdx.x < 2 * kCostBins) hist[threadIdx.x] = 0u;
 }
 
 }  // namespace
 
+// Wavefronts that share a query (see k_projected_area): a small batch leaves the chip
+// idle otherwise, and its longest query decides.  Of sigma 1 to 8 on a scratched 1024^2
+// map, 8, 4 or 1 wavefronts each: 256 queries 60, 88, 340 us; 1024: -, 118, 349; 4096:
+// -, 288, 443 (ordered).  Beyond, the queries fill the chip and the setup that each
+// wavefront repeats costs more than the sharing gives (narrow footprints, 65536 queries: 564
+// against 234 us).
+static int projarea_waves(int64_t nq) { return nq <= 512 ? 8 : (nq <= 4096 ? 4 : 1); }
+
+template <int KER>
+static void launch_queries(const HierDev& H, const ProjArgs& c, hipStream_t s)
+{
+    const dim3 grid((unsigned)c.nq);
+    const int w = projarea_waves(c.nq);
+    if (w == 8) hipLaunchKernelGGL((k_projected_area<KER, 8>), grid, dim3(512), 0, s, H, c);
+    else if (w == 4) hipLaunchKernelGGL((k_projected_area<KER, 4>), grid, dim3(256), 0, s, H, c);
+    else hipLaunchKernelGGL((k_projected_area<KER, 1>), grid, dim3(64), 0, s, H, c);
+}
+
 hipError_t launch_projected_area(const HierDev& H, const ProjArgs& a, hipStream_t s)
 {
-    // one wavefront-sized workgroup per query, in launches of at most launch_chunk()
-    // workgroups (2^24 x 64 = 2^30 work-items), each in heaviest-first order
-    // (workspace: order, keys and counters of one launch, stream-ordered)
+    // one workgroup per query, in launches of at most launch_chunk() (2^24 x 64 = 2^30
+    // work-items), each in heaviest-first order (workspace: order, keys and counters of
+    // one launch, stream-ordered).  Up to kAllResident queries all run at once, in any
+    // order.
+    constexpr int64_t kAllResident = 4096;
     const int64_t chunk = launch_chunk();
     const int64_t most = std::min(chunk, a.nq);
     uint32_t* buf = nullptr;
-    if (most > 0) {
-        const hipError_t e = hipMallocAsync((void**)&buf, sizeof(uint32_t) * (2 * (size_t)most + kCostBins), s);
+    if (most > kAllResident) {
+        const hipError_t e = hipMallocAsync((void**)&buf, sizeof(uint32_t) * (2 * (size_t)most + 2 * kCostBins), s);
         if (e != hipSuccess) return e;
     }
     for (int64_t off = 0; off < a.nq; off += chunk) {
@@ -484,24 +669,21 @@ hipError_t launch_projected_area(const HierDev& H, const ProjArgs& a, hipStream_
         c.P = a.P + off;
         if (a.lambda) c.lambda = a.lambda + off;
         c.nq = std::min(chunk, a.nq - off);
-        uint32_t* key = buf + most;
-        uint32_t* hist = key + most;
-        const unsigned g = (unsigned)std::max<int64_t>(1, std::min<int64_t>(256, (c.nq + 4095) / 4096));
-        hipLaunchKernelGGL(k_cost_zero, dim3(1), dim3(64), 0, s, hist);
-        hipLaunchKernelGGL(k_cost_hist, dim3(g), dim3(256), 0, s, c.q, c.nq, c.s2r, c.kernel, H, key, hist);
-        hipLaunchKernelGGL(k_cost_scan, dim3(1), dim3(kCostBins), 0, s, hist);
-        hipLaunchKernelGGL(k_cost_scatter, dim3(g), dim3(256), 0, s, key, c.nq, hist, buf);
-        c.order = buf;
-        const dim3 grid((unsigned)c.nq), block(64);
-        if (a.kernel == PNDF_KERNEL_DISK)
-            hipLaunchKernelGGL(k_projected_area<PNDF_KERNEL_DISK>, grid, block, 0, s, H, c);
-        else if (a.kernel == PNDF_KERNEL_BOX)
-            hipLaunchKernelGGL(k_projected_area<PNDF_KERNEL_BOX>, grid, block, 0, s, H, c);
-        else
-            hipLaunchKernelGGL(k_projected_area<PNDF_KERNEL_GAUSSIAN>, grid, block, 0, s, H, c);
+        if (c.nq > kAllResident) {
+            uint32_t* key = buf + most;
+            uint32_t* hist = key + most;
+            const unsigned g = (unsigned)std::min<int64_t>(256, (c.nq + 1023) / 1024);
+            hipLaunchKernelGGL(k_cost_zero, dim3(1), dim3(2 * kCostBins), 0, s, hist);
+            hipLaunchKernelGGL(k_cost_hist, dim3(g), dim3(256), 0, s, c.q, c.nq, c.s2r, c.kernel, H, key, hist);
+            hipLaunchKernelGGL(k_cost_scatter, dim3(g), dim3(256), 0, s, key, c.nq, hist, buf);
+            c.order = buf;
+        }
+        if (a.kernel == PNDF_KERNEL_DISK) launch_queries<PNDF_KERNEL_DISK>(H, c, s);
+        else if (a.kernel == PNDF_KERNEL_BOX) launch_queries<PNDF_KERNEL_BOX>(H, c, s);
+        else launch_queries<PNDF_KERNEL_GAUSSIAN>(H, c, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {
-            (void)hipFreeAsync(buf, s);
+            if (buf) (void)hipFreeAsync(buf, s);
             return e;
         }
     }
