@@ -918,7 +918,7 @@ __global__ __launch_bounds__(256) void k_eval_brute(HierDev H, EvalArgs a)
     if (local >= a.slots) return;
     const int64_t qi = a.slot0 + local;
     const int lane = threadIdx.x & 63;
-    const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, 0.f, H.L, H.eps, a.kernel));
+    const QuerySetup q = setup_wave<KER>(a.q[qi], a.s2r, 0.f, H);
     if (!q.valid) { invalid<MODE>(a, qi); return; }
     const int n = H.n, msk = n - 1;
     const int spanx = q.cxhi - q.cxlo + 1, spany = q.cyhi - q.cylo + 1;
@@ -968,7 +968,7 @@ __global__ __launch_bounds__(64) void k_eval_plain(HierDev H, EvalArgs a)
     if (MODE == kModeValue && a.narrow && slot >= (int64_t)*a.narrow) return;  // a wide query (k_tile_emit)
     const int64_t qi = a.order ? (int64_t)a.order[slot] : slot;
     uint32_t* lists = lds;
-    const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, a.kernel));
+    const QuerySetup q = setup_wave<KER>(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H);
     if (!q.valid) { invalid<MODE>(a, qi); return; }
     Acc acc;
     Rec rec{a.ids, a.terms, MODE == kModeRecord ? a.offsets[qi] : 0,
@@ -1021,7 +1021,7 @@ __global__ __launch_bounds__(64 * W) void k_eval_split(HierDev H, EvalArgs a)
     const QuerySetup u = setup_support(a.q[qi], a.s2r);
     const bool alone = !(u.valid && fmaxf(u.rx, u.ry) > kSplitAlone);
     if (alone && wave != 0) return;
-    const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, a.kernel));
+    const QuerySetup q = setup_wave<KER>(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H);
     if (!q.valid) {
         invalid<kModeValue>(a, qi);
         return;
@@ -1151,7 +1151,7 @@ __global__ __launch_bounds__(64) void k_tile_emit(HierDev H, EvalArgs a)
         if (c.at >= c.end) break;
         for (uint32_t local = c.at; local < c.end; ++local) {
             const int64_t qi = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.order[first + local]);
-            const QuerySetup q = uniform_query(setup_query(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H.L, H.eps, a.kernel));
+            const QuerySetup q = setup_wave<KER>(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H);
             Acc acc;
             const int lr = max(descent_start<CUT>(H, q), kTileLevel);
             bool ok;
@@ -1549,7 +1549,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
             root_ok = false;
             tested = false;
         }
-        const QuerySetup q = uniform_query(setup_query(qs[qi], pa.s2r, CUT ? pa.tau : 0.f, H.L, H.eps, pa.kernel));
+        const QuerySetup q = setup_wave<KER>(qs[qi], pa.s2r, CUT ? pa.tau : 0.f, H);
         Acc acc;
         if (lev < 0) {
             lev = descent_start<CUT>(H, q);

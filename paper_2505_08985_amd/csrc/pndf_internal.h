@@ -510,9 +510,19 @@ __device__ __forceinline__ QuerySetup setup_support(const pndf_query& qr, float 
     return q;
 }
 
+__device__ __forceinline__ double readlane_f64(double v, int lane)
+{
+    const long long b = __double_as_longlong(v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)b, lane);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(b >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 // Support box, entry level and kernel constants of one query (see pndf.h).
-__device__ inline QuerySetup setup_query(const pndf_query& qr, float s2r, float tau, int L,
-                                         float eps, int kernel)
+// WAVE: the query is the same in all 64 lanes, which are active; three of them take one
+// of the three divisions each.
+template <bool WAVE>
+__device__ __forceinline__ QuerySetup setup_as(const pndf_query& qr, float s2r, float tau, int L, float eps, int kernel)
 {
     QuerySetup q = setup_support(qr, s2r);
     const bool ok = q.valid;
@@ -535,29 +545,42 @@ __device__ inline QuerySetup setup_query(const pndf_query& qr, float s2r, float 
     q.cxlo = (int)ceilf(lox) - 1; q.cxhi = (int)floorf(hix);
     q.cylo = (int)ceilf(loy) - 1; q.cyhi = (int)floorf(hiy);
     float rmax = fmaxf(rx, ry);
-    int l0 = 0;
-    while (l0 < L && (float)(1 << l0) < rmax) l0++;
-    q.l0 = l0;
+    // the smallest l0 with 2^l0 >= rmax
+    const int up = (int)((__float_as_uint(rmax) + 0x7fffffu) >> 23) - 127;
+    q.l0 = min(max(up, 0), L);
     q.t = tau > 0.f ? __fmul_rn(__fmul_rn(rx, ry), tau) : -1.f;
     const double log2e = 1.4426950408889634074;
-    q.kx = log2e / (2.0 * (double)qr.sx * (double)qr.sx);
-    q.ky = log2e / (2.0 * (double)qr.sy * (double)qr.sy);
     const double pi = 3.14159265358979323846;
-    const double norm = kernel == PNDF_KERNEL_BOX    ? 1.0 / (4.0 * (double)rx * (double)ry)
-                        : kernel == PNDF_KERNEL_DISK ? 1.0 / (pi * (double)rx * (double)ry)
-                                                     : 1.0 / (2.0 * pi * (double)qr.sx * (double)qr.sy);
-    q.norm = norm;
+    const double peak = kernel == PNDF_KERNEL_BOX ? 4.0 : (kernel == PNDF_KERNEL_DISK ? pi : 2.0 * pi);
+    const float ex = kernel == PNDF_KERNEL_GAUSSIAN ? qr.sx : rx, ey = kernel == PNDF_KERNEL_GAUSSIAN ? qr.sy : ry;
+    if constexpr (WAVE) {
+        const int lane = (int)(threadIdx.x & 63);
+        const double f = lane == 2 ? peak : 2.0, num = lane == 2 ? 1.0 : log2e;
+        const float u = lane == 2 ? ex : (lane == 1 ? qr.sy : qr.sx), v = lane == 2 ? ey : (lane == 1 ? qr.sy : qr.sx);
+        const double d = num / (f * (double)u * (double)v);
+        q.kx = readlane_f64(d, 0);
+        q.ky = readlane_f64(d, 1);
+        q.norm = readlane_f64(d, 2);
+    } else {
+        q.kx = log2e / (2.0 * (double)qr.sx * (double)qr.sx);
+        q.ky = log2e / (2.0 * (double)qr.sy * (double)qr.sy);
+        q.norm = 1.0 / (peak * (double)ex * (double)ey);
+    }
     // Every term is at most norm / eps per included cell image and triangle (node
     // images of a cluster reach at most one cell beyond the box per side), so
     // D < bound = 2 (nx + 2) (ny + 2) norm / eps.  The exact accumulator counts in
     // units of 2^fexp with bound < 2^(fexp + 190): 192 bits hold any D, and every
     // float32 term down to bound 2^-190 is represented exactly.
     const double bound = 2.0 * ((double)(q.cxhi - q.cxlo) + 3.0) * ((double)(q.cyhi - q.cylo) + 3.0) *
-                         norm / (double)eps;
+                         q.norm / (double)eps;
     int e2;
     frexp(bound, &e2);
     q.fexp = e2 + 1 - 190;
     return q;
+}
+__device__ inline QuerySetup setup_query(const pndf_query& qr, float s2r, float tau, int L, float eps, int kernel)
+{
+    return setup_as<false>(qr, s2r, tau, L, eps, kernel);
 }
 
 // The setup of a query owned by a whole wave is the same in every lane: keep it in
@@ -595,6 +618,12 @@ __device__ __forceinline__ QuerySetup uniform_query(const QuerySetup& q)
     u.fexp = __builtin_amdgcn_readfirstlane(q.fexp);
     u.valid = __builtin_amdgcn_readfirstlane((int)q.valid) != 0;
     return u;
+}
+// The setup of the query of a whole wave.
+template <int KER>
+__device__ __forceinline__ QuerySetup setup_wave(const pndf_query& qr, float s2r, float tau, const HierDev& H)
+{
+    return uniform_query(setup_as<true>(qr, s2r, tau, H.L, H.eps, KER));
 }
 
 // Bits [64 w, 64 w + 64) of m 2^sh for s = sh - 64 w (m < 2^53): m << s for
@@ -854,24 +883,17 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return v;
 }
 
-// Row shift of a 64-bit value by DPP (control 0x110 + n: row_shr n; lanes shifted in
-// from outside the 16-lane row read 0).
-template <int CTRL>
-__device__ __forceinline__ uint64_t dpp_row_shr(uint64_t v)
+// Wave sum of a 32-bit value, in lane 63: row shifts 1, 2, 4, 8 (lane 15 of each row
+// of 16 then holds its sum), then lane 15 to the next row's and lane 31 to the upper half.
+__device__ __forceinline__ uint32_t dpp_sum_u32(uint32_t v)
 {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, 0xf, 0xf, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), CTRL, 0xf, 0xf, false);
-    return ((uint64_t)hi << 32) | lo;
-}
-
-template <int CTRL>
-__device__ __forceinline__ void fix_add_row_shr(Fix192& v)
-{
-    Fix192 w;
-    w.w0 = dpp_row_shr<CTRL>(v.w0);
-    w.w1 = dpp_row_shr<CTRL>(v.w1);
-    w.w2 = dpp_row_shr<CTRL>(v.w2);
-    fix_add(v, w);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);
+    return v;
 }
 
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane)
@@ -881,27 +903,29 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int lane)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// Exact sum over the wave (every lane must be active): within each row of 16 lanes
-// by DPP row shifts 1, 2, 4, 8 (lane 15 of the row then holds the row's sum), then
-// the four row sums read from lanes 15, 31, 47 and 63.
-__device__ __forceinline__ Fix192 wave_sum_fix(Fix192 v)
+// Exact sum over the wave (every lane must be active), modulo 2^192.  In eight limbs of
+// 26 bits, as 64 of them sum within 32: one instruction per limb and step and no carries
+// until the sums are in scalar registers (about 90 vector instructions; as three
+// 64-bit words with carries 176).
+__device__ __forceinline__ Fix192 wave_sum_fix(const Fix192& v)
 {
-    fix_add_row_shr<0x111>(v);
-    fix_add_row_shr<0x112>(v);
-    fix_add_row_shr<0x114>(v);
-    fix_add_row_shr<0x118>(v);
-    Fix192 s;
-    s.w0 = readlane_u64(v.w0, 15);
-    s.w1 = readlane_u64(v.w1, 15);
-    s.w2 = readlane_u64(v.w2, 15);
+    const uint32_t d[6] = {(uint32_t)v.w0, (uint32_t)(v.w0 >> 32), (uint32_t)v.w1, (uint32_t)(v.w1 >> 32),
+                           (uint32_t)v.w2, (uint32_t)(v.w2 >> 32)};
+    uint64_t sum[8];
 #pragma unroll
-    for (int r = 1; r < 4; ++r) {
-        Fix192 t;
-        t.w0 = readlane_u64(v.w0, 16 * r + 15);
-        t.w1 = readlane_u64(v.w1, 16 * r + 15);
-        t.w2 = readlane_u64(v.w2, 16 * r + 15);
-        fix_add(s, t);
+    for (int k = 0; k < 8; ++k) {
+        const int at = 26 * k, i = at >> 5, sh = at & 31;
+        const uint32_t t = sh == 0 ? d[i] : (i == 5 ? d[5] >> sh : __builtin_amdgcn_alignbit(d[i + 1], d[i], sh));
+        sum[k] = (uint32_t)__builtin_amdgcn_readlane((int)dpp_sum_u32(t & 0x3ffffffu), 63);
     }
+    const uint64_t a0 = sum[0] + (sum[1] << 26), a1 = sum[2] + (sum[3] << 26);  // at bits 0, 52, 104, 156
+    const uint64_t a2 = sum[4] + (sum[5] << 26), a3 = sum[6] + (sum[7] << 26);
+    Fix192 s;
+    s.w0 = a0 + (a1 << 52);
+    const uint64_t c0 = s.w0 < a0 ? 1ull : 0ull, m = (a1 >> 12) + c0;  // < 2^48
+    s.w1 = m + (a2 << 40);
+    const uint64_t c1 = s.w1 < m ? 1ull : 0ull;
+    s.w2 = (a2 >> 24) + (a3 << 28) + c1;
     return s;
 }
 

@@ -391,7 +391,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const int lane = threadIdx.x & 63, wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     ClipQueue& Q = queues[wave];
     const pndf_query qr = a.q[qi];
-    const QuerySetup q = uniform_query(setup_query(qr, a.s2r, 0.f, H.L, H.eps, KER));
+    const QuerySetup q = setup_wave<KER>(qr, a.s2r, 0.f, H);
     const double wx = qr.hx, wy = qr.hy;
     const double wl2 = wx * wx + wy * wy;
     if (!q.valid || !(wl2 <= 1.0)) {
