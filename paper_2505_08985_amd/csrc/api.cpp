@@ -60,6 +60,53 @@ void blocks_expire(Blocks& b)
 
 }  // namespace
 
+namespace {
+constexpr int kPoolDevices = 64;
+struct Pools {
+    std::mutex mu;
+    hipMemPool_t pool[kPoolDevices] = {};
+    bool refused[kPoolDevices] = {};  // no pools on this device: the default one serves
+};
+Pools& pools()
+{
+    static Pools* p = new Pools;  // (as the runtime may be gone at exit)
+    return *p;
+}
+
+hipMemPool_t pool_of(int dev)
+{
+    if (dev < 0 || dev >= kPoolDevices) return nullptr;
+    Pools& p = pools();
+    std::lock_guard<std::mutex> lock(p.mu);
+    if (p.pool[dev] || p.refused[dev]) return p.pool[dev];
+    hipMemPoolProps props{};
+    props.allocType = hipMemAllocationTypePinned;
+    props.location.type = hipMemLocationTypeDevice;
+    props.location.id = dev;
+    hipMemPool_t made = nullptr;
+    uint64_t keep = kStreamKeep;
+    int wait = 0;
+    if (hipMemPoolCreate(&made, &props) == hipSuccess &&
+        hipMemPoolSetAttribute(made, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess &&
+        hipMemPoolSetAttribute(made, hipMemPoolReuseAllowInternalDependencies, &wait) == hipSuccess) {
+        p.pool[dev] = made;
+        return made;
+    }
+    (void)hipGetLastError();
+    if (made) (void)hipMemPoolDestroy(made);
+    p.refused[dev] = true;
+    return nullptr;
+}
+
+void pool_trim(int dev)
+{
+    if (dev < 0 || dev >= kPoolDevices) return;
+    Pools& p = pools();
+    std::lock_guard<std::mutex> lock(p.mu);
+    if (p.pool[dev] && hipMemPoolTrimTo(p.pool[dev], 0) != hipSuccess) (void)hipGetLastError();
+}
+}  // namespace
+
 hipError_t block_alloc(size_t bytes, void** p)
 {
     *p = nullptr;
@@ -84,13 +131,27 @@ hipError_t block_alloc(size_t bytes, void** p)
         return hipSuccess;
     }
     e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory && !b.kept.empty()) {
+    if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
+        pool_trim(dev);
         blocks_drop(b, [](const Blocks::Kept&) { return true; });
         e = hipMalloc(p, bytes);
     }
     if (e == hipSuccess) b.used[*p] = {bytes, dev};
     return e;
+}
+
+hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = 0;
+    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
+        hipGetDevice(&dev) == hipSuccess) {
+        const hipMemPool_t pool = pool_of(dev);
+        if (pool && hipMallocFromPoolAsync(p, bytes, pool, s) == hipSuccess) return hipSuccess;
+    }
+    (void)hipGetLastError();
+    return hipMallocAsync(p, bytes, s);
 }
 
 void block_free(void* p)
@@ -104,11 +165,14 @@ void block_free(void* p)
     const int dev = it->second.second;
     b.used.erase(it);
     blocks_expire(b);
+    bool last = true;
+    for (const auto& u : b.used) last = last && u.second.second != dev;
     int cur = 0;
     size_t avail = 0, total = 0;
     bool keep = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess);
     keep = keep && hipDeviceSynchronize() == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess &&
            size <= total / kBlockKeepShare;
+    if (last) pool_trim(dev);
     if (cur != dev) (void)hipSetDevice(cur);
     if (!keep) {
         (void)hipGetLastError();  // (a refused synchronisation is not the caller's error)

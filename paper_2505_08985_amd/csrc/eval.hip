@@ -1803,7 +1803,7 @@ hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s
     int nb, bshift;
     order_shape(H.logn, &nb, &bshift);
     uint32_t* buf = nullptr;  // order[nq] | key[nq] | counters
-    hipError_t e = hipMallocAsync((void**)&buf, sizeof(uint32_t) * (2 * (size_t)nq + order_words(nb, T.ctl != nullptr)), s);
+    hipError_t e = stream_alloc((void**)&buf, sizeof(uint32_t) * (2 * (size_t)nq + order_words(nb, T.ctl != nullptr)), s);
     if (e != hipSuccess) return e;
     e = order_passes(H, q, nq, s2r, T.ctl, buf, narrow, s);
     if (e != hipSuccess) {
@@ -1890,7 +1890,7 @@ void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s)
     const size_t bytes = tiles_bytes(H, nq);
     void* buf = nullptr;
     if (!bytes) return;
-    if (hipMallocAsync(&buf, bytes, s) != hipSuccess) {
+    if (stream_alloc(&buf, bytes, s) != hipSuccess) {
         (void)hipGetLastError();
         return;
     }

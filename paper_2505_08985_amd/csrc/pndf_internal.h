@@ -392,6 +392,17 @@ constexpr size_t kBlockKeepShare = 128;   // 1 / 128
 constexpr double kBlockKeepSeconds = 10.0;
 hipError_t block_alloc(size_t bytes, void** p);
 void block_free(void* p);
+
+// Workspace of one call, in stream order; given back with hipFreeAsync.  The
+// device's default pool returns its memory to the driver at each synchronisation, and a
+// caller that waits for every batch pays for mapping it anew (a 16384-query tile
+// of the 4096^2 map: 561 us instead of 207, 67 MB each for the tile items and their sorted copy).  Calls therefore
+// draw on a pool of the library's own, which keeps up to kStreamKeep bytes (the largest
+// workspace of a round of tiles is 360 MB) until the last handle on the device is released
+// or a map finds no memory.  It never makes one stream wait for another's release.  Under
+// capture the default pool serves, whose allocations become nodes of the graph.
+constexpr uint64_t kStreamKeep = (uint64_t)512 << 20;
+hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s);
 // Lays arrays out in one allocation (256 B aligned): sizes first, then pointers.
 struct Arena {
     char* base = nullptr;

@@ -660,7 +660,7 @@ hipError_t launch_projected_area(const HierDev& H, const ProjArgs& a, hipStream_
     const int64_t most = std::min(chunk, a.nq);
     uint32_t* buf = nullptr;
     if (most > kAllResident) {
-        const hipError_t e = hipMallocAsync((void**)&buf, sizeof(uint32_t) * (2 * (size_t)most + 2 * kCostBins), s);
+        const hipError_t e = stream_alloc((void**)&buf, sizeof(uint32_t) * (2 * (size_t)most + 2 * kCostBins), s);
         if (e != hipSuccess) return e;
     }
     for (int64_t off = 0; off < a.nq; off += chunk) {
