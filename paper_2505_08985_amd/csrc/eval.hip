@@ -5,9 +5,12 @@
 //   - brute force: lanes stride over the included cells;
 //   - hierarchical: a breadth-limited, depth-first quad-tree descent.  Each level
 //     has a list in LDS; the wave pops up to 64 nodes of the lowest non-empty level
-//     (one per lane), tests the min-max box (and the cluster cut), and pushes the
-//     surviving children with a ballot prefix.  A level-1 node tests the triangles
+//     (one per lane), tests their children's octagons (and the cluster cut), and pushes
+//     the surviving children with a ballot prefix.  A level-1 node tests the triangles
 //     of its 2 x 2 cells from its leaf record.
+//   - split: the wavefronts of a workgroup share a query of a small batch.
+//   - tiles: queries wider than a 256-texel tile leave their surviving tiles as items,
+//     which are sorted and evaluated tile by tile.
 //   - persistent: a fixed grid of workers takes chunks of queries (each XCD from
 //     its own share of the spatial order); once the queries run out, idle workers
 //     ask the busy ones for part of their pending subtrees through a global task
@@ -15,8 +18,8 @@
 // Triangle tests run in float32 and only queue the hits; a queued hit is confirmed
 // and its barycentrics recomputed in FP64 from the float32 vertices 64 at a time
 // (one per lane), so the recovered uv and the term are accurate even for sliver
-// triangles while the traversal itself stays small.  Jacobians come from the mesh build
-// (FP64, clamped), never from the hot loop.  Terms are summed exactly (192-bit
+// triangles while the traversal itself stays small.  The hit's Jacobian is formed there
+// from the same corners, as the mesh build forms the stored one.  Terms are summed exactly (192-bit
 // fixed point at a per-query binary point), so D does not depend on the order in
 // which hits are found: all algorithms, batch compositions and work splits give
 // the same bits.
@@ -1651,7 +1654,7 @@ __global__ void k_order_zero(OrderArgs o)
     if (o.ctl) tile_reset(o.ctl, t);
 }
 
-constexpr int kOrderMaxBins = 8192;
+constexpr int kOrderMaxBins = (1 << (2 * kOrderBits)) + (1 << (2 * kOrderBits - kOrderWideShift));
 constexpr int kOrderThreads = 1024;
 
 __device__ __forceinline__ uint32_t order_bucket(const pndf_query& q, int n, int bshift)
@@ -1678,7 +1681,7 @@ __device__ __forceinline__ void order_hist(const pndf_query* __restrict__ q, int
         if (bins > nb) {
             // (a query the evaluation rejects is not wide: k_eval_plain answers it)
             const QuerySetup u = setup_support(qr, s2r);
-            if (u.valid && fmaxf(u.rx, u.ry) > wide) k += nb;
+            if (u.valid && fmaxf(u.rx, u.ry) > wide) k = nb + (k >> kOrderWideShift);
         }
         key[i] = k;
         atomicAdd(&loc[k], 1u);
@@ -1688,27 +1691,33 @@ __device__ __forceinline__ void order_hist(const pndf_query* __restrict__ q, int
         if (loc[b]) atomicAdd(&hist[b], loc[b]);
 }
 
-// exclusive scan of `bins` counters into LDS by a workgroup of 1024 threads
+// exclusive scan of `bins` counters into LDS by a workgroup of 1024 threads: each
+// thread's run of counters, the wave's threads by shuffles, the waves' sums from LDS
 __device__ __forceinline__ void order_scan(const uint32_t* __restrict__ hist, int bins, uint32_t* first)
 {
-    __shared__ uint32_t part[kOrderThreads];
-    const int t = threadIdx.x, per = (bins + kOrderThreads - 1) / kOrderThreads;
-    uint32_t sum = 0;
-    for (int k = 0; k < per; ++k)
-        if (t * per + k < bins) sum += hist[t * per + k];
-    part[t] = sum;
-    __syncthreads();
-    for (int o = 1; o < kOrderThreads; o <<= 1) {
-        const uint32_t v = t >= o ? part[t - o] : 0u;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
+    constexpr int per = (kOrderMaxBins + kOrderThreads - 1) / kOrderThreads;
+    __shared__ uint32_t part[kOrderThreads / 64];
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    uint32_t v[per], sum = 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        v[k] = t * per + k < bins ? hist[t * per + k] : 0u;
+        sum += v[k];
     }
-    uint32_t run = part[t] - sum;
+    uint32_t run = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(run, o);
+        if (lane >= o) run += u;
+    }
+    if (lane == 63) part[wave] = run;
+    __syncthreads();
+    run -= sum;
+    for (int w = 0; w < wave; ++w) run += part[w];
+#pragma unroll
     for (int k = 0; k < per; ++k)
         if (t * per + k < bins) {
             first[t * per + k] = run;
-            run += hist[t * per + k];
+            run += v[k];
         }
     __syncthreads();
 }
@@ -1771,7 +1780,7 @@ static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, TileCtl* ct
     order_shape(H.logn, &o.nb, &o.bshift);
     o.nq = nq;
     o.n = H.n;
-    o.bins = ctl ? 2 * o.nb : o.nb;
+    o.bins = order_bins(o.nb, ctl != nullptr);
     o.s2r = s2r;
     o.wide = (float)(1 << kTileLevel);
     o.order = buf;

@@ -276,13 +276,17 @@ struct PersistArgs {
     long long wait_ticks; // give-up bound of a worker's waits, in wall_clock64 ticks
 };
 
-// Arguments of the spatial order's passes.  With tiles, buckets [nb, 2 nb) hold the
-// wide queries (half-width above `wide`), so they come last in the same order.
+// Arguments of the spatial order's passes.  With tiles, the buckets from nb on hold the
+// wide queries, 8 x 8 coarser than the others' (k_tile_emit reads the upper levels only,
+// and its items are sorted by tile).  As many as the others have made the passes
+// longer (a 16384-query tile 188 us, with a scan by barriers instead of shuffles; now 180) and
+// gained nothing (60001 wide queries 46.8 and 46.9 ms).
+constexpr int kOrderWideShift = 6;
 struct OrderArgs {
     const pndf_query* q;
     int64_t nq;
     const QueueCtl* batch;     // a plan's passes: q and nq are read from here
-    int n, bshift, nb, bins;   // bins = 2 nb with tiles, else nb
+    int n, bshift, nb, bins;   // bins = order_bins()
     float s2r, wide;
     uint32_t* key;
     uint32_t* hist;            // bins counters, then bins cursors
@@ -291,7 +295,8 @@ struct OrderArgs {
     TileCtl* ctl;
 };
 // 32-bit words of the order's counters (the passes' histogram, cursors and *narrow).
-inline size_t order_words(int nb, bool tiles) { return (size_t)(tiles ? 4 : 2) * nb + 1; }
+inline int order_bins(int nb, bool tiles) { return tiles ? nb + (nb >> kOrderWideShift) : nb; }
+inline size_t order_words(int nb, bool tiles) { return 2 * (size_t)order_bins(nb, tiles) + 1; }
 
 // Device resources and the instantiated launch graph of a persistent plan.
 struct PersistPlan {
