@@ -146,7 +146,7 @@ hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     int dev = 0;
     if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        hipGetDevice(&dev) == hipSuccess) {
+        (s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) == hipSuccess) {
         const hipMemPool_t pool = pool_of(dev);
         if (pool && hipMallocFromPoolAsync(p, bytes, pool, s) == hipSuccess) return hipSuccess;
     }
