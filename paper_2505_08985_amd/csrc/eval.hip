@@ -1102,6 +1102,30 @@ __device__ __forceinline__ void batch_args(EvalArgs& a)
     }
 }
 
+// A round's wide queries, [first, first + count) of them.  Their number and their items
+// are known on the device only, the rounds are launched by the host: round a.slot0 of
+// a.slots.  Each round's sort sets how many the next one takes: all that a round can
+// hold or, if their items (at this round's number per query) would not fit, as many
+// as fill three quarters of the room; no fewer than the rounds that are left need.  What
+// does not fit is evaluated where it was found, each query at its own pace through the
+// memory: 2^22 queries of sigma 4 to 1024 at 4096^2, tau = 1e-4, with 2^24 items for each
+// 2^19 queries 6970 ms, with rounds that fit 3040 (15/16 of the room: 3380).  Many
+// rounds start with a small one; a few do not, as one round more costs what it
+// reads again (2^21 queries at 8192^2, tau = 1e-3, whose items fit: 92.5 and 94.7 ms).
+struct TileRange {
+    uint32_t first, count;
+};
+__device__ __forceinline__ TileRange tile_range(const EvalArgs& a)
+{
+    const TileCtl* c = a.tile.ctl;
+    const int r = (int)a.slot0, rounds = (int)a.slots;
+    const uint32_t first = c->first[r & 1];
+    const int64_t left = max(a.nq - (int64_t)*a.narrow - (int64_t)first, (int64_t)0);
+    const int64_t least = (left + (rounds - r) - 1) / (rounds - r);
+    const uint32_t count = r > 0 ? c->count[r & 1] : (rounds > kTileFewRounds ? kTileFirst : a.tile.round);
+    return TileRange{first, (uint32_t)min(min(left, (int64_t)a.tile.round), max((int64_t)count, least))};
+}
+
 struct Claim {
     uint32_t at, end;
 };
@@ -1143,14 +1167,14 @@ __global__ __launch_bounds__(64) void k_tile_emit(HierDev H, EvalArgs a)
     batch_args(a);
     const TileWork& T = a.tile;
     const int lane = lane_id();
-    const int64_t first = (int64_t)*a.narrow + a.slot0;
-    const int64_t wide = min(a.nq - first, (int64_t)T.round);
-    if (wide <= 0) return;
+    const TileRange range = tile_range(a);
+    const int64_t first = (int64_t)*a.narrow + range.first;
+    if (range.count == 0) return;
     TaskQueue none{};
     Rec rec{nullptr, nullptr, 0, 0};
     int x = 0;
     while (true) {
-        const Claim c = claim_run(T.ctl->qclaim, (uint32_t)wide, kWideClaim, &x);
+        const Claim c = claim_run(T.ctl->qclaim, range.count, kWideClaim, &x);
         if (c.at >= c.end) break;
         for (uint32_t local = c.at; local < c.end; ++local) {
             const int64_t qi = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)a.order[first + local]);
@@ -1209,6 +1233,12 @@ __device__ __forceinline__ void tile_reset(TileCtl* c, int t)
     if (t < kMaxTiles) c->hist[t] = c->cursor[t] = 0;
 }
 
+// Before a batch.
+__device__ __forceinline__ void tile_start(TileCtl* c, int t)
+{
+    if (t == 0) c->first[0] = 0;
+}
+
 constexpr int kTileParts = 8;  // blocks per segment of the sorting passes
 
 // Count the items of each tile (LDS first: one global atomic per tile and block).
@@ -1232,8 +1262,19 @@ __global__ __launch_bounds__(256) void k_tile_hist(TileWork T)
 
 // Place the items by tile: each block counts its share again, reserves its range of
 // every tile (the tiles' first places are a scan of the counts) and writes.
-__global__ __launch_bounds__(256) void k_tile_scatter(TileWork T)
+__global__ __launch_bounds__(256) void k_tile_scatter(EvalArgs a)
 {
+    batch_args(a);
+    const TileWork& T = a.tile;
+    const TileRange range = tile_range(a);
+    const int next = ((int)a.slot0 + 1) & 1;
+    if (range.count == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            T.ctl->first[next] = range.first;
+            T.ctl->count[next] = 0;
+        }
+        return;
+    }
     __shared__ uint32_t loc[kMaxTiles], first[kMaxTiles], part_sum[256];
     const uint32_t seg = blockIdx.x & (kTileSegs - 1), part = blockIdx.x / kTileSegs;
     const uint32_t cnt = min(T.ctl->seg[seg].v, T.segcap);
@@ -1252,6 +1293,15 @@ __global__ __launch_bounds__(256) void k_tile_scatter(TileWork T)
         __syncthreads();
     }
     if (blockIdx.x == 0 && t == 255) T.ctl->total = part_sum[255];
+    if (blockIdx.x == 0 && t < 64) {
+        const uint32_t asked = wave_sum_u32(t < kTileSegs ? T.ctl->seg[t].v : 0u);
+        const uint64_t room = (uint64_t)T.segcap * kTileSegs;
+        if (t == 0) {
+            T.ctl->first[next] = range.first + range.count;
+            const bool fits = (uint64_t)asked * T.round <= room * range.count;
+            T.ctl->count[next] = fits ? T.round : (uint32_t)((uint64_t)range.count * (room / 4 * 3) / asked);
+        }
+    }
     uint32_t run = part_sum[t] - sum;
     for (int k = 0; k < per; ++k)
         if (t * per + k < T.tiles) {
@@ -1283,9 +1333,9 @@ __global__ __launch_bounds__(256) void k_tile_finish(EvalArgs a)
     batch_args(a);
     const int t = blockIdx.x * 256 + threadIdx.x;
     tile_reset(a.tile.ctl, t);
-    const int64_t first = (int64_t)*a.narrow + a.slot0;
-    const int64_t wide = min(a.nq - first, (int64_t)a.tile.round);
-    for (int64_t local = t; local < wide; local += (int64_t)gridDim.x * 256) {
+    const TileRange range = tile_range(a);
+    const int64_t first = (int64_t)*a.narrow + range.first;
+    for (int64_t local = t; local < (int64_t)range.count; local += (int64_t)gridDim.x * 256) {
         const unsigned long long* w = a.tile.acc + 6 * local;
         uint64_t limb[6], carry = 0;
         for (int k = 0; k < 6; ++k) {
@@ -1334,7 +1384,10 @@ __global__ void k_persist_reset(QueueCtl* ctl, Fix192* acc, int* fexp, const pnd
     if (hist)
         for (long long i = t; i < 2 * nb; i += (long long)gridDim.x * blockDim.x) hist[i] = 0;
     if (tiles)
-        for (long long i = t; i < kMaxTiles; i += (long long)gridDim.x * blockDim.x) tile_reset(tiles, (int)i);
+        for (long long i = t; i < kMaxTiles; i += (long long)gridDim.x * blockDim.x) {
+            tile_reset(tiles, (int)i);
+            tile_start(tiles, (int)i);
+        }
     if (t == 0) {
         for (int x = 0; x < kXcds; ++x) ctl->qhead[x].v = 0;
         ctl->head = 0;
@@ -1651,7 +1704,10 @@ __global__ void k_order_zero(OrderArgs o)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     for (int i = t; i < 2 * o.bins; i += gridDim.x * blockDim.x) o.hist[i] = 0;
-    if (o.ctl) tile_reset(o.ctl, t);
+    if (o.ctl) {
+        tile_reset(o.ctl, t);
+        tile_start(o.ctl, t);
+    }
 }
 
 constexpr int kOrderMaxBins = (1 << (2 * kOrderBits)) + (1 << (2 * kOrderBits - kOrderWideShift));
@@ -1999,7 +2055,7 @@ template <typename Add>
 static hipError_t tile_round(const HierDev& H, EvalArgs& a, const TileFuncs& f, Add add)
 {
     const size_t lds = sizeof(uint32_t) * wave_lds_words(H.L, a.tau > 0.f);
-    const int64_t left = a.nq - a.slot0;
+    const int64_t left = std::min<int64_t>(a.nq, a.tile.round);
     void* both[] = {(void*)&H, (void*)&a};
     void* tile[] = {(void*)&a.tile};
     void* all[] = {(void*)&a};
@@ -2007,19 +2063,26 @@ static hipError_t tile_round(const HierDev& H, EvalArgs& a, const TileFuncs& f, 
     const unsigned fin = (unsigned)std::max<int64_t>(kMaxTiles / 256, std::min<int64_t>(1024, (left + 255) / 256));
     hipError_t e = add(f.emit, dim3((unsigned)std::min<int64_t>(kTileWaves, left)), b64, lds, both);
     if (e == hipSuccess) e = add((void*)k_tile_hist, sort, b256, 0, tile);
-    if (e == hipSuccess) e = add((void*)k_tile_scatter, sort, b256, 0, tile);
+    if (e == hipSuccess) e = add((void*)k_tile_scatter, sort, b256, 0, all);
     if (e == hipSuccess) e = add(f.tiles, dim3(kTileWaves), b64, lds, both);
     if (e == hipSuccess) e = add((void*)k_tile_finish, dim3(fin), b256, 0, all);
     return e;
 }
 
-// The wide queries of a batch, in rounds (their number is known on the device only: a
-// round without any costs its five launches).
+// Rounds of a batch's wide queries (their number is known on the device only: a round
+// without any costs its five launches, 23 us).  As many as hold all queries; in large
+// batches twice that, so that rounds may be smaller where queries leave many items.
+static int64_t tile_rounds(int64_t nq, int64_t round)
+{
+    const int64_t n = (nq + round - 1) / round;
+    return n <= kTileFewRounds ? n : (nq + round / 2 - 1) / std::max<int64_t>(1, round / 2);
+}
+
 static hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s)
 {
     const TileFuncs f = tile_funcs(a.tau > 0.f, a.kernel);
-    for (int64_t off = 0; off < a.nq; off += a.tile.round) {
-        a.slot0 = off;
+    a.slots = tile_rounds(a.nq, a.tile.round);
+    for (a.slot0 = 0; a.slot0 < a.slots; ++a.slot0) {
         const hipError_t e = tile_round(H, a, f, [&](void* fn, dim3 g, dim3 b, size_t lds, void** args) {
             return hipLaunchKernel(fn, g, b, args, lds, s);
         });
@@ -2053,8 +2116,9 @@ void persist_prepare(const HierDev& H, PersistPlan& P)
     P.order_bins = P.oargs.bins;
     P.pa.narrow = P.oargs.narrow;
     if (!P.tile.ctl) return;
-    for (int64_t off = 0; off < P.max_nq; off += P.tile.round) {
-        EvalArgs a{nullptr, P.order, P.max_nq, off,     0,     nullptr,  nullptr,     nullptr,
+    const int64_t rounds = tile_rounds(P.max_nq, P.tile.round);
+    for (int64_t r = 0; r < rounds; ++r) {
+        EvalArgs a{nullptr, P.order, P.max_nq, r,       rounds, nullptr,  nullptr,     nullptr,
                    nullptr, nullptr, P.tau,    P.s2r, P.kernel, P.pa.narrow, P.tile};
         a.batch = P.ctl;
         P.targs.push_back(a);

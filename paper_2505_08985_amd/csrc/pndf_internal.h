@@ -225,7 +225,9 @@ constexpr int kTileLevel = 8;
 constexpr int kTileDepth = 3, kTileSpan = 9;
 constexpr int kTileSegs = 64;                        // item segments, each with a counter of its own
 constexpr int kMaxTiles = 1 << (2 * (13 - kTileLevel));
-constexpr int64_t kTileChunk = (int64_t)1 << 19;     // wide queries per round
+constexpr int64_t kTileChunk = (int64_t)1 << 19;     // most wide queries per round
+constexpr int kTileFewRounds = 4;
+constexpr uint32_t kTileFirst = 1u << 17;            // the first of more rounds, before their items are known
 constexpr int64_t kTileItems = (int64_t)1 << 24;     // items per round
 // Maps with tiles: below 1024^2 there are fewer than 16 and the caches hold the map.
 __host__ __device__ inline bool has_tiles(int logn) { return logn >= kTileLevel + 2; }
@@ -234,6 +236,7 @@ struct TileCtl {
         uint32_t v;
     } seg[kTileSegs], qclaim[8], claim[8];           // items written per segment; queries, items claimed per XCD's share
     alignas(128) uint32_t total;                     // items after sorting
+    uint32_t first[2], count[2];                     // wide queries of the even and the odd rounds (see tile_range)
     alignas(128) uint32_t hist[kMaxTiles], cursor[kMaxTiles];
 };
 struct TileWork {
@@ -242,7 +245,7 @@ struct TileWork {
     unsigned long long* items;      // sorted by tile
     unsigned long long* acc;        // per wide query: six 32-bit limbs of its exact sum, each in a 64-bit word
     QuerySetup* setup;              // per wide query
-    uint32_t segcap, round;         // room of a segment; wide queries per round
+    uint32_t segcap, round;         // room of a segment; most wide queries per round
     int tiles;                      // tiles of the map
 };
 
