@@ -41,7 +41,7 @@ METRIC = "P-NDF queries/sec at 1 MI355X vs footprint size; p99 tile latency (ser
 HBM_PEAK_GBS = 8000.0
 ALU_PEAK_TOPS = 256 * 64 * 2.4e9 / 1e12   # 32-bit lane operations per second, in T
 EVAL_SRC = ("eval.hip", "pndf_internal.h")
-SAMPLE_SRC = ("sample.hip", "pndf_internal.h")
+SAMPLE_SRC = ("sample.hip", "normal_tail.inc", "pndf_internal.h")
 SAMPLE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_sample_powerlaw2048.json")
 WORKCOUNT_SRC = os.path.join(ROOT, "bench_workcount.c")
 WORKCOUNT_LIB = os.path.join(ROOT, "bench_workcount.so")
