@@ -2074,8 +2074,8 @@ static hipError_t tile_round(const HierDev& H, EvalArgs& a, const TileFuncs& f, 
 // batches twice that, so that rounds may be smaller where queries leave many items.
 static int64_t tile_rounds(int64_t nq, int64_t round)
 {
-    const int64_t n = (nq + round - 1) / round;
-    return n <= kTileFewRounds ? n : (nq + round / 2 - 1) / std::max<int64_t>(1, round / 2);
+    const int64_t n = (nq + round - 1) / round, half = std::max<int64_t>(1, round / 2);
+    return n <= kTileFewRounds ? n : (nq + half - 1) / half;
 }
 
 static hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s)

@@ -76,3 +76,25 @@ def test_tiles_rounds_and_overflow(hier, monkeypatch, tau, chunk, count):
     for _ in range(2):
         a = P.eval_batch(hier, tq, tau=tau)
         assert torch.equal(a.view(torch.int32), b.view(torch.int32))
+
+
+# the shortest rounds, with every query wide: none may be left over
+@pytest.mark.parametrize("chunk", [1, 2, 3])
+@pytest.mark.parametrize("plan", [False, True])
+def test_tiles_shortest_rounds(hier, monkeypatch, plan, chunk):
+    import torch
+    import paper_2505_08985_amd as P
+    count = 4096 if not plan else 101
+    tq = torch.from_numpy(queries(1024, count, 19, 130.0, 300.0)).cuda()
+    b = P.eval_batch(hier, tq, tau=1e-2, input_order=True)
+    assert not bool(torch.isnan(b).any())
+    out = torch.full((count,), float("nan"), device="cuda")
+    monkeypatch.setenv("PNDF_LAUNCH_CHUNK", str(chunk))
+    if plan:
+        p = P.Plan(hier, count, tau=1e-2)
+        p.eval(tq, out=out)
+        assert p.stats()["error"] == 0
+        p.close()
+    else:
+        P.eval_batch(hier, tq, tau=1e-2, out=out)
+    assert torch.equal(out.view(torch.int32), b.view(torch.int32))
