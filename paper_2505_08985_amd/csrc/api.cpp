@@ -60,53 +60,6 @@ void blocks_expire(Blocks& b)
 
 }  // namespace
 
-namespace {
-constexpr int kPoolDevices = 64;
-struct Pools {
-    std::mutex mu;
-    hipMemPool_t pool[kPoolDevices] = {};
-    bool refused[kPoolDevices] = {};  // no pools on this device: the default one serves
-};
-Pools& pools()
-{
-    static Pools* p = new Pools;  // (as the runtime may be gone at exit)
-    return *p;
-}
-
-hipMemPool_t pool_of(int dev)
-{
-    if (dev < 0 || dev >= kPoolDevices) return nullptr;
-    Pools& p = pools();
-    std::lock_guard<std::mutex> lock(p.mu);
-    if (p.pool[dev] || p.refused[dev]) return p.pool[dev];
-    hipMemPoolProps props{};
-    props.allocType = hipMemAllocationTypePinned;
-    props.location.type = hipMemLocationTypeDevice;
-    props.location.id = dev;
-    hipMemPool_t made = nullptr;
-    uint64_t keep = kStreamKeep;
-    int wait = 0;
-    if (hipMemPoolCreate(&made, &props) == hipSuccess &&
-        hipMemPoolSetAttribute(made, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess &&
-        hipMemPoolSetAttribute(made, hipMemPoolReuseAllowInternalDependencies, &wait) == hipSuccess) {
-        p.pool[dev] = made;
-        return made;
-    }
-    (void)hipGetLastError();
-    if (made) (void)hipMemPoolDestroy(made);
-    p.refused[dev] = true;
-    return nullptr;
-}
-
-void pool_trim(int dev)
-{
-    if (dev < 0 || dev >= kPoolDevices) return;
-    Pools& p = pools();
-    std::lock_guard<std::mutex> lock(p.mu);
-    if (p.pool[dev] && hipMemPoolTrimTo(p.pool[dev], 0) != hipSuccess) (void)hipGetLastError();
-}
-}  // namespace
-
 hipError_t block_alloc(size_t bytes, void** p)
 {
     *p = nullptr;
@@ -133,25 +86,12 @@ hipError_t block_alloc(size_t bytes, void** p)
     e = hipMalloc(p, bytes);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        pool_trim(dev);
+        if (hipDeviceSynchronize() == hipSuccess) spaces_drop(dev);
         blocks_drop(b, [](const Blocks::Kept&) { return true; });
         e = hipMalloc(p, bytes);
     }
     if (e == hipSuccess) b.used[*p] = {bytes, dev};
     return e;
-}
-
-hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s)
-{
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int dev = 0;
-    if (hipStreamIsCapturing(s, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone &&
-        (s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) == hipSuccess) {
-        const hipMemPool_t pool = pool_of(dev);
-        if (pool && hipMallocFromPoolAsync(p, bytes, pool, s) == hipSuccess) return hipSuccess;
-    }
-    (void)hipGetLastError();
-    return hipMallocAsync(p, bytes, s);
 }
 
 void block_free(void* p)
@@ -170,9 +110,9 @@ void block_free(void* p)
     int cur = 0;
     size_t avail = 0, total = 0;
     bool keep = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess);
-    keep = keep && hipDeviceSynchronize() == hipSuccess && hipMemGetInfo(&avail, &total) == hipSuccess &&
-           size <= total / kBlockKeepShare;
-    if (last) pool_trim(dev);
+    keep = keep && hipDeviceSynchronize() == hipSuccess;
+    if (last && keep) spaces_drop(dev);
+    keep = keep && hipMemGetInfo(&avail, &total) == hipSuccess && size <= total / kBlockKeepShare;
     if (cur != dev) (void)hipSetDevice(cur);
     if (!keep) {
         (void)hipGetLastError();  // (a refused synchronisation is not the caller's error)
@@ -585,19 +525,14 @@ pndf_status pndf_eval_batch(const pndf_hier* h, const pndf_query* d_q, int64_t n
     pndf_status st = eval_common(h, d_q, nq, opts, d_out, &o);
     if (st != PNDF_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    uint32_t* order = nullptr;
-    const uint32_t* narrow = nullptr;
-    TileWork tile{};
+    OrderWork w;
     hipError_t e = hipSuccess;
-    if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER)) {
-        make_tiles(h->dev, nq, &tile, s);
-        e = make_order(h->dev, d_q, nq, o.sigma_to_r, tile, &order, &narrow, s);
-    }
-    EvalArgs a{d_q, order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, narrow, tile};
-    if (!order && o.algo != PNDF_ALGO_BRUTE) a.split = split_waves(nq);
+    if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER))
+        e = make_order(h->dev, d_q, nq, o.sigma_to_r, &w, s);
+    EvalArgs a{d_q, w.order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, w.narrow, w.tile};
+    if (!w.order && o.algo != PNDF_ALGO_BRUTE) a.split = split_waves(nq);
     if (e == hipSuccess) e = launch_eval(h->dev, a, o.algo, s);
-    free_tiles(tile, s);
-    free_order(order, s);
+    stream_free(w.mem, s);
     return e == hipSuccess ? PNDF_OK : hip_fail(e, "pndf_eval_batch");
 }
 

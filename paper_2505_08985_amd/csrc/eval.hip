@@ -1860,23 +1860,27 @@ static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq
     return hipGetLastError();
 }
 
-hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, const TileWork& T, uint32_t** order,
-                      const uint32_t** narrow, hipStream_t s)
+hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, OrderWork* w, hipStream_t s)
 {
-    *order = nullptr;
-    *narrow = nullptr;
+    *w = OrderWork{};
     int nb, bshift;
     order_shape(H.logn, &nb, &bshift);
-    uint32_t* buf = nullptr;  // order[nq] | key[nq] | counters
-    hipError_t e = stream_alloc((void**)&buf, sizeof(uint32_t) * (2 * (size_t)nq + order_words(nb, T.ctl != nullptr)), s);
-    if (e != hipSuccess) return e;
-    e = order_passes(H, q, nq, s2r, T.ctl, buf, narrow, s);
+    // tiles | order[nq] | key[nq] | counters
+    size_t tiles = tiles_bytes(H, nq);
+    auto bytes = [&] { return tiles + sizeof(uint32_t) * (2 * (size_t)nq + order_words(nb, tiles != 0)); };
+    hipError_t e = stream_alloc(&w->mem, bytes(), s);
+    if (e != hipSuccess && tiles) {
+        (void)hipGetLastError();
+        tiles = 0;
+        e = stream_alloc(&w->mem, bytes(), s);
+    }
     if (e != hipSuccess) {
-        (void)hipFreeAsync(buf, s);
+        w->mem = nullptr;
         return e;
     }
-    *order = buf;
-    return hipSuccess;
+    if (tiles) tiles_place(H, nq, w->mem, &w->tile);
+    w->order = reinterpret_cast<uint32_t*>(static_cast<char*>(w->mem) + tiles);
+    return order_passes(H, q, nq, s2r, w->tile.ctl, w->order, &w->narrow, s);
 }
 
 // Workspace of the spatial order for callers that cannot allocate: one array per
@@ -1948,29 +1952,6 @@ size_t tiles_bytes(const HierDev& H, int64_t nq)
 }
 
 void tiles_place(const HierDev& H, int64_t nq, void* base, TileWork* w) { tiles_layout(H, nq, static_cast<char*>(base), w); }
-
-void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s)
-{
-    *w = TileWork{};
-    const size_t bytes = tiles_bytes(H, nq);
-    void* buf = nullptr;
-    if (!bytes) return;
-    if (stream_alloc(&buf, bytes, s) != hipSuccess) {
-        (void)hipGetLastError();
-        return;
-    }
-    tiles_place(H, nq, buf, w);
-}
-
-void free_tiles(const TileWork& w, hipStream_t s)
-{
-    if (w.ctl) (void)hipFreeAsync(w.ctl, s);
-}
-
-void free_order(uint32_t* order, hipStream_t s)
-{
-    if (order) (void)hipFreeAsync(order, s);
-}
 
 static hipError_t launch_tiles(const HierDev& H, EvalArgs a, hipStream_t s);
 

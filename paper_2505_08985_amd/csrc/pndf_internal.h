@@ -401,16 +401,25 @@ constexpr double kBlockKeepSeconds = 10.0;
 hipError_t block_alloc(size_t bytes, void** p);
 void block_free(void* p);
 
-// Workspace of one call, in stream order; given back with hipFreeAsync.  The
-// device's default pool returns its memory to the driver at each synchronisation, and a
-// caller that waits for every batch pays for mapping it anew (a 16384-query tile
-// of the 4096^2 map: 561 us instead of 207, 67 MB each for the tile items and their sorted copy).  Calls therefore
-// draw on a pool of the library's own, which keeps up to kStreamKeep bytes (the largest
-// workspace of a round of tiles is 360 MB) until the last handle on the device is released
-// or a map finds no memory.  It never makes one stream wait for another's release.  Under
-// capture the default pool serves, whose allocations become nodes of the graph.
+// Workspace of one call, in stream order: the call's stream may write it at once, and
+// stream_free gives it back behind what that stream has by then.  The driver's
+// stream-ordered allocation costs a call more than its launches: a hipFreeAsync takes 15
+// to 20 us of the caller's time, and with calls on four streams a 16 MB allocation 150 to
+// 300 us, from the default pool or from one of our own with any of its reuse attributes.
+// So the library keeps the spaces that calls have used, each with an event behind its last
+// call (a record takes 1 us), and a later call has one on the same stream or once that
+// call is over; streams never wait for each other.  Batches of 4608 narrow queries at
+// 2048^2 on four streams: 26 us each, 71 with two allocations from a pool of our own, 36
+// with one from the default pool; 16 served tiles of them: 0.60, 1.65 and 0.75 ms.  At
+// most kStreamKeep bytes per device are kept (the largest workspace, of a round of 2^19
+// wide queries in a batch of 2^24, is 0.5 GB), until the last handle on the device is
+// released or a map finds no memory.  Safe from several threads.  Under capture, and on a
+// stream of another device than the current one, the driver's calls serve (under capture
+// they become nodes of the graph).
 constexpr uint64_t kStreamKeep = (uint64_t)512 << 20;
 hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s);
+void stream_free(void* p, hipStream_t s);
+void spaces_drop(int dev);   // gives the kept ones back whose calls are over
 // Lays arrays out in one allocation (256 B aligned): sizes first, then pointers.
 struct Arena {
     char* base = nullptr;
@@ -471,24 +480,26 @@ hipError_t launch_projected_area(const HierDev& H, const ProjArgs& a, hipStream_
 
 // Spatial processing order of a batch: queries bucketed by the Morton code of their
 // centre cell (64 x 64 buckets over the torus), stream-ordered workspace.
-// With tiles the wide queries come last and *narrow counts the others (device memory
-// of the same allocation), else *narrow is nullptr.
-hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, const TileWork& T, uint32_t** order,
-                      const uint32_t** narrow, hipStream_t s);
+// With tiles the wide queries come last and *narrow counts the others (device memory),
+// else narrow is nullptr.  The order and the tiles' workspace are one allocation, which
+// the caller returns (stream_free(w->mem)); without memory for the tiles w->tile.ctl is nullptr.
+struct OrderWork {
+    void* mem = nullptr;
+    uint32_t* order = nullptr;
+    const uint32_t* narrow = nullptr;
+    TileWork tile{};
+};
+hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, OrderWork* w, hipStream_t s);
 // The same in the library's static per-GPU workspace (no allocation), for batches of
 // at most kStaticOrderQueries queries; the order must not be freed.
 constexpr int64_t kStaticOrderQueries = (int64_t)1 << 22;
 hipError_t make_order_static(const HierDev& H, const pndf_query* q, int64_t nq, uint32_t** order, hipStream_t s);
 // Bucket count and coordinate shift of the spatial order for a map of side 2^logn.
 void order_shape(int logn, int* nb, int* bshift);
-void free_order(uint32_t* order, hipStream_t s);
-// Workspace of the tiled evaluation for batches of nq queries (one allocation,
-// stream-ordered); w->ctl stays nullptr where it does not pay or there is no memory.
-void make_tiles(const HierDev& H, int64_t nq, TileWork* w, hipStream_t s);
-// Size of that workspace (0: no tiles), and its layout at `base`.
+// Size of the tiled evaluation's workspace for batches of nq queries (0: no tiles), and
+// its layout at `base`.
 size_t tiles_bytes(const HierDev& H, int64_t nq);
 void tiles_place(const HierDev& H, int64_t nq, void* base, TileWork* w);
-void free_tiles(const TileWork& w, hipStream_t s);
 
 // ---------------------------------------------------------------- device side
 #if defined(__HIPCC__)

@@ -683,11 +683,12 @@ hipError_t launch_projected_area(const HierDev& H, const ProjArgs& a, hipStream_
         else launch_queries<PNDF_KERNEL_GAUSSIAN>(H, c, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) {
-            if (buf) (void)hipFreeAsync(buf, s);
+            stream_free(buf, s);
             return e;
         }
     }
-    return buf ? hipFreeAsync(buf, s) : hipSuccess;
+    stream_free(buf, s);
+    return hipSuccess;
 }
 
 }  // namespace pndf
