@@ -959,16 +959,28 @@ __global__ __launch_bounds__(256) void k_eval_brute(HierDev H, EvalArgs a)
 
 // ------------------------------------------------------------ hierarchical
 
+// The slot of block b's query.  In a batch with tiles the wide queries are in the last slots and
+// run tiled: the others are spread over the XCDs by themselves (in eighths of all slots
+// the last XCDs had nothing to do: 2^21 queries at 8192^2 93.1 ms, so 88.9).  False when
+// none is left.
+template <int MODE>
+__device__ __forceinline__ bool whole_slot(const EvalArgs& a, int64_t b, int64_t* slot)
+{
+    int64_t slots = a.slots;
+    if (MODE == kModeValue && a.narrow) slots = min(slots, max((int64_t)*a.narrow - a.slot0, (int64_t)0));
+    if (b >= slots) return false;
+    *slot = a.slot0 + xcd_contiguous(b, slots);
+    return true;
+}
+
 // One wavefront per workgroup (a long query holds only its own LDS).  LDS: the node
 // lists of levels 1..L (NodeLists), the hit queue and, with the cut, the cluster queue.
 template <int MODE, bool CUT, int KER>
 __global__ __launch_bounds__(64) void k_eval_plain(HierDev H, EvalArgs a)
 {
     extern __shared__ uint32_t lds[];
-    const int64_t local = xcd_contiguous(blockIdx.x, gridDim.x);
-    if (local >= a.slots) return;
-    const int64_t slot = a.slot0 + local;
-    if (MODE == kModeValue && a.narrow && slot >= (int64_t)*a.narrow) return;  // a wide query (k_tile_emit)
+    int64_t slot;
+    if (!whole_slot<MODE>(a, blockIdx.x, &slot)) return;
     const int64_t qi = a.order ? (int64_t)a.order[slot] : slot;
     uint32_t* lists = lds;
     const QuerySetup q = setup_wave<KER>(a.q[qi], a.s2r, CUT ? a.tau : 0.f, H);
@@ -1203,6 +1215,7 @@ __global__ __launch_bounds__(64) void k_eval_tiles(HierDev H, EvalArgs a)
     const TileWork& T = a.tile;
     const int lane = lane_id();
     const uint32_t total = T.ctl->total;
+    if (total == 0) return;
     TaskQueue none{};
     Rec rec{nullptr, nullptr, 0, 0};
     int x = 0;
@@ -1721,35 +1734,41 @@ __device__ __forceinline__ uint32_t order_bucket(const pndf_query& q, int n, int
     return morton(cx, cy);
 }
 
+// The bucket of a query; with tiles (bins > nb) the wide ones' come last.
+__device__ __forceinline__ uint32_t order_key(const pndf_query& q, const OrderArgs& o)
+{
+    const uint32_t k = order_bucket(q, o.n, o.bshift);
+    if (o.bins > o.nb) {
+        // (a query the evaluation rejects is not wide: k_eval_plain answers it)
+        const QuerySetup u = setup_support(q, o.s2r);
+        if (u.valid && fmaxf(u.rx, u.ry) > (float)(1 << kTileLevel)) return o.nb + (k >> kOrderWideShift);
+    }
+    return k;
+}
+
 // The histogram and the scatter count in LDS first, so the global counters see one
 // atomic per non-empty bin per workgroup instead of one per query; a workgroup takes
 // a strided share of the batch (order_blocks).
-__device__ __forceinline__ void order_hist(const pndf_query* __restrict__ q, int64_t nq, int n, int bshift, int nb, int bins,
-                                           float s2r, float wide, uint32_t* __restrict__ key, uint32_t* __restrict__ hist)
+__device__ __forceinline__ void order_hist(const pndf_query* __restrict__ q, int64_t nq, const OrderArgs& o)
 {
     __shared__ uint32_t loc[kOrderMaxBins];
-    for (int b = threadIdx.x; b < bins; b += blockDim.x) loc[b] = 0u;
+    for (int b = threadIdx.x; b < o.bins; b += blockDim.x) loc[b] = 0u;
     __syncthreads();
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nq;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const pndf_query qr = q[i];
-        uint32_t k = order_bucket(qr, n, bshift);
-        if (bins > nb) {
-            // (a query the evaluation rejects is not wide: k_eval_plain answers it)
-            const QuerySetup u = setup_support(qr, s2r);
-            if (u.valid && fmaxf(u.rx, u.ry) > wide) k = nb + (k >> kOrderWideShift);
-        }
-        key[i] = k;
+        const uint32_t k = order_key(q[i], o);
+        o.key[i] = k;
         atomicAdd(&loc[k], 1u);
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < bins; b += blockDim.x)
-        if (loc[b]) atomicAdd(&hist[b], loc[b]);
+    for (int b = threadIdx.x; b < o.bins; b += blockDim.x)
+        if (loc[b]) atomicAdd(&o.hist[b], loc[b]);
 }
 
-// exclusive scan of `bins` counters into LDS by a workgroup of 1024 threads: each
-// thread's run of counters, the wave's threads by shuffles, the waves' sums from LDS
-__device__ __forceinline__ void order_scan(const uint32_t* __restrict__ hist, int bins, uint32_t* first)
+// exclusive scan of `bins` counters into LDS (in place if they are there) by a workgroup of
+// 1024 threads: each thread's run of counters, the wave's threads by shuffles, the waves'
+// sums from LDS
+__device__ __forceinline__ void order_scan(const uint32_t* hist, int bins, uint32_t* first)
 {
     constexpr int per = (kOrderMaxBins + kOrderThreads - 1) / kOrderThreads;
     __shared__ uint32_t part[kOrderThreads / 64];
@@ -1799,8 +1818,7 @@ __device__ __forceinline__ void order_scatter(const uint32_t* __restrict__ key, 
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_hist(OrderArgs o)
 {
-    const pndf_query* q = o.batch ? o.batch->q : o.q;
-    order_hist(q, o.batch ? o.batch->nq : o.nq, o.n, o.bshift, o.nb, o.bins, o.s2r, o.wide, o.key, o.hist);
+    order_hist(o.batch ? o.batch->q : o.q, o.batch ? o.batch->nq : o.nq, o);
 }
 
 __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(OrderArgs o)
@@ -1809,6 +1827,41 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(OrderArgs o)
     order_scan(o.hist, o.bins, first);
     if (o.narrow && blockIdx.x == 0 && threadIdx.x == 0) *o.narrow = first[o.nb];
     order_scatter(o.key, o.batch ? o.batch->nq : o.nq, o.bins, first, o.hist + o.bins, o.order);
+}
+
+// The whole order of a batch of up to kOrderSmall queries by one workgroup, keys and places
+// within the buckets in registers: such a batch waits for the order as long as for its
+// queries (4096 narrow ones: 15 us in three launches, 8.5 in this one).
+constexpr int kOrderSmallPer = 8;
+constexpr int64_t kOrderSmall = (int64_t)kOrderSmallPer * kOrderThreads;
+__global__ __launch_bounds__(kOrderThreads) void k_order_small(OrderArgs o)
+{
+    __shared__ uint32_t loc[kOrderMaxBins];
+    const pndf_query* q = o.batch ? o.batch->q : o.q;
+    const int nq = (int)(o.batch ? o.batch->nq : o.nq), t = threadIdx.x;
+    for (int b = t; b < o.bins; b += kOrderThreads) loc[b] = 0u;
+    if (o.ctl && !o.batch) {  // (a plan's reset has done it)
+        tile_reset(o.ctl, t);
+        tile_start(o.ctl, t);
+    }
+    __syncthreads();
+    uint32_t key[kOrderSmallPer], at[kOrderSmallPer];
+#pragma unroll
+    for (int k = 0; k < kOrderSmallPer; ++k) {
+        const int i = t + k * kOrderThreads;
+        if (i < nq) key[k] = order_key(q[i], o);
+    }
+#pragma unroll
+    for (int k = 0; k < kOrderSmallPer; ++k)
+        if (t + k * kOrderThreads < nq) at[k] = atomicAdd(&loc[key[k]], 1u);
+    __syncthreads();
+    order_scan(loc, o.bins, loc);
+    if (o.narrow && t == 0) *o.narrow = loc[o.nb];
+#pragma unroll
+    for (int k = 0; k < kOrderSmallPer; ++k) {
+        const int i = t + k * kOrderThreads;
+        if (i < nq) o.order[loc[key[k]] + at[k]] = (uint32_t)i;
+    }
 }
 
 }  // namespace
@@ -1838,7 +1891,6 @@ static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, TileCtl* ct
     o.n = H.n;
     o.bins = order_bins(o.nb, ctl != nullptr);
     o.s2r = s2r;
-    o.wide = (float)(1 << kTileLevel);
     o.order = buf;
     o.key = buf + nq;
     o.hist = o.key + nq;
@@ -1853,6 +1905,10 @@ static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq
     OrderArgs o = order_args(H, nq, s2r, ctl, buf);
     o.q = q;
     if (narrow) *narrow = o.narrow;
+    if (nq <= kOrderSmall) {
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kOrderThreads), 0, s, o);
+        return hipGetLastError();
+    }
     const unsigned g = order_blocks(nq);
     hipLaunchKernelGGL(k_order_zero, dim3(8), dim3(kOrderThreads), 0, s, o);
     hipLaunchKernelGGL(k_order_hist, dim3(g), dim3(kOrderThreads), 0, s, o);
@@ -2150,8 +2206,12 @@ hipError_t persist_graph_build(const HierDev& H, PersistPlan& P)
     P.hargs[0] = &P.oargs;
     if (P.order) {
         const dim3 g(order_blocks(P.max_nq)), b(kOrderThreads);
-        if (e == hipSuccess) e = add((void*)k_order_hist, g, b, 0, P.hargs);
-        if (e == hipSuccess) e = add((void*)k_order_scatter, g, b, 0, P.hargs);
+        if (P.max_nq <= kOrderSmall) {
+            if (e == hipSuccess) e = add((void*)k_order_small, dim3(1), b, 0, P.hargs);
+        } else {
+            if (e == hipSuccess) e = add((void*)k_order_hist, g, b, 0, P.hargs);
+            if (e == hipSuccess) e = add((void*)k_order_scatter, g, b, 0, P.hargs);
+        }
     }
     if (e == hipSuccess) e = chain(work);
     if (e == hipSuccess) e = chain(fin);  // (writes zeros for the wide queries, which the tiles then overwrite)
@@ -2173,7 +2233,9 @@ hipError_t persist_run(PersistPlan& P, const pndf_query* q, long long nq, float*
     }
     hipLaunchKernelGGL(k_persist_reset, P.reset.gridDim, P.reset.blockDim, 0, s, P.ctl, P.acc, P.fexp,
                        q, nq, out, P.epoch, P.ohist, P.order_bins, P.tile.ctl);
-    if (P.order) {
+    if (P.order && P.max_nq <= kOrderSmall) {
+        hipLaunchKernelGGL(k_order_small, dim3(1), dim3(kOrderThreads), 0, s, P.oargs);
+    } else if (P.order) {
         hipLaunchKernelGGL(k_order_hist, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.oargs);
         hipLaunchKernelGGL(k_order_scatter, dim3(order_blocks(P.max_nq)), dim3(kOrderThreads), 0, s, P.oargs);
     }

@@ -290,7 +290,7 @@ struct OrderArgs {
     int64_t nq;
     const QueueCtl* batch;     // a plan's passes: q and nq are read from here
     int n, bshift, nb, bins;   // bins = order_bins()
-    float s2r, wide;
+    float s2r;
     uint32_t* key;
     uint32_t* hist;            // bins counters, then bins cursors
     uint32_t* order;

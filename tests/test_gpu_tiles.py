@@ -98,3 +98,30 @@ def test_tiles_shortest_rounds(hier, monkeypatch, plan, chunk):
     else:
         P.eval_batch(hier, tq, tau=1e-2, out=out)
     assert torch.equal(out.view(torch.int32), b.view(torch.int32))
+
+
+# the sizes up to which one workgroup orders a batch, in calls and in plans, with
+# launches that end among the narrow and among the wide queries
+@pytest.mark.parametrize("count", [4096, 8191, 8192, 8193])
+@pytest.mark.parametrize("chunk", [None, 3000])
+def test_order_sizes(hier, monkeypatch, chunk, count):
+    import torch
+    import paper_2505_08985_amd as P
+    q = queries(1024, count, 23, 0.5, 30.0)
+    q[::3] = queries(1024, len(q[::3]), 25, 90.0, 400.0)
+    q[5, 0] = np.nan
+    tq = torch.from_numpy(q).cuda()
+    b = P.eval_batch(hier, tq, tau=1e-3, input_order=True)
+    if chunk:
+        monkeypatch.setenv("PNDF_LAUNCH_CHUNK", str(chunk))
+    out = torch.full((count,), 7.0, device="cuda")
+    P.eval_batch(hier, tq, tau=1e-3, out=out)
+    assert torch.equal(out.view(torch.int32), b.view(torch.int32))
+    for use_graph in (0, 1):
+        p = P.Plan(hier, count, tau=1e-3, tuning=dict(blocks_per_cu=2, split_level=3, queue_factor=16, use_graph=use_graph))
+        for k in (count, 100, count):
+            out.fill_(7.0)
+            p.eval(tq[:k], out=out[:k])
+            assert p.stats()["error"] == 0
+            assert torch.equal(out[:k].view(torch.int32), b[:k].view(torch.int32))
+        p.close()
