@@ -208,6 +208,7 @@ static void fill_view(pndf_hier* h)
     d.oct_c = h->oct_c;
     d.clu_em = h->clu_em;
     d.tile_e = h->tile_e;
+    d.level_e = h->level_e;
     d.nodes = (uint32_t)h->nodes;
     d.quad = h->quad;
     d.n = m->n;
@@ -387,6 +388,7 @@ pndf_status pndf_build_hierarchy(const pndf_mesh* mesh, const pndf_hier_opts* op
         mem.place(&h->oct_c, 3 * nodes);
         mem.place(&h->clu_em, nodes);
         mem.place(&h->tile_e, 2 * kMaxTiles);
+        mem.place(&h->level_e, kMaxLevels + 1);
     };
     layout();
     hipError_t e = block_alloc(mem.size, &h->mem);
@@ -528,7 +530,7 @@ pndf_status pndf_eval_batch(const pndf_hier* h, const pndf_query* d_q, int64_t n
     OrderWork w;
     hipError_t e = hipSuccess;
     if (nq >= kOrderMin && o.algo != PNDF_ALGO_BRUTE && !(o.flags & PNDF_EVAL_INPUT_ORDER))
-        e = make_order(h->dev, d_q, nq, o.sigma_to_r, &w, s);
+        e = make_order(h->dev, d_q, nq, o.sigma_to_r, o.tau, &w, s);
     EvalArgs a{d_q, w.order, nq, 0, 0, d_out, nullptr, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, w.narrow, w.tile};
     if (!w.order && o.algo != PNDF_ALGO_BRUTE) a.split = split_waves(nq);
     if (e == hipSuccess) e = launch_eval(h->dev, a, o.algo, s);

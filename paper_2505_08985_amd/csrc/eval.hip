@@ -494,11 +494,11 @@ __device__ __forceinline__ int64_t tile_reserve(const TileWork& T, int n)
 // child is no better than the child's own), so the largest one some levels beneath
 // tells whether the descent gets that far.
 template <bool CUT>
-__device__ __forceinline__ bool tile_item(const HierDev& H, const QuerySetup& q, int lev, uint32_t m)
+__device__ __forceinline__ bool tile_item(const HierDev& H, const TileWork& T, const QuerySetup& q, int lev, uint32_t m)
 {
     if (!CUT) return lev == kTileLevel;
     const float2 e = H.tile_e[(uint32_t)(level_offset(H.logn, lev) - level_offset(H.logn, kTileLevel)) + m];
-    return e.x > q.t && (lev == kTileLevel || e.y <= q.t);
+    return e.x > q.t && (lev == kTileLevel || (T.coarse && e.y <= q.t));
 }
 
 // An item's word: the query's place, the node's level less kTileLevel (bits 24..27
@@ -583,7 +583,7 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
         cut = cut && ok;
         const uint32_t entry = root_item | (kids_cut ? kAllCut : 0u);
         if (TILES == kTilesEmit && root_level >= kTileLevel) {
-            const uint64_t be = __ballot(ok && !cut && tile_item<CUT>(H, q, root_level, m));
+            const uint64_t be = __ballot(ok && !cut && tile_item<CUT>(H, T, q, root_level, m));
             const int64_t out = be ? tile_reserve(T, __popcll(be)) : -1;
             if (out >= 0 && ((be >> lane) & 1ull)) {
                 T.raw[out + __popcll(be & ((1ull << lane) - 1ull))] = tile_word(qidx, root_level, entry);
@@ -779,7 +779,7 @@ __device__ void descend(const HierDev& H, const QuerySetup& q, uint32_t* lists, 
             if (TILES == kTilesEmit && l - 1 >= kTileLevel) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    if ((chl & (1u << c)) && tile_item<CUT>(H, q, l - 1, m4 + c)) che |= 1u << c;
+                    if ((chl & (1u << c)) && tile_item<CUT>(H, T, q, l - 1, m4 + c)) che |= 1u << c;
                 chl &= ~che;
             }
             const int below = __builtin_amdgcn_readlane(cntv, l - 1);
@@ -959,17 +959,22 @@ __global__ __launch_bounds__(256) void k_eval_brute(HierDev H, EvalArgs a)
 
 // ------------------------------------------------------------ hierarchical
 
-// The slot of block b's query.  In a batch with tiles the wide queries are in the last slots and
-// run tiled: the others are spread over the XCDs by themselves (in eighths of all slots
-// the last XCDs had nothing to do: 2^21 queries at 8192^2 93.1 ms, so 88.9).  False when
-// none is left.
+// The slot of block b's query.  In a batch with tiles the last slots hold the queries that run
+// tiled: of the others the wide ones come first, then the narrow ones, each spread over
+// the XCDs by themselves (in eighths of all slots the last XCDs had nothing to do: 2^21
+// queries at 8192^2 93.1 ms, so 88.9).  False when none is left.
 template <int MODE>
 __device__ __forceinline__ bool whole_slot(const EvalArgs& a, int64_t b, int64_t* slot)
 {
-    int64_t slots = a.slots;
-    if (MODE == kModeValue && a.narrow) slots = min(slots, max((int64_t)*a.narrow - a.slot0, (int64_t)0));
-    if (b >= slots) return false;
-    *slot = a.slot0 + xcd_contiguous(b, slots);
+    if (MODE != kModeValue || !a.narrow) {
+        *slot = a.slot0 + xcd_contiguous(b, gridDim.x);
+        return *slot < a.slot0 + a.slots;
+    }
+    const int64_t end = a.slot0 + a.slots;
+    const int64_t mid = min(max((int64_t)a.narrow[2], a.slot0), end), last = min(max((int64_t)a.narrow[0], mid), end);
+    const int64_t wide = last - mid;
+    if (b >= last - a.slot0) return false;
+    *slot = b < wide ? mid + xcd_contiguous(b, wide) : a.slot0 + xcd_contiguous(b - wide, mid - a.slot0);
     return true;
 }
 
@@ -1172,11 +1177,13 @@ constexpr uint32_t kWideClaim = 8;
 
 // The wide queries of a round: each leaves its tiles as items and stores its set-up
 // and its sum so far (of what it evaluated above or instead of items).
+// (5 waves per SIMD: 96 vector registers)
 template <bool CUT, int KER>
-__global__ __launch_bounds__(64) void k_tile_emit(HierDev H, EvalArgs a)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_tile_emit(HierDev H, EvalArgs a)
 {
     extern __shared__ uint32_t lds[];
     batch_args(a);
+    a.tile.coarse = a.narrow[1] != 0u;
     const TileWork& T = a.tile;
     const int lane = lane_id();
     const TileRange range = tile_range(a);
@@ -1216,11 +1223,14 @@ __global__ __launch_bounds__(64) void k_eval_tiles(HierDev H, EvalArgs a)
     const int lane = lane_id();
     const uint32_t total = T.ctl->total;
     if (total == 0) return;
+    // (fewer of few items, which are whole nodes or the batch's last work: 8192 queries at 8192^2
+    // 4.1 and 3.5 ms; a quarter as many is too many claims, 5.2 ms for 4.4 at 2048^2)
+    const uint32_t most = max(1u, min(kTileClaim, total / (4u * gridDim.x)));
     TaskQueue none{};
     Rec rec{nullptr, nullptr, 0, 0};
     int x = 0;
     while (true) {
-        const Claim c = claim_run(T.ctl->claim, total, kTileClaim, &x);
+        const Claim c = claim_run(T.ctl->claim, total, most, &x);
         if (c.at >= c.end) break;
         for (uint32_t i = c.at; i < c.end; ++i) {
             const unsigned long long w = uniform_u64(T.items[i]);
@@ -1723,7 +1733,7 @@ __global__ void k_order_zero(OrderArgs o)
     }
 }
 
-constexpr int kOrderMaxBins = (1 << (2 * kOrderBits)) + (1 << (2 * kOrderBits - kOrderWideShift));
+constexpr int kOrderMaxBins = (1 << (2 * kOrderBits)) + 2 * (1 << (2 * kOrderBits - kOrderWideShift));
 constexpr int kOrderThreads = 1024;
 
 __device__ __forceinline__ uint32_t order_bucket(const pndf_query& q, int n, int bshift)
@@ -1734,16 +1744,47 @@ __device__ __forceinline__ uint32_t order_bucket(const pndf_query& q, int n, int
     return morton(cx, cy);
 }
 
-// The bucket of a query; with tiles (bins > nb) the wide ones' come last.
+// Does a wide query take few nodes (see kLightNodes)?  Its descent goes to about the level
+// where half of the nodes are under the cut, between the levels whose means its threshold lies
+// between.
+__device__ __forceinline__ bool is_light(const OrderArgs& o, const QuerySetup& u)
+{
+    if (!(u.t > 0.f)) return false;
+    const float t = log2f(u.t);
+    float below = o.level_e[1], level = 1.f;
+    for (int l = 2; l <= o.logn; ++l) {
+        const float e = o.level_e[l];
+        if (t <= below) break;
+        level = t < e ? (float)(l - 1) + (t - below) / (e - below) : (float)l;
+        below = e;
+    }
+    const float n = (float)o.n;
+    return log2f(fminf(2.f * u.rx, n) * fminf(2.f * u.ry, n)) - 2.f * level <= kLightNodes;
+}
+
+// The bucket of a query; with tiles (bins > nb) the wide ones' come last, the light ones before the others.
 __device__ __forceinline__ uint32_t order_key(const pndf_query& q, const OrderArgs& o)
 {
     const uint32_t k = order_bucket(q, o.n, o.bshift);
     if (o.bins > o.nb) {
         // (a query the evaluation rejects is not wide: k_eval_plain answers it)
-        const QuerySetup u = setup_support(q, o.s2r);
-        if (u.valid && fmaxf(u.rx, u.ry) > (float)(1 << kTileLevel)) return o.nb + (k >> kOrderWideShift);
+        QuerySetup u = setup_support(q, o.s2r);
+        if (u.valid && fmaxf(u.rx, u.ry) > (float)(1 << kTileLevel)) {
+            u.t = o.tau > 0.f ? __fmul_rn(__fmul_rn(u.rx, u.ry), o.tau) : -1.f;
+            return o.nb + (is_light(o, u) ? 0 : o.nb >> kOrderWideShift) + (k >> kOrderWideShift);
+        }
     }
     return k;
+}
+
+// How the wide queries run (one thread); first holds the bins' first places.
+__device__ __forceinline__ void order_narrow(const OrderArgs& o, int64_t nq, const uint32_t* first)
+{
+    const uint32_t narrow = first[o.nb], heavy = first[o.nb + (o.nb >> kOrderWideShift)];
+    const uint32_t tiled = (uint64_t)nq - narrow > (o.logn > 11 ? 2 * kLightMin : kLightMin) ? heavy : narrow;
+    o.narrow[0] = tiled;
+    o.narrow[1] = ((uint64_t)nq - tiled) << (2 * (o.logn - kTileLevel)) > (tiled == narrow ? 4 * kTileFine : kTileFine);
+    o.narrow[2] = narrow;
 }
 
 // The histogram and the scatter count in LDS first, so the global counters see one
@@ -1825,8 +1866,9 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_scatter(OrderArgs o)
 {
     __shared__ uint32_t first[kOrderMaxBins];
     order_scan(o.hist, o.bins, first);
-    if (o.narrow && blockIdx.x == 0 && threadIdx.x == 0) *o.narrow = first[o.nb];
-    order_scatter(o.key, o.batch ? o.batch->nq : o.nq, o.bins, first, o.hist + o.bins, o.order);
+    const int64_t nq = o.batch ? o.batch->nq : o.nq;
+    if (o.narrow && blockIdx.x == 0 && threadIdx.x == 0) order_narrow(o, nq, first);
+    order_scatter(o.key, nq, o.bins, first, o.hist + o.bins, o.order);
 }
 
 // The whole order of a batch of up to kOrderSmall queries by one workgroup, keys and places
@@ -1856,7 +1898,7 @@ __global__ __launch_bounds__(kOrderThreads) void k_order_small(OrderArgs o)
         if (t + k * kOrderThreads < nq) at[k] = atomicAdd(&loc[key[k]], 1u);
     __syncthreads();
     order_scan(loc, o.bins, loc);
-    if (o.narrow && t == 0) *o.narrow = loc[o.nb];
+    if (o.narrow && t == 0) order_narrow(o, nq, loc);
 #pragma unroll
     for (int k = 0; k < kOrderSmallPer; ++k) {
         const int i = t + k * kOrderThreads;
@@ -1882,8 +1924,8 @@ static unsigned order_blocks(int64_t nq)
 }
 
 // The three passes of the spatial order into buf = order[nq] | key[nq] | hist[2 bins] |
-// narrow (the counters are cleared by a kernel, never a memset node).
-static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, TileCtl* ctl, uint32_t* buf)
+// narrow[3] (the counters are cleared by a kernel, never a memset node).
+static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, float tau, TileCtl* ctl, uint32_t* buf)
 {
     OrderArgs o{};
     order_shape(H.logn, &o.nb, &o.bshift);
@@ -1891,6 +1933,9 @@ static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, TileCtl* ct
     o.n = H.n;
     o.bins = order_bins(o.nb, ctl != nullptr);
     o.s2r = s2r;
+    o.tau = tau;
+    o.logn = H.logn;
+    o.level_e = H.level_e;
     o.order = buf;
     o.key = buf + nq;
     o.hist = o.key + nq;
@@ -1899,10 +1944,10 @@ static OrderArgs order_args(const HierDev& H, int64_t nq, float s2r, TileCtl* ct
     return o;
 }
 
-static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, TileCtl* ctl, uint32_t* buf,
+static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, float tau, TileCtl* ctl, uint32_t* buf,
                                const uint32_t** narrow, hipStream_t s)
 {
-    OrderArgs o = order_args(H, nq, s2r, ctl, buf);
+    OrderArgs o = order_args(H, nq, s2r, tau, ctl, buf);
     o.q = q;
     if (narrow) *narrow = o.narrow;
     if (nq <= kOrderSmall) {
@@ -1916,7 +1961,7 @@ static hipError_t order_passes(const HierDev& H, const pndf_query* q, int64_t nq
     return hipGetLastError();
 }
 
-hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, OrderWork* w, hipStream_t s)
+hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, float tau, OrderWork* w, hipStream_t s)
 {
     *w = OrderWork{};
     int nb, bshift;
@@ -1936,7 +1981,7 @@ hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s
     }
     if (tiles) tiles_place(H, nq, w->mem, &w->tile);
     w->order = reinterpret_cast<uint32_t*>(static_cast<char*>(w->mem) + tiles);
-    return order_passes(H, q, nq, s2r, w->tile.ctl, w->order, &w->narrow, s);
+    return order_passes(H, q, nq, s2r, tau, w->tile.ctl, w->order, &w->narrow, s);
 }
 
 // Workspace of the spatial order for callers that cannot allocate: one array per
@@ -1975,7 +2020,7 @@ hipError_t make_order_static(const HierDev& H, const pndf_query* q, int64_t nq, 
     int nb, bshift;
     order_shape(H.logn, &nb, &bshift);
     if (nb > 4096) return hipErrorInvalidValue;
-    e = order_passes(H, q, nq, 0.f, nullptr, buf, nullptr, s);
+    e = order_passes(H, q, nq, 0.f, 0.f, nullptr, buf, nullptr, s);
     if (e == hipSuccess) *order = buf;
     return e;
 }
@@ -2147,7 +2192,7 @@ void persist_prepare(const HierDev& H, PersistPlan& P)
     P.pa.narrow = nullptr;
     P.targs.clear();
     if (!P.order) return;
-    P.oargs = order_args(H, P.max_nq, P.s2r, P.tile.ctl, P.order);
+    P.oargs = order_args(H, P.max_nq, P.s2r, P.tau, P.tile.ctl, P.order);
     P.oargs.batch = P.ctl;
     P.ohist = P.oargs.hist;
     P.order_bins = P.oargs.bins;

@@ -763,6 +763,32 @@ __global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, float2* __res
     }
 }
 
+// A middle value of the residuals of level blockIdx.x + 1 (HierDev::level_e): halfway
+// between the mean of their logarithms and the logarithm of their mean, as few large ones
+// (scratches) make many nodes above them; over at most 4096 nodes at even steps.
+__global__ __launch_bounds__(256) void k_level_means(HierDev H, float* __restrict__ le)
+{
+    __shared__ float red[2][256];
+    const int level = (int)blockIdx.x + 1, nodes = 1 << (2 * (H.logn - level)), count = min(nodes, 4096), t = (int)threadIdx.x;
+    const float* e = H.clu_e + level_offset(H.logn, level);
+    float v = 0.f, m = 0.f;
+    for (int i = t; i < count; i += 256) {
+        const float x = fmaxf(e[(int64_t)i * (nodes / count)], 1e-30f);
+        v += log2f(x);
+        m += x;
+    }
+    red[0][t] = v;
+    red[1][t] = m;
+    for (int o = 128; o > 0; o >>= 1) {
+        __syncthreads();
+        if (t < o) {
+            red[0][t] += red[0][t + o];
+            red[1][t] += red[1][t + o];
+        }
+    }
+    if (t == 0) le[level] = 0.5f * (red[0][0] / (float)count + log2f(red[1][0] / (float)count));
+}
+
 hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
 {
     const HierDev& H = h->dev;
@@ -809,6 +835,7 @@ hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
             const unsigned parts = std::max(1u, (1u << (2 * kTileSpan)) / kTilePart);
             hipLaunchKernelGGL(k_tile_residuals, dim3((unsigned)(h->nodes - level_offset(H.logn, kTileLevel)), parts), dim3(256),
                                0, s, H, h->tile_e);
+            hipLaunchKernelGGL(k_level_means, dim3((unsigned)H.L), dim3(256), 0, s, H, h->level_e);
         }
     }
     err = hipGetLastError();

@@ -109,6 +109,7 @@ struct HierDev {
     const float* clu_e;     // e^l per node
     const float2* tile_e;   // maps with tiles: per node of level kTileLevel and above (packed like the others, from
                             // level kTileLevel on) the largest e^l kTileDepth and kTileSpan levels beneath
+    const float* level_e;   // with tiles, per level from 1: logarithm (base 2) of a middle residual
     const float2* clu_det;  // cluster triangle Jacobians (lower, upper), eps when clamped
     const QuadRec* quad;    // level-1 leaf records (Morton order)
     uint32_t nodes;         // nodes of all levels
@@ -221,8 +222,16 @@ struct QuerySetup;
 // level 8 otherwise): 2^21 queries at 8192^2, tau = 1e-3: 130, 98, 94, 106 ms (97
 // untiled); 60001 queries of sigma 4 to 1024 on the 4096^2 scratched map, tau = 1e-4:
 // 158 -> 47 ms at any span, L2 misses 7.7e9 -> 4e7, the vector ALU then always busy.
+//
+// A batch of few wide queries has every item one tile: a whole node's item is one wave's work
+// and decides when the batch ends.  Wide queries x tiles up to 4 kTileFine (tau = 1e-3, sigma 90
+// to an eighth of the map, with items of whole nodes and with tiles alone): 8192 queries at
+// 2048^2 2276 and 1533 us; 128 at 8192^2 1714 and 456 us, 8192 3.7 and 4.0 ms, 16384 5.5 and
+// 7.1.  Without the light queries (see OrderArgs), which are most of those that whole nodes make
+// long, up to kTileFine: 15000 others at 4096^2 9.6 and 12.5 ms.
 constexpr int kTileLevel = 8;
 constexpr int kTileDepth = 3, kTileSpan = 9;
+constexpr uint64_t kTileFine = (uint64_t)1 << 20;
 constexpr int kTileSegs = 64;                        // item segments, each with a counter of its own
 constexpr int kMaxTiles = 1 << (2 * (13 - kTileLevel));
 constexpr int64_t kTileChunk = (int64_t)1 << 19;     // most wide queries per round
@@ -247,6 +256,7 @@ struct TileWork {
     QuerySetup* setup;              // per wide query
     uint32_t segcap, round;         // room of a segment; most wide queries per round
     int tiles;                      // tiles of the map
+    bool coarse;                    // nodes above the tile level become items (set by k_tile_emit)
 };
 
 struct EvalArgs {
@@ -262,7 +272,7 @@ struct EvalArgs {
     float tau;
     float s2r;
     int kernel;                // PNDF_KERNEL_*
-    const uint32_t* narrow;    // with tiles: slots from *narrow on hold the wide queries
+    const uint32_t* narrow;    // with tiles: slots from *narrow on hold the queries that run tiled (see OrderArgs)
     TileWork tile;
     int split = 0;                    // wavefronts per query of a small batch (4 or 16; 0: one)
     const QueueCtl* batch = nullptr;  // a plan's tile kernels: the batch (q, nq, out) is read from here
@@ -284,22 +294,37 @@ struct PersistArgs {
 // and its items are sorted by tile).  As many as the others have made the passes
 // longer (a 16384-query tile 188 us, with a scan by barriers instead of shuffles; now 180) and
 // gained nothing (60001 wide queries 46.8 and 46.9 ms).
+//
+// Wide queries that the cut leaves few nodes lose by tiles, whose items cost more than such
+// a query's cache misses.  The nodes that a query visits (counted on power-law and scratched
+// maps of 1024^2 to 8192^2, tau 1e-4 to 1e-2) are 0.8 to 1.6 times the area of its
+// support in nodes of the level at which half of the nodes are under the cut (2 to 3 times on
+// the scratched ones); up to 2^kLightNodes of them a wide query is light.  In batches of more
+// than kLightMin wide queries (twice that above 2048^2) the light ones are evaluated whole;
+// fewer leave the GPU idle that way.  tau = 1e-3, power law, sigma 1 to the map's side, with
+// all of the wide ones tiled, with this rule, and before there were tiles: 131072 queries at
+// 2048^2 9.4, 5.7 and 7.9 ms, at 1024^2 5.7, 3.1 and 4.9; 2^21 at 8192^2 88.9, 78.0 and
+// 107.5.  A limit of 2^14.6 takes 12 % longer at 2048^2, one of 2^15.4 15 % at 8192^2.
 constexpr int kOrderWideShift = 6;
+constexpr float kLightNodes = 15.f;
+constexpr uint64_t kLightMin = 8192;
 struct OrderArgs {
     const pndf_query* q;
     int64_t nq;
     const QueueCtl* batch;     // a plan's passes: q and nq are read from here
     int n, bshift, nb, bins;   // bins = order_bins()
-    float s2r;
+    float s2r, tau;
+    int logn;
+    const float* level_e;
     uint32_t* key;
     uint32_t* hist;            // bins counters, then bins cursors
     uint32_t* order;
-    uint32_t* narrow;          // number of queries that are not wide (nullptr without tiles)
+    uint32_t* narrow;          // with tiles: the first slot that runs tiled, whether items may be whole nodes, narrow queries
     TileCtl* ctl;
 };
-// 32-bit words of the order's counters (the passes' histogram, cursors and *narrow).
-inline int order_bins(int nb, bool tiles) { return tiles ? nb + (nb >> kOrderWideShift) : nb; }
-inline size_t order_words(int nb, bool tiles) { return 2 * (size_t)order_bins(nb, tiles) + 1; }
+// 32-bit words of the order's counters (the passes' histogram, cursors and narrow).
+inline int order_bins(int nb, bool tiles) { return tiles ? nb + 2 * (nb >> kOrderWideShift) : nb; }
+inline size_t order_words(int nb, bool tiles) { return 2 * (size_t)order_bins(nb, tiles) + 3; }
 
 // Device resources and the instantiated launch graph of a persistent plan.
 struct PersistPlan {
@@ -373,6 +398,7 @@ struct pndf_hier {
     uint4* oct_c = nullptr;       // 3 x nodes (kOctSub, kOctOwn, kOctKids)
     float2* clu_em = nullptr;
     float2* tile_e = nullptr;
+    float* level_e = nullptr;
     float4* bbox_clu = nullptr;   // box of the node's own cluster triangles (float32)
     float4* clu_n = nullptr;      // the fitted normals as float32 (exported; the kernels read clu_t)
     float4* clu_t = nullptr;
@@ -489,7 +515,7 @@ struct OrderWork {
     const uint32_t* narrow = nullptr;
     TileWork tile{};
 };
-hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, OrderWork* w, hipStream_t s);
+hipError_t make_order(const HierDev& H, const pndf_query* q, int64_t nq, float s2r, float tau, OrderWork* w, hipStream_t s);
 // The same in the library's static per-GPU workspace (no allocation), for batches of
 // at most kStaticOrderQueries queries; the order must not be freed.
 constexpr int64_t kStaticOrderQueries = (int64_t)1 << 22;
