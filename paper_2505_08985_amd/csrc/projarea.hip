@@ -434,7 +434,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3, 8))) 
             const int j = spany >= n ? cb : ((q.cylo + cb) & msk);
             cell = (uint32_t)i | ((uint32_t)j << 13);
             const float2 dd = H.det[(int64_t)j * n + i];
-            const uint8_t deg = H.deg[(int64_t)j * n + i];
+            const uint32_t deg = H.deg[(int64_t)j * n + i] & 3u;
             // kernel at the uv centroid over the included images, divided by J
             double kh[2];
             if (table) {
@@ -447,58 +447,72 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(3, 8))) 
                 kh[0] = hit_term<KER>(q, i, j, 0, 0, 1.0 / 3.0, 1.0 / 3.0, dd.x, H.logn);
                 kh[1] = hit_term<KER>(q, i, j, 0, 1, 1.0 / 3.0, 1.0 / 3.0, dd.y, H.logn);
             }
-            if ((deg & 3u) == 0u) {
-                // both halves regular: lower (n0, n1, n2) and upper (n3, n2, n1) share the
-                // diagonal n1 -> n2, which the upper runs backwards.  The corners are rotated
-                // once; a triangle's CCW boundary integral is its orientation sign times
-                // the integral in vertex order, so with both triangles inside V the
-                // diagonal's term is computed once with weight s_l k_l - s_u k_u.
-                const int wdt = n + 1;
-                const float2* p = H.nrm + (int64_t)j * wdt + i;
-                const float2 nn[4] = {p[0], p[1], p[wdt], p[wdt + 1]};
-                double x[4], y[4], mz[4];
-                bool vis[4], left[4];
+            // lower (n0, n1, n2) and upper (n3, n2, n1) share the diagonal n1 -> n2, which the
+            // upper runs backwards.  The corners are rotated once; a triangle's CCW boundary
+            // integral is its orientation sign times the integral in vertex order, so with
+            // both triangles inside V the diagonal's term is computed once with weight
+            // s_l k_l - s_u k_u.  Both halves of a cell have the same replacement triangle: where
+            // both are clamped it takes the lower one's place with both weights (1024^2,
+            // patches of 16 x 16, 65536 queries of sigma 1 to 4: 375 us, 1271 when they were clipped); a
+            // clamped half beside a regular one is left to clip_round.
+            const int wdt = n + 1;
+            const float2* p = H.nrm + (int64_t)j * wdt + i;
+            const float2 nn[4] = {p[0], p[1], p[wdt], p[wdt + 1]};
+            double x[4], y[4], mz[4];
+            bool vis[4], left[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    x[k] = c * (double)nn[k].x + sn * (double)nn[k].y;
-                    y[k] = -sn * (double)nn[k].x + c * (double)nn[k].y;
-                    const double r2 = x[k] * x[k] + y[k] * y[k];
-                    vis[k] = visible(x[k], y[k], wz);
-                    left[k] = x[k] < -wz;
-                    mz[k] = sqrt_unit(fmax(0.0, 1.0 - r2));
-                }
-                const double sl = (x[1] - x[0]) * (y[2] - y[0]) - (y[1] - y[0]) * (x[2] - x[0]) < 0.0 ? -1.0 : 1.0;
-                const double su = (x[2] - x[3]) * (y[1] - y[3]) - (y[2] - y[3]) * (x[1] - x[3]) < 0.0 ? -1.0 : 1.0;
-                const bool lo_live = kh[0] != 0.0 && !(left[0] && left[1] && left[2]);
-                const bool up_live = kh[1] != 0.0 && !(left[3] && left[2] && left[1]);
-                const bool lo_full = lo_live && vis[0] && vis[1] && vis[2];
-                const bool up_full = up_live && vis[3] && vis[2] && vis[1];
-                bool lo_ok = lo_full, up_ok = up_full;
-                if (lo_full || up_full) {
-                    // edges 0 -> 1, 2 -> 0 (lower), 3 -> 2, 1 -> 3 (upper), 1 -> 2 (both)
-                    constexpr int from[5] = {0, 2, 3, 1, 1}, to[5] = {1, 0, 2, 3, 2};
-                    double v[5];
-                    bool ok[5];
-#pragma unroll
-                    for (int e = 0; e < 5; ++e) {
-                        const int f = from[e], t = to[e];
-                        v[e] = segment_short(x[f], y[f], mz[f], x[t], y[t], mz[t], wl, wz, &ok[e]);
-                    }
-                    lo_ok = lo_full && ok[0] && ok[1] && ok[4];
-                    up_ok = up_full && ok[2] && ok[3] && ok[4];
-                    if (lo_ok) acc += kh[0] * sl * (v[0] + v[4] + v[1]);
-                    if (up_ok) acc += kh[1] * su * (v[2] - v[4] + v[3]);
-                }
-                clip = (lo_live && !lo_full ? 1u : 0u) | (up_live && !up_full ? 2u : 0u);
-                far = (lo_full && !lo_ok ? 1u : 0u) | (up_full && !up_ok ? 2u : 0u);
-                kw[0] = kh[0];
-                kw[1] = kh[1];
-            } else {
-                // a clamped half: its replacement triangle
-                clip = (kh[0] != 0.0 ? 1u : 0u) | (kh[1] != 0.0 ? 2u : 0u);
-                kw[0] = kh[0];
-                kw[1] = kh[1];
+            for (int k = 0; k < 4; ++k) {
+                x[k] = (double)nn[k].x;
+                y[k] = (double)nn[k].y;
             }
+            if (deg == 3u) {
+                double v[6];
+                eqtri_f64(0.5 * (x[1] + x[2]), 0.5 * (y[1] + y[2]), (double)H.rho, v);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    x[k] = v[2 * k];
+                    y[k] = v[2 * k + 1];
+                }
+                kh[0] += kh[1];
+                kh[1] = 0.0;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double u = x[k], w = y[k];
+                x[k] = c * u + sn * w;
+                y[k] = -sn * u + c * w;
+                const double r2 = x[k] * x[k] + y[k] * y[k];
+                vis[k] = visible(x[k], y[k], wz);
+                left[k] = x[k] < -wz;
+                mz[k] = sqrt_unit(fmax(0.0, 1.0 - r2));
+            }
+            const double sl = (x[1] - x[0]) * (y[2] - y[0]) - (y[1] - y[0]) * (x[2] - x[0]) < 0.0 ? -1.0 : 1.0;
+            const double su = (x[2] - x[3]) * (y[1] - y[3]) - (y[2] - y[3]) * (x[1] - x[3]) < 0.0 ? -1.0 : 1.0;
+            const bool lo_live = deg != 1u && kh[0] != 0.0 && !(left[0] && left[1] && left[2]);
+            const bool up_live = deg != 2u && kh[1] != 0.0 && !(left[3] && left[2] && left[1]);
+            const bool lo_full = lo_live && vis[0] && vis[1] && vis[2];
+            const bool up_full = up_live && vis[3] && vis[2] && vis[1];
+            bool lo_ok = lo_full, up_ok = up_full;
+            if (lo_full || up_full) {
+                // edges 0 -> 1, 2 -> 0 (lower), 3 -> 2, 1 -> 3 (upper), 1 -> 2 (both)
+                constexpr int from[5] = {0, 2, 3, 1, 1}, to[5] = {1, 0, 2, 3, 2};
+                double v[5];
+                bool ok[5];
+#pragma unroll
+                for (int e = 0; e < 5; ++e) {
+                    const int f = from[e], t = to[e];
+                    v[e] = segment_short(x[f], y[f], mz[f], x[t], y[t], mz[t], wl, wz, &ok[e]);
+                }
+                lo_ok = lo_full && ok[0] && ok[1] && ok[4];
+                up_ok = up_full && ok[2] && ok[3] && ok[4];
+                if (lo_ok) acc += kh[0] * sl * (v[0] + v[4] + v[1]);
+                if (up_ok) acc += kh[1] * su * (v[2] - v[4] + v[3]);
+            }
+            clip = (lo_live && !lo_full ? 1u : 0u) | (up_live && !up_full ? 2u : 0u);
+            if (deg == 1u || deg == 2u) clip |= (deg == 1u ? kh[0] : kh[1]) != 0.0 ? deg : 0u;
+            far = (lo_full && !lo_ok ? 1u : 0u) | (up_full && !up_ok ? 2u : 0u);
+            kw[0] = kh[0];
+            kw[1] = kh[1];
         }
         ca += da;
         cb += db;

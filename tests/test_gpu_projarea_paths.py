@@ -54,3 +54,51 @@ def test_axis_table_limit(P, oracle_mod, kernel, sigma):
     q[20:, 2] *= 2.0
     q[20:, 3] *= np.array([0.2, 0.3, 0.4, 0.5], np.float32)
     check(P, oracle_mod, nrm, q, kernel, np.arange(24))
+
+
+def patched(kind, n=64, seed=5):
+    """Maps of clamped cells: constant; constant patches; single triangles clamped beside
+    regular ones (three of a cell's corners on a line)."""
+    rng = np.random.default_rng(seed)
+    if kind == "constant":
+        return np.full((n, n, 2), (0.3, -0.2), np.float32)
+    if kind == "patches":
+        r = rng.uniform(-0.6, 0.6, (n // 4, n // 4, 2)).astype(np.float32)
+        return np.repeat(np.repeat(r, 4, 0), 4, 1)
+    nrm = rng.uniform(-0.6, 0.6, (n, n, 2)).astype(np.float32)
+    nrm[::3, 1::3] = nrm[::3, ::3][:, :nrm[::3, 1::3].shape[1]]
+    nrm[2::4, 2::4] = 0.97 * nrm[2::4, 2::4] / np.linalg.norm(nrm[2::4, 2::4], axis=-1, keepdims=True)
+    return nrm
+
+
+@pytest.mark.parametrize("nq", [300, 3000, 6000])
+@pytest.mark.parametrize("kind", ["constant", "patches", "single"])
+def test_clamped_cells(P, oracle_mod, kind, nq):
+    announce("projected area, clamped cells: %s, %d queries" % (kind, nq))
+    q = queries(64, nq, 90 + nq, 0.3, 4.0)
+    check(P, oracle_mod, patched(kind), q, "gaussian", np.arange(0, nq, max(1, nq // 200)))
+
+
+def test_clamped_cells_are_not_slower(P):
+    """A constant map, whose cells are all clamped, takes no longer than a power-law map (0.7 of
+    the time; when all of its triangles were clipped, 2.4 times)."""
+    import time
+    import torch
+    import workloads
+    q = to_dev(queries(512, 65536, 97, 1.0, 4.0))
+
+    def best(nrm):
+        _, h = build(P, nrm)
+        t = []
+        for _ in range(8):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            for _ in range(4):
+                P.projected_area(h, q)
+            torch.cuda.synchronize()
+            t.append(time.perf_counter() - a)
+        return min(t) / 4
+
+    flat, rough = best(patched("constant", 512)), best(workloads.make_map("powerlaw", 512, 7))
+    print("constant %.0f us, power law %.0f us" % (flat * 1e6, rough * 1e6))
+    assert flat < rough
