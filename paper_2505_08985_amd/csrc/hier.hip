@@ -735,14 +735,47 @@ __global__ void k_residual_pairs(HierDev H, float2* __restrict__ em, float2* __r
     em[idx] = make_float2(H.clu_e[idx], kids);
 }
 
+// A middle value of a level's residuals (HierDev::level_e): halfway between the mean of
+// their logarithms and the logarithm of their mean, as few large ones (scratches) make
+// many nodes above them; over at most 1024 nodes at even steps.
+__device__ __forceinline__ void level_mean(const HierDev& H, int level, float (*red)[256], float* __restrict__ le)
+{
+    const int nodes = 1 << (2 * (H.logn - level)), count = min(nodes, 1024), t = (int)threadIdx.x;
+    const float* e = H.clu_e + level_offset(H.logn, level);
+    float v = 0.f, m = 0.f;
+#pragma unroll 4
+    for (int i = t; i < count; i += 256) {
+        const float x = fmaxf(e[(int64_t)i * (nodes / count)], 1e-30f);
+        v += log2f(x);
+        m += x;
+    }
+    red[0][t] = v;
+    red[1][t] = m;
+    for (int o = 128; o > 0; o >>= 1) {
+        __syncthreads();
+        if (t < o) {
+            red[0][t] += red[0][t + o];
+            red[1][t] += red[1][t + o];
+        }
+    }
+    if (t == 0) le[level] = 0.5f * (red[0][0] / (float)count + log2f(red[1][0] / (float)count));
+}
+
 // Largest residuals kTileDepth and kTileSpan levels beneath each node of the levels
 // from kTileLevel up (HierDev::tile_e, cleared before): one workgroup per node and
 // part of kTilePart values (the top nodes look over 4^9), the parts' maxima by atomic
-// maximum (the values are not negative, so their bits compare like them).
+// maximum (the values are not negative, so their bits compare like them).  The workgroups
+// past the nodes take a level's middle residual each.
 constexpr int kTilePart = 16384;
-__global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, float2* __restrict__ te)
+__global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, float2* __restrict__ te, float* __restrict__ le)
 {
-    __shared__ float red[256];
+    __shared__ float both[2][256];
+    float* const red = both[0];
+    const int tiles = (int)(H.nodes - level_offset(H.logn, kTileLevel));
+    if ((int)blockIdx.x >= tiles) {
+        if (blockIdx.y == 0) level_mean(H, (int)blockIdx.x - tiles + 1, both, le);
+        return;
+    }
     int64_t t;
     const int level = packed_level(H, kTileLevel, blockIdx.x, &t);
     for (int k = 0; k < 2; ++k) {
@@ -761,32 +794,6 @@ __global__ __launch_bounds__(256) void k_tile_residuals(HierDev H, float2* __res
         if (threadIdx.x == 0) atomicMax(reinterpret_cast<unsigned*>(te) + 2 * blockIdx.x + k, __float_as_uint(red[0]));
         __syncthreads();
     }
-}
-
-// A middle value of the residuals of level blockIdx.x + 1 (HierDev::level_e): halfway
-// between the mean of their logarithms and the logarithm of their mean, as few large ones
-// (scratches) make many nodes above them; over at most 4096 nodes at even steps.
-__global__ __launch_bounds__(256) void k_level_means(HierDev H, float* __restrict__ le)
-{
-    __shared__ float red[2][256];
-    const int level = (int)blockIdx.x + 1, nodes = 1 << (2 * (H.logn - level)), count = min(nodes, 4096), t = (int)threadIdx.x;
-    const float* e = H.clu_e + level_offset(H.logn, level);
-    float v = 0.f, m = 0.f;
-    for (int i = t; i < count; i += 256) {
-        const float x = fmaxf(e[(int64_t)i * (nodes / count)], 1e-30f);
-        v += log2f(x);
-        m += x;
-    }
-    red[0][t] = v;
-    red[1][t] = m;
-    for (int o = 128; o > 0; o >>= 1) {
-        __syncthreads();
-        if (t < o) {
-            red[0][t] += red[0][t + o];
-            red[1][t] += red[1][t + o];
-        }
-    }
-    if (t == 0) le[level] = 0.5f * (red[0][0] / (float)count + log2f(red[1][0] / (float)count));
 }
 
 hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
@@ -833,9 +840,8 @@ hipError_t build_hierarchy_levels(pndf_hier* h, hipStream_t s)
                            h->tile_e);
         if (has_tiles(H.logn)) {
             const unsigned parts = std::max(1u, (1u << (2 * kTileSpan)) / kTilePart);
-            hipLaunchKernelGGL(k_tile_residuals, dim3((unsigned)(h->nodes - level_offset(H.logn, kTileLevel)), parts), dim3(256),
-                               0, s, H, h->tile_e);
-            hipLaunchKernelGGL(k_level_means, dim3((unsigned)H.L), dim3(256), 0, s, H, h->level_e);
+            hipLaunchKernelGGL(k_tile_residuals, dim3((unsigned)(h->nodes - level_offset(H.logn, kTileLevel) + H.L), parts),
+                               dim3(256), 0, s, H, h->tile_e, h->level_e);
         }
     }
     err = hipGetLastError();
