@@ -7,128 +7,9 @@
 #include <string>
 #include <vector>
 
-#include <chrono>
-#include <map>
-#include <mutex>
-
 #include "pndf_internal.h"
 
 namespace pndf {
-
-namespace {
-
-struct Blocks {
-    struct Kept {
-        void* p;
-        size_t size;
-        int dev;
-        std::chrono::steady_clock::time_point since;
-    };
-    std::mutex mu;
-    std::vector<Kept> kept;                            // oldest first
-    std::map<void*, std::pair<size_t, int>> used;      // size and device of every block handed out
-};
-
-// (never destroyed: handles may outlive the library's static objects)
-Blocks& blocks()
-{
-    static Blocks* b = new Blocks;
-    return *b;
-}
-
-// Give back the kept blocks that match; called with the lock held.
-template <typename Pred>
-void blocks_drop(Blocks& b, Pred match)
-{
-    size_t out = 0;
-    for (size_t i = 0; i < b.kept.size(); ++i) {
-        if (match(b.kept[i]))
-            (void)hipFree(b.kept[i].p);
-        else
-            b.kept[out++] = b.kept[i];
-    }
-    b.kept.resize(out);
-}
-
-void blocks_expire(Blocks& b)
-{
-    const auto now = std::chrono::steady_clock::now();
-    blocks_drop(b, [&](const Blocks::Kept& k) {
-        return std::chrono::duration<double>(now - k.since).count() > kBlockKeepSeconds;
-    });
-}
-
-}  // namespace
-
-hipError_t block_alloc(size_t bytes, void** p)
-{
-    *p = nullptr;
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    Blocks& b = blocks();
-    std::lock_guard<std::mutex> lock(b.mu);
-    blocks_expire(b);
-    // the smallest kept block that holds it without wasting more than an eighth
-    size_t best = b.kept.size();
-    for (size_t i = 0; i < b.kept.size(); ++i) {
-        const Blocks::Kept& k = b.kept[i];
-        if (k.dev == dev && k.size >= bytes && k.size <= bytes + bytes / 8 &&
-            (best == b.kept.size() || k.size < b.kept[best].size))
-            best = i;
-    }
-    if (best < b.kept.size()) {
-        *p = b.kept[best].p;
-        b.used[*p] = {b.kept[best].size, dev};
-        b.kept.erase(b.kept.begin() + (long)best);
-        return hipSuccess;
-    }
-    e = hipMalloc(p, bytes);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        if (hipDeviceSynchronize() == hipSuccess) spaces_drop(dev);
-        blocks_drop(b, [](const Blocks::Kept&) { return true; });
-        e = hipMalloc(p, bytes);
-    }
-    if (e == hipSuccess) b.used[*p] = {bytes, dev};
-    return e;
-}
-
-void block_free(void* p)
-{
-    if (!p) return;
-    Blocks& b = blocks();
-    std::lock_guard<std::mutex> lock(b.mu);
-    const auto it = b.used.find(p);
-    if (it == b.used.end()) return;
-    const size_t size = it->second.first;
-    const int dev = it->second.second;
-    b.used.erase(it);
-    blocks_expire(b);
-    bool last = true;
-    for (const auto& u : b.used) last = last && u.second.second != dev;
-    int cur = 0;
-    size_t avail = 0, total = 0;
-    bool keep = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess);
-    keep = keep && hipDeviceSynchronize() == hipSuccess;
-    if (last && keep) spaces_drop(dev);
-    keep = keep && hipMemGetInfo(&avail, &total) == hipSuccess && size <= total / kBlockKeepShare;
-    if (cur != dev) (void)hipSetDevice(cur);
-    if (!keep) {
-        (void)hipGetLastError();  // (a refused synchronisation is not the caller's error)
-        (void)hipFree(p);
-        return;
-    }
-    // the oldest ones make room
-    size_t held = size;
-    for (const Blocks::Kept& k : b.kept) held += k.dev == dev ? k.size : 0;
-    blocks_drop(b, [&](const Blocks::Kept& k) {
-        if (k.dev != dev || held <= total / kBlockKeepShare) return false;
-        held -= k.size;
-        return true;
-    });
-    b.kept.push_back({p, size, dev, std::chrono::steady_clock::now()});
-}
 
 static thread_local std::string g_last_error;
 
@@ -584,7 +465,7 @@ pndf_status pndf_eval_hits(const pndf_hier* h, const pndf_query* d_q, int64_t nq
     hipStream_t s = (hipStream_t)stream;
     if (nq == 0) return PNDF_OK;
     uint32_t* d_counts = nullptr;
-    hipError_t e = hipMalloc(&d_counts, sizeof(uint32_t) * 4 * (size_t)nq);
+    hipError_t e = device_alloc((void**)&d_counts, sizeof(uint32_t) * 4 * (size_t)nq);
     if (e != hipSuccess) return hip_fail(e, "pndf_eval_hits");
     EvalArgs a{d_q, nullptr, nq, 0, 0, d_out, d_counts, nullptr, nullptr, nullptr, o.tau, o.sigma_to_r, o.kernel, nullptr, {}};
     e = launch_eval(h->dev, a, o.algo, s);

@@ -118,22 +118,25 @@ pndf_status pndf_plan_create(const pndf_hier* h, int64_t max_nq, const pndf_eval
     const int resident = persist_resident_blocks(h->dev, P);
     if (resident > 0 && t.blocks_per_cu > resident) p->tuning.blocks_per_cu = resident;
     P.blocks = compute_units() * p->tuning.blocks_per_cu;
-    hipError_t e = hipMalloc(&P.ctl, sizeof(QueueCtl));
-    if (e == hipSuccess) e = hipMalloc(&P.acc, sizeof(Fix192) * (size_t)max_nq);
-    if (e == hipSuccess) e = hipMalloc(&P.fexp, sizeof(int) * (size_t)max_nq);
-    if (e == hipSuccess) e = hipMalloc(&P.tasks, sizeof(unsigned long long) * P.capacity);
-    if (e == hipSuccess) e = hipMalloc(&P.flags, sizeof(unsigned) * P.capacity);
+    hipError_t e = device_alloc((void**)&P.ctl, sizeof(QueueCtl));
+    if (e == hipSuccess) e = device_alloc((void**)&P.acc, sizeof(Fix192) * (size_t)max_nq);
+    if (e == hipSuccess) e = device_alloc((void**)&P.fexp, sizeof(int) * (size_t)max_nq);
+    if (e == hipSuccess) e = device_alloc((void**)&P.tasks, sizeof(unsigned long long) * P.capacity);
+    if (e == hipSuccess) e = device_alloc((void**)&P.flags, sizeof(unsigned) * P.capacity);
     if (e == hipSuccess && !(o.flags & PNDF_EVAL_INPUT_ORDER)) {
         // workers take the queries in spatial (Morton bucket) order
         order_shape(h->dev.logn, &P.order_nb, &P.order_bshift);
-        // ... and wide footprints run tiled (without the memory for it, as the others)
         const size_t tiles = tiles_bytes(h->dev, max_nq);
-        if (tiles && hipMalloc(&P.tile_mem, tiles) != hipSuccess) {
-            (void)hipGetLastError();
-            P.tile_mem = nullptr;
+        e = device_alloc((void**)&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + order_words(P.order_nb, tiles != 0)));
+        // ... and wide footprints run tiled (without the memory for it, as the others)
+        if (e == hipSuccess && tiles) {
+            if (device_alloc(&P.tile_mem, tiles) == hipSuccess) {
+                tiles_place(h->dev, max_nq, P.tile_mem, &P.tile);
+            } else {
+                (void)hipGetLastError();
+                P.tile_mem = nullptr;
+            }
         }
-        if (P.tile_mem) tiles_place(h->dev, max_nq, P.tile_mem, &P.tile);
-        e = hipMalloc(&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + order_words(P.order_nb, P.tile.ctl != nullptr)));
     }
     // flags start at 0; the first run publishes with epoch 1
     if (e == hipSuccess) e = hipMemsetAsync(P.flags, 0, sizeof(unsigned) * P.capacity, (hipStream_t)stream);
@@ -196,7 +199,7 @@ pndf_status pndf_autotune(const pndf_hier* h, const pndf_query* d_q, int64_t nq,
     if (nq < 1 || !d_q) return plan_invalid("autotuning needs a non-empty query sample");
     hipStream_t s = (hipStream_t)stream;
     float* d_out = nullptr;
-    hipError_t e = hipMalloc(&d_out, sizeof(float) * (size_t)nq);
+    hipError_t e = device_alloc((void**)&d_out, sizeof(float) * (size_t)nq);
     if (e != hipSuccess) return hip_fail(e, "pndf_autotune");
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);

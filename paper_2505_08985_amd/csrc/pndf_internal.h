@@ -417,15 +417,21 @@ namespace pndf {
 // cost about 0.3 ms together whatever their size, and memory that goes back to the
 // driver is cleared before it is handed out again (about 29 GB/s: 14 ms for a 2048^2
 // map's 0.4 GB when maps are loaded one after the other; 1.6 ms from kept blocks).
-// Released blocks are therefore kept for later handles: at most kBlockKeepShare of
-// the device's memory, none for longer than kBlockKeepSeconds past the next allocation
-// or release, and all of them go back when an allocation fails.  A block is kept only
-// once the device is idle (as hipFree itself waits), so any stream may have it next.
-// Safe from several threads.  block_alloc uses the current device.
+// Released blocks are therefore kept for later handles: at most 1 / kBlockKeepShare of
+// the device's memory, none for longer than kBlockKeepSeconds (a thread of the library
+// frees them, which exists while there are any; a hipFree that waits for the device
+// does not hold up other threads), and all of them go back when an allocation of the library
+// fails.  A block is kept only once the device is idle (as hipFree itself waits), so any stream
+// may have it next.  Safe from several threads.  block_alloc uses the current device.
 constexpr size_t kBlockKeepShare = 128;   // 1 / 128
-constexpr double kBlockKeepSeconds = 10.0;
+#ifndef PNDF_BLOCK_KEEP_SECONDS
+#define PNDF_BLOCK_KEEP_SECONDS 10.0
+#endif
+constexpr double kBlockKeepSeconds = PNDF_BLOCK_KEEP_SECONDS;
 hipError_t block_alloc(size_t bytes, void** p);
 void block_free(void* p);
+// hipMalloc, tried once more without what the library keeps on the device.
+hipError_t device_alloc(void** p, size_t bytes);
 
 // Workspace of one call, in stream order: the call's stream may write it at once, and
 // stream_free gives it back behind what that stream has by then.  The driver's
@@ -439,13 +445,12 @@ void block_free(void* p);
 // with one from the default pool; 16 served tiles of them: 0.60, 1.65 and 0.75 ms.  At
 // most kStreamKeep bytes per device are kept (the largest workspace, of a round of 2^19
 // wide queries in a batch of 2^24, is 0.5 GB), until the last handle on the device is
-// released or a map finds no memory.  Safe from several threads.  Under capture, and on a
+// released or an allocation of the library fails.  Safe from several threads.  Under capture, and on a
 // stream of another device than the current one, the driver's calls serve (under capture
 // they become nodes of the graph).
 constexpr uint64_t kStreamKeep = (uint64_t)512 << 20;
 hipError_t stream_alloc(void** p, size_t bytes, hipStream_t s);
 void stream_free(void* p, hipStream_t s);
-void spaces_drop(int dev);   // gives the kept ones back whose calls are over
 // Lays arrays out in one allocation (256 B aligned): sizes first, then pointers.
 struct Arena {
     char* base = nullptr;

@@ -399,8 +399,8 @@ pndf_status pndf_server_create(const pndf_hier* const* maps, int32_t nmaps, cons
     for (Slot& sl : s->slots) {
         hipError_t e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipMalloc(&sl.d_q, sizeof(pndf_query) * (size_t)o.max_batch_queries);
-        if (e == hipSuccess) e = hipMalloc(&sl.d_out, sizeof(float) * (size_t)o.max_batch_queries);
+        if (e == hipSuccess) e = pndf::device_alloc((void**)&sl.d_q, sizeof(pndf_query) * (size_t)o.max_batch_queries);
+        if (e == hipSuccess) e = pndf::device_alloc((void**)&sl.d_out, sizeof(float) * (size_t)o.max_batch_queries);
         if (e != hipSuccess) {
             st = pndf::hip_fail(e, "pndf_server_create");
             break;

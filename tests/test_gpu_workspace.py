@@ -152,3 +152,25 @@ def test_calls_on_four_streams_cost_what_one_costs():
     four = best(lambda k: P.eval_batch(h, q, tau=1e-3, out=out[k % 4], stream=streams[k % 4]))
     print("per call: %.1f us on one stream, %.1f on four" % (one / 64 * 1e6, four / 64 * 1e6))
     assert four < 1.8 * one
+
+
+@pytest.mark.parametrize("wait", [0, 13])
+def test_kept_blocks_go_back(wait):
+    """The blocks of a released 1024^2 map (90 MB and more) stay for the next map, and go back to
+    the driver after ten seconds without any further call; a process that ends earlier ends
+    as it should."""
+    code = """
+import sys, time; sys.path[:0] = ['tests', '.']
+import torch, paper_2505_08985_amd as P
+from test_gpu_blocks import load
+torch.cuda.synchronize()
+load(P, 64, 3, True)
+h = load(P, 1024, 3, True); h.mesh.close(); h.close(); torch.cuda.synchronize()
+kept = torch.cuda.mem_get_info()[0]
+time.sleep(%d)
+print((torch.cuda.mem_get_info()[0] - kept) >> 20)
+""" % wait
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    back = int(r.stdout.split()[-1])
+    assert back >= 90 if wait else back == 0, back
