@@ -1223,9 +1223,12 @@ __global__ __launch_bounds__(64) void k_eval_tiles(HierDev H, EvalArgs a)
     const int lane = lane_id();
     const uint32_t total = T.ctl->total;
     if (total == 0) return;
-    // (fewer of few items, which are whole nodes or the batch's last work: 8192 queries at 8192^2
-    // 4.1 and 3.5 ms; a quarter as many is too many claims, 5.2 ms for 4.4 at 2048^2)
-    const uint32_t most = max(1u, min(kTileClaim, total / (4u * gridDim.x)));
+    batch_args(a);
+    // (shorter claims of few items, which the batch waits for at its end, and shortest where
+    // queries left up to four of them, whole nodes: 131072 queries at 4096^2, tau = 1e-3, 11.2 and
+    // 10.5 ms; items of one tile are too short for so many claims: 8192 queries at 2048^2
+    // 1.6 and 3.3 ms)
+    const uint32_t most = max(1u, min(kTileClaim, total / ((total / 4u < tile_range(a).count ? 16u : 4u) * gridDim.x)));
     TaskQueue none{};
     Rec rec{nullptr, nullptr, 0, 0};
     int x = 0;
@@ -1783,7 +1786,7 @@ __device__ __forceinline__ void order_narrow(const OrderArgs& o, int64_t nq, con
     const uint32_t narrow = first[o.nb], heavy = first[o.nb + (o.nb >> kOrderWideShift)];
     const uint32_t tiled = (uint64_t)nq - narrow > (o.logn > 11 ? 2 * kLightMin : kLightMin) ? heavy : narrow;
     o.narrow[0] = tiled;
-    o.narrow[1] = ((uint64_t)nq - tiled) << (2 * (o.logn - kTileLevel)) > (tiled == narrow ? 4 * kTileFine : kTileFine);
+    o.narrow[1] = ((uint64_t)nq - tiled) << (2 * (o.logn - kTileLevel)) > (tiled == narrow ? 3 * kTileFine : kTileFine);
     o.narrow[2] = narrow;
 }
 

@@ -224,10 +224,11 @@ struct QuerySetup;
 // 158 -> 47 ms at any span, L2 misses 7.7e9 -> 4e7, the vector ALU then always busy.
 //
 // A batch of few wide queries has every item one tile: a whole node's item is one wave's work
-// and decides when the batch ends.  Wide queries x tiles up to 4 kTileFine (tau = 1e-3, sigma 90
+// and decides when the batch ends.  Wide queries x tiles up to 3 kTileFine (tau = 1e-3, sigma 90
 // to an eighth of the map, with items of whole nodes and with tiles alone): 8192 queries at
 // 2048^2 2276 and 1533 us; 128 at 8192^2 1714 and 456 us, 8192 3.7 and 4.0 ms, 16384 5.5 and
-// 7.1.  Without the light queries (see OrderArgs), which are most of those that whole nodes make
+// 7.1; 10000 at 4096^2 (sigma 90 to 1000) 5.1 and 3.7 ms, 16384 of sigma 90 to 4000 5.0 and 6.1.
+// Without the light queries (see OrderArgs), which are most of those that whole nodes make
 // long, up to kTileFine: 15000 others at 4096^2 9.6 and 12.5 ms.
 constexpr int kTileLevel = 8;
 constexpr int kTileDepth = 3, kTileSpan = 9;
