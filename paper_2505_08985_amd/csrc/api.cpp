@@ -80,11 +80,8 @@ static void fill_view(pndf_hier* h)
     d.nrm = m->nrm;
     d.deg = m->deg;
     d.det = m->det;
-    d.bbox = h->bbox;
-    d.bbox_all = h->bbox_all;
     d.clu_t = h->clu_t;
     d.clu_e = h->clu_e;
-    d.clu_det = h->clu_det;
     d.oct_k = h->oct_k;
     d.oct_c = h->oct_c;
     d.clu_em = h->clu_em;

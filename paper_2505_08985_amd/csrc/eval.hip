@@ -2115,8 +2115,6 @@ int persist_resident_blocks(const HierDev& H, const PersistPlan& P)
     return nb;
 }
 
-
-
 // The tile kernels for a plan's or call's cut setting and footprint kernel.
 struct TileFuncs {
     void *emit, *tiles;

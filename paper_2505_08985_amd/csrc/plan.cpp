@@ -125,9 +125,10 @@ pndf_status pndf_plan_create(const pndf_hier* h, int64_t max_nq, const pndf_eval
     if (e == hipSuccess) e = device_alloc((void**)&P.flags, sizeof(unsigned) * P.capacity);
     if (e == hipSuccess && !(o.flags & PNDF_EVAL_INPUT_ORDER)) {
         // workers take the queries in spatial (Morton bucket) order
-        order_shape(h->dev.logn, &P.order_nb, &P.order_bshift);
+        int nb, bshift;
+        order_shape(h->dev.logn, &nb, &bshift);
         const size_t tiles = tiles_bytes(h->dev, max_nq);
-        e = device_alloc((void**)&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + order_words(P.order_nb, tiles != 0)));
+        e = device_alloc((void**)&P.order, sizeof(uint32_t) * (2 * (size_t)max_nq + order_words(nb, tiles != 0)));
         // ... and wide footprints run tiled (without the memory for it, as the others)
         if (e == hipSuccess && tiles) {
             if (device_alloc(&P.tile_mem, tiles) == hipSuccess) {

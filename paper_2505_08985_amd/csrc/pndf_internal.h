@@ -90,9 +90,18 @@ static_assert(sizeof(QuadRec) == 80, "QuadRec is five 16-byte words");
 struct HierDev {
     const float2* nrm;      // (n+1) x (n+1) padded texel normals (last row/column wrap)
     const uint8_t* deg;     // n x n clamp bits (bit0 lower, bit1 upper)
-    const float2* det;      // n x n Jacobians used by the evaluation (lower, upper)
-    const float4* bbox;     // all levels packed: min x, min y, max x, max y (map triangles)
-    const float4* bbox_all; // same, extended by cluster triangles (nullptr without clusters)
+    const float2* det;      // n x n Jacobians (lower, upper), eps when clamped (projected area)
+    const QuadRec* quad;    // level-1 leaf records (Morton order)
+    // the cluster test record, 2 float4 per node: (N0.x, N0.y, N1.x, N1.y), (N2.x,
+    // N2.y, N3.x, N3.y), except that a clamped triangle's free vertex (N0 of the
+    // lower, N3 of the upper: its replacement is built from the shared edge N1 N2
+    // alone) holds NaN, so the record carries the clamp bits (clamp_bits)
+    const float4* clu_t;
+    const float* clu_e;     // e^l per node
+    int n, L, logn;
+    float eps;
+    float rho;              // circumradius of the clamp replacement triangle (area eps / 2)
+    uint32_t nodes;         // nodes of all levels
     // octagons of the traversal (see Octagon): oct_k the map triangles beneath the node
     // (tau = 0); with clusters oct_c holds three arrays of `nodes` octagons, indexed
     // cls * nodes + node: kOctSub the map and cluster triangles beneath the node,
@@ -101,21 +110,9 @@ struct HierDev {
     const uint4* oct_k;
     const uint4* oct_c;
     const float2* clu_em;   // per node e^l and the largest e^l of its four children (+inf at level 1)
-    // the cluster test record, 2 float4 per node: (N0.x, N0.y, N1.x, N1.y), (N2.x,
-    // N2.y, N3.x, N3.y), except that a clamped triangle's free vertex (N0 of the
-    // lower, N3 of the upper: its replacement is built from the shared edge N1 N2
-    // alone) holds NaN, so the record carries the clamp bits (clamp_bits)
-    const float4* clu_t;
-    const float* clu_e;     // e^l per node
     const float2* tile_e;   // maps with tiles: per node of level kTileLevel and above (packed like the others, from
                             // level kTileLevel on) the largest e^l kTileDepth and kTileSpan levels beneath
     const float* level_e;   // with tiles, per level from 1: logarithm (base 2) of a middle residual
-    const float2* clu_det;  // cluster triangle Jacobians (lower, upper), eps when clamped
-    const QuadRec* quad;    // level-1 leaf records (Morton order)
-    uint32_t nodes;         // nodes of all levels
-    int n, L, logn;
-    float eps;
-    float rho;              // circumradius of the clamp replacement triangle (area eps / 2)
 };
 
 // Clamp bits of a cluster test record (a, b) = clu_t[2 idx], clu_t[2 idx + 1]: bit 0
@@ -336,7 +333,7 @@ struct PersistPlan {
     unsigned int* flags = nullptr;
     unsigned long long capacity = 0;
     uint32_t* order = nullptr;  // order[max_nq] | key[max_nq] | order_words(...) counters (nullptr: input order)
-    int order_nb = 0, order_bins = 0, order_bshift = 0;
+    int order_bins = 0;
     void* tile_mem = nullptr;
     TileWork tile{};            // wide queries run tiled on maps with tiles (ctl nullptr: none)
     std::vector<EvalArgs> targs;  // per round: arguments of its tile kernels
