@@ -35,3 +35,27 @@ def test_gaussian_draw_tails(oracle_mod, s2r, sigma):
     ok = (ref["flags"] & 2) == 0
     assert ok.mean() > 0.5
     np.testing.assert_array_equal(tri.cpu().numpy().view(np.uint64)[ok], ref["tri"][ok])
+
+
+@pytest.mark.parametrize("sigma", [0.6, 9.0, 300.0])
+def test_gaussian_draw_centre(oracle_mod, sigma):
+    """Away from the tails (|z| < 3): both sides' probabilities are within 4e-15 (the table's
+    relative error of 3e-15 at 1/2, two roundings), which the quantile's slope 1 / phi(z) turns into
+    u's error; 1e-13 for the roundings of u itself."""
+    import torch
+    import workloads
+    import paper_2505_08985_amd as P
+    nrm = workloads.make_map("powerlaw", 64, 7)
+    hier = P.build_hierarchy(P.build_mesh(torch.from_numpy(nrm).cuda()), cluster=False)
+    rng = np.random.default_rng(13)
+    xi = rng.uniform(0.002, 0.998, (4000, 2))
+    q = np.zeros((4000, 6), np.float32)
+    q[:, :2] = rng.uniform(0, 64, (4000, 2))
+    q[:, 2:4] = sigma * np.exp(rng.uniform(-0.2, 0.2, (4000, 2)))
+    _, _, u = P.sample_batch(hier, torch.from_numpy(q).cuda(), torch.from_numpy(xi[None]).cuda(), u=True)
+    ref = oracle_mod.sample(nrm, q, xi)["u"]
+    z = (ref - q[:, :2]) / q[:, 2:4]
+    assert np.abs(z).max() < 3.5
+    tol = 2 * 4e-15 * np.sqrt(2 * np.pi) * np.exp(0.5 * z * z) * q[:, 2:4] + 1e-13 * np.maximum(1.0, q[:, 2:4] / 64)
+    err = np.abs(u.cpu().numpy() - ref)
+    assert (err <= tol).all(), float((err / tol).max())

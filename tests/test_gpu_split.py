@@ -61,3 +61,23 @@ def test_split_footprint_kernels(hier, kernel):
         want, _ = P.eval_counts(hier, q, tau=tau, kernel=kernel, sigma_to_r=1.5)
         got = P.eval_batch(hier, q, tau=tau, kernel=kernel, sigma_to_r=1.5)
         assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+
+
+@pytest.mark.parametrize("nq", [16, 256, 1000])
+def test_split_largest_map(nq):
+    """The deepest lists: sixteen and four waves of them in a workgroup's LDS."""
+    import torch
+    import paper_2505_08985_amd as P
+    g = torch.Generator(device="cuda").manual_seed(5)
+    k = torch.arange(8192, device="cuda") * (2 * np.pi / 8192)
+    nrm = 0.05 * torch.randn(8192, 8192, 2, generator=g, device="cuda")
+    nrm[..., 0] += 0.3 * torch.sin(3 * k)[None, :]
+    nrm[..., 1] += 0.3 * torch.cos(2 * k)[:, None]
+    hier = P.build_hierarchy(P.build_mesh(nrm.clamp_(-0.6, 0.6)), cluster=True)
+    q = torch.from_numpy(queries(8192, nq, 7, 0.5)).cuda()
+    q[:, 2:4] = q[:, 2:4].clamp(max=400.0)
+    for tau in (0.0, 1e-3):
+        want, _ = P.eval_counts(hier, q, tau=tau)
+        got = P.eval_batch(hier, q, tau=tau)
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32))
+        assert bool((got > 0).any())
