@@ -31,6 +31,15 @@
  *     cell-centre normal n(floor(u) + 1/2) = (n1 + n2)/2 (section "Preventing
  *     Jacobian singularity", Eq. debias); its vertices sit at 90, 210, 330 degrees,
  *     assigned to the triangle's (a, b, c).
+ *   - Device memory beside the handles': batches of 4096 or more evaluated queries and
+ *     launches of more than 4096 projected areas take a workspace of 8 bytes per query;
+ *     on maps of 1024^2 and more an evaluation adds one for the wide queries, for
+ *     n = min(nq, 2^19) queries 32 n (N / 256)^2 bytes, at most 268 MB, and about 160 n
+ *     (without the memory for it they run as the others).  Workspaces that
+ *     calls have used are kept for later calls, at most 512 MB per device, until the last
+ *     mesh or hierarchy on the device is released; the memory of a released handle, if at
+ *     most 1/128 of the device's in all, is kept for ten seconds.  Both go back to the
+ *     driver before an allocation of the library fails.
  *   - Device pointers are HIP device (HBM) addresses; `stream` is a hipStream_t
  *     (NULL = the default stream).  Every call returns a pndf_status and never
  *     aborts; pndf_last_error() gives a thread-local message for the last failure.
@@ -97,9 +106,11 @@ typedef struct pndf_eval_opts {
 } pndf_eval_opts;
 
 /* Batches of 4096 or more queries are processed in a spatial order (Morton buckets
- * of the footprint centres) for cache locality, and on maps of 1024^2 and more the
- * wide ones among them (support half-width above 256 texels) tile by tile; results do
- * not depend on either.  This flag keeps the caller's order and whole queries. */
+ * of the footprint centres) for cache locality, and on maps of 1024^2 and more wide ones
+ * among them (support half-width above 256 texels; in batches of many of them those that
+ * the cut leaves enough work) tile by tile.  This flag keeps the caller's order and does
+ * without tiles.  Batches of at most 1024 queries share each query among several
+ * wavefronts, with or without it.  Results do not depend on any of this. */
 enum { PNDF_EVAL_INPUT_ORDER = 1 };
 
 typedef struct pndf_hier_opts {
@@ -252,9 +263,9 @@ pndf_status pndf_sample_batch(const pndf_hier* h, const pndf_query* d_q, int64_t
  *  d_P       device, nq floats: P(w); NaN for an invalid query (as for the
  *            evaluation) or w_x^2 + w_y^2 > 1.
  *  d_lambda  device, nq floats: Lambda(w) (+inf at w_z = 0); may be NULL.
- * Queries run heaviest first (by their number of included cells), which changes
- * no result; the order's workspace (8 bytes per query) is allocated and freed
- * stream-ordered.  Asynchronous on `stream`; deterministic.
+ * Batches of more than 4096 queries run heaviest first (by their number of included
+ * cells), smaller ones several wavefronts to a query; neither changes a result beyond
+ * the rounding of the FP64 sum.  Asynchronous on `stream`; deterministic.
  */
 pndf_status pndf_projected_area(const pndf_hier* h, const pndf_query* d_q, int64_t nq, const pndf_eval_opts* opts,
                                 float* d_P, float* d_lambda, void* stream);
@@ -281,9 +292,11 @@ const char* pndf_last_error(void);
  * bit-identical to pndf_eval_batch whatever the split, the schedule or the batch
  * composition.  The launch sequence (reset, spatial order, workers, finalize) is
  * instantiated once as a HIP graph and replayed per batch.  On maps of 1024^2 and
- * more, with the spatial order, queries wider than 256 texels are evaluated tile by
- * tile instead (as pndf_eval_batch does), in further launches of the same sequence;
- * the statistics below count the workers' queries alone.
+ * more, with the spatial order, wide queries are evaluated tile by tile instead (as
+ * pndf_eval_batch does), in further launches of the same sequence; the statistics
+ * below count the workers' queries alone.  A plan holds 28 + 12 queue_factor bytes
+ * of device memory per query of max_nq, with the spatial order 8 more and the wide queries'
+ * workspace (see above: 270 MB from 8192 queries on at 8192^2).
  */
 typedef struct pndf_plan pndf_plan;
 
@@ -312,7 +325,7 @@ pndf_status pndf_default_tuning(const pndf_hier* h, pndf_tuning* out);
 /*
  * Create a plan for batches of at most max_nq (>= 1) queries with the given options
  * (opts->algo is ignored) and tuning (NULL: pndf_default_tuning).  The hierarchy must
- * outlive the plan.  Allocates device memory; synchronises `stream`.
+ * outlive the plan.  Allocates device memory (see above); synchronises `stream`.
  */
 pndf_status pndf_plan_create(const pndf_hier* h, int64_t max_nq, const pndf_eval_opts* opts,
                              const pndf_tuning* tuning, void* stream, pndf_plan** out);
@@ -376,7 +389,8 @@ typedef struct pndf_server_opts {
     pndf_tuning tuning;         /* persistent-plan tuning (blocks_per_cu = 0: default) */
     int32_t algo;               /* evaluation of a batch: PNDF_ALGO_PLAIN (or AUTO): one
                                  * pndf_eval_batch on the slot's stream; PNDF_ALGO_PERSISTENT:
-                                 * the slot's persistent plan for the batch's map */
+                                 * the slot's persistent plan for the batch's map (one plan of
+                                 * max_batch_queries, with its memory, per slot and map) */
     int32_t kernel;             /* footprint kernel of every request (pndf_kernel) */
     int64_t chunk_queries;      /* largest piece of one request in one batch (0: whole requests) */
 } pndf_server_opts;

@@ -2153,7 +2153,7 @@ static hipError_t tile_round(const HierDev& H, EvalArgs& a, const TileFuncs& f, 
 }
 
 // Rounds of a batch's wide queries (their number is known on the device only: a round
-// without any costs its five launches, 23 us).  As many as hold all queries; in large
+// without any costs its five launches, 13 us).  As many as hold all queries; in large
 // batches twice that, so that rounds may be smaller where queries leave many items.
 static int64_t tile_rounds(int64_t nq, int64_t round)
 {

@@ -102,7 +102,7 @@ struct HierDev {
     float eps;
     float rho;              // circumradius of the clamp replacement triangle (area eps / 2)
     uint32_t nodes;         // nodes of all levels
-    // octagons of the traversal (see Octagon): oct_k the map triangles beneath the node
+    // octagons of the traversal (see kOctSub): oct_k the map triangles beneath the node
     // (tau = 0); with clusters oct_c holds three arrays of `nodes` octagons, indexed
     // cls * nodes + node: kOctSub the map and cluster triangles beneath the node,
     // kOctOwn its own two cluster triangles, kOctKids (from level 2) the union of its
@@ -290,7 +290,7 @@ struct PersistArgs {
 // Arguments of the spatial order's passes.  With tiles, the buckets from nb on hold the
 // wide queries, 8 x 8 coarser than the others' (k_tile_emit reads the upper levels only,
 // and its items are sorted by tile).  As many as the others have made the passes
-// longer (a 16384-query tile 188 us, with a scan by barriers instead of shuffles; now 180) and
+// longer (a 16384-query tile 188 us and 180) and
 // gained nothing (60001 wide queries 46.8 and 46.9 ms).
 //
 // Wide queries that the cut leaves few nodes lose by tiles, whose items cost more than such

@@ -95,8 +95,9 @@ __device__ __forceinline__ double arc_prim_diff(double a, double b)
 //   d_y / 2 [w_z (P_x + Q_x) - w_l (p + q + (asin(z) / z - 1) Y / l^2)]
 //     = d_y / 2 [w_z (P_x + Q_x) - w_l (p + q + Y (Y / E)^2 C(z^2))],
 // C(u) = (asin(z) / z - 1) / u at u = z^2: the trapezoid rule and its correction, all
-// terms of one sign, without a square root, an arcsine or a cancellation.  C is a fit of
-// degree 8 on [0, 0.1], 1.1e-16 off at most.  *ok is false beyond it (jumps of a
+// terms of one sign, without a square root, an arcsine or a cancellation.  C is the polynomial
+// of degree 8 that interpolates it at the 9 Chebyshev nodes of [0, 0.1] (from the series of
+// the arcsine, in 60 decimal digits), 1.1e-16 off at most.  *ok is false beyond it (jumps of a
 // scratched map), where the segment is longer than rho (the angle may then pass pi / 2)
 // and where it hugs the circle: the triangle is then left to far_round.
 __device__ __forceinline__ double segment_short(double px, double py, double p, double qx, double qy, double q, double wl,

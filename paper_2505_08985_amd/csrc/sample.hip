@@ -63,9 +63,12 @@ __device__ __forceinline__ double normal_cdf(const double* tab, double z)
 
 // The standard normal quantile at the tail probability r = Phi(-t) in [kLeastTail,
 // 1/2]: t.  First in float32, t = (1 - 2 r) P(w) with w = -log(4 r (1 - r)) (the
-// variable in which the quantile is nearly a polynomial; P is a fit of degree 10 in
-// w - 5, 1.6e-6 off at most), then one third-order step on Phi(-t) - r, which leaves
-// less than 1e-16 of that.
+// variable in which the quantile is nearly a polynomial: M. Giles, "Approximating the
+// erfinv function", GPU Computing Gems, 2011), then one third-order step on
+// Phi(-t) - r, which leaves less than 1e-16 of that.  P, of degree 10 in w - 5, is a
+// weighted least-squares fit of t / (1 - 2 r) over 120001 values of t in [1e-4, 4.25],
+// weights 1 - 2 r multiplied 200 times by (1/2 + error / largest error)^0.7 towards equal
+// errors, the best of them: 1.6e-6 off at most.
 constexpr double kLeastTail = 1.1e-5;  // t <= 4.24
 __device__ __forceinline__ double normal_tail_quantile(const double* tab, double r)
 {
