@@ -20,9 +20,13 @@ sample from the GPU (the hit set is fixed by the definition), and priced as
     bytes  B = 24 (query) + 4 (D) + 16 nodes + 8 cells + 36 clusters
     ops    F = 12 nodes + 40 cells + 40 clusters + 30 hits   (32-bit lane operations)
 against 8 TB/s and 256 CUs x 64 lanes x 2.4 GHz = 39.3 T lane-ops/s.  The
-duration is measured with HIP events on the stream the kernel runs on.  HBM
-traffic comes from rocprofv3 FETCH_SIZE / WRITE_SIZE runs recorded under
-profiles/ (null when the kernel source changed since they were taken).
+duration is measured with HIP events on the stream the kernel runs on.  These are the
+work of the method with boxes; octagons and tiles do with less of it.  So where
+rocprofv3 counters of this source and batch are recorded under profiles/, the roofline is
+the measured one: HBM traffic (FETCH_SIZE, WRITE_SIZE) and issued vector instructions
+(SQ_INSTS_VALU, 64 lane operations each) over the same duration, "basis": "counters".
+Otherwise (the kernel source changed since they were taken) the basis is the
+algorithmic work, whose bytes bound nothing on maps that run tiled.
 """
 import argparse
 import hashlib
@@ -58,9 +62,10 @@ def traffic_file(workload, algo):
     return os.path.join(ROOT, "profiles", "traffic_eval_%s_%s.json" % (algo, workload))
 
 
-def load_traffic(workload, algo, kernel="gaussian", sigma_to_r=3.0, queries=None):
-    """The measured HBM bytes per launch, if the committed counters were taken on this
-    source and this exact launch: the workload's own batch at the default support."""
+def load_counters(workload, algo, kernel="gaussian", sigma_to_r=3.0, queries=None):
+    """The measured HBM bytes and vector instructions per launch, if the committed counters
+    were taken on this source and this exact launch: the workload's own batch at the
+    default support."""
     path = traffic_file(workload, algo)
     if not os.path.exists(path):
         return None
@@ -73,7 +78,7 @@ def load_traffic(workload, algo, kernel="gaussian", sigma_to_r=3.0, queries=None
             or t.get("kernel", "gaussian") != kernel or sigma_to_r != 3.0
             or queries != workloads.CONFIGS[workload]["queries"]["count"] or t.get("queries") != queries):
         return None
-    return float(t["hbm_bytes_per_launch"])
+    return t
 
 
 def build_workcount(force=False):
@@ -757,15 +762,22 @@ def measure(P, workload, args, steps, warmup, algo="plain", octaves=True):
 
     work = algorithmic_work(P, hier, q, tq, n, tau, s2r, kw)
     abytes, aops = work["algorithmic_bytes_per_launch"], work["algorithmic_alu_ops_per_launch"]
+    counters = load_counters(workload, algo, kern, s2r, count)
+    traffic = float(counters["hbm_bytes_per_launch"]) if counters else None
+    measured = counters is not None and "valu_insts_per_launch" in counters
+    if measured:
+        abytes, aops = traffic, 64.0 * float(counters["valu_insts_per_launch"])
     achieved = abytes / (kernel_ms * 1e-3) / 1e9
     achieved_ops = aops / (kernel_ms * 1e-3) / 1e12
-    traffic = load_traffic(workload, algo, kern, s2r, count)
+    basis = "counters" if measured else "algorithmic"
     hbm = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-           "frac": achieved / HBM_PEAK_GBS, "traffic": traffic}
+           "frac": achieved / HBM_PEAK_GBS, "traffic": traffic, "basis": basis}
     alu = {"bound": "alu", "achieved": achieved_ops, "peak": ALU_PEAK_TOPS, "unit": "Tops/s",
-           "frac": achieved_ops / ALU_PEAK_TOPS, "traffic": traffic}
-    # the binding roofline is the one the launch comes closer to
-    roof, alt = (hbm, alu) if hbm["frac"] >= alu["frac"] else (alu, hbm)
+           "frac": achieved_ops / ALU_PEAK_TOPS, "traffic": traffic, "basis": basis}
+    # the binding roofline is the one the launch comes closer to (tiles read less than the
+    # algorithmic bytes)
+    tiled = algo != "brute" and n >= 1024
+    roof, alt = (hbm, alu) if hbm["frac"] >= alu["frac"] and (measured or not tiled) else (alu, hbm)
 
     oct_rates = None
     if octaves:

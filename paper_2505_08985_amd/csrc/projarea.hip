@@ -33,8 +33,8 @@
 // memory).  The pieces of V's boundary, which few edges leave, wait once more, 64 to a
 // round.  The footprint weight at a cell's centroids is a product of two factors that
 // depend on its column and its row alone, formed once per query in LDS.
-// Bound by FP64 vector instructions (82 % of the issue slots): 65536 queries of sigma 1
-// to 8 on the 2048^2 power-law map take 1055 us and 7240 instructions per wavefront,
+// Bound by FP64 vector instructions (78 % of the issue slots): 65536 queries of sigma 1
+// to 8 on the 2048^2 power-law map take 1070 us and 7400 instructions per wavefront,
 // against 1312 us and 10090 with arcsines for every segment, weights per cell and a
 // triangle per lane in the clipping.
 #include <algorithm>
